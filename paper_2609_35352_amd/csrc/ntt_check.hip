@@ -74,8 +74,8 @@ struct Checker {
     }
     return &sets_host[(a - sets_dev) / sizeof(NttSet)];
   }
-  bool tables(const NttSet &S, const Tw *dft, uint32_t logm) {
-    return span("DFT twiddles", (uint64_t)dft, 0, (uint64_t)(1u << logm) / 2 * sizeof(Tw), nullptr);
+  bool tables(const Tw *dft, uint32_t n) {
+    return span("transform twiddles", (uint64_t)dft, 0, (uint64_t)n * sizeof(Tw), nullptr);
   }
 };
 
@@ -86,23 +86,23 @@ bool pass_a(Checker &C, const PassLaunch &L) {
   const NttPass &P = L.P;
   const uint32_t N1 = 1u << P.log_n1, N2 = D::M, gx = N1 / kNttCols;
   if (P.log_n1 != L.log_other || N1 < kNttCols) return C.fail("pass A: bad sides");
-  const bool trans = P.load == fiona::kLoadU64T;
+  const bool trans = P.load == fiona::kLoadU64T, blocked = P.load == fiona::kLoadF64;
   // per column block: the largest ends of the accesses relative to each descriptor's base
-  std::vector<uint64_t> in_hi(gx, 0), pre_hi(gx, 0), tmp_hi(gx, 0), mid_hi(gx, 0);
+  std::vector<uint64_t> in_hi(gx, 0), tmp_hi(gx, 0), mid_hi(gx, 0);
   for (uint32_t cb = 0; cb < gx; ++cb) {
     for (uint32_t it = 0; it < D::IT1; ++it) {
       const uint32_t cl = G::col(it, trans), ip = G::grp(it, trans), n1 = cb * kNttCols + cl;
       for (uint32_t u = 0; u < 16; ++u) {
-        if (!C.grow(in_hi[cb], trans ? G::in_t(n1, ip, u, N1) : G::in(n1, ip, u, N1), 8, "pass A input"))
+        if (!C.grow(in_hi[cb], blocked ? G::in_b(cb, cl, ip, u) : trans ? G::in_t(n1, ip, u, N1) : G::in(n1, ip, u, N1),
+                    8, "pass A input"))
           return false;
-        if (!trans && !C.grow(pre_hi[cb], G::pre(ip, u), 16, "pass A pre")) return false;
       }
     }
     for (uint32_t it = 0; it < D::IT2; ++it) {
       const uint32_t cl = G::col2(it), o = G::off2(it), n1 = cb * kNttCols + cl;
       for (uint32_t u = 0; u < D::E2; ++u)
         if (!C.grow(tmp_hi[cb], G::tmp(o, n1, u, N1), 8, "pass A tmp") ||
-            !C.grow(mid_hi[cb], G::mid(o, n1, u, N1), 16, "pass A mid"))
+            !C.grow(mid_hi[cb], G::mid(cb, cl, o, u), 8, "pass A mid"))
           return false;
     }
   }
@@ -113,16 +113,12 @@ bool pass_a(Checker &C, const PassLaunch &L) {
       if (!S) return false;
       const uint64_t v = (uint64_t)un.set * P.vps + un.lv;
       const uint64_t in_base = (uint64_t)P.in + (un.set * P.in_set_stride + un.lv * P.in_stride) * 8;
-      const uint64_t tmp_base = (uint64_t)P.tmp + v * N1 * N2 * 8;
+      const uint64_t tmp_base = (uint64_t)P.tmp + v * fiona::tmp_words(N1, N2) * 8;
       if (!C.span("pass A input", in_base, 0, in_hi[un.cb], P.in_end) ||
           !C.span("pass A tmp", tmp_base, 0, tmp_hi[un.cb], P.tmp_end) ||
           !C.span("pass A mid", (uint64_t)S->mid, 0, mid_hi[un.cb], nullptr) ||
-          !C.span("pass A mid table", (uint64_t)S->mid, 0, (uint64_t)N1 * N2 * sizeof(Tw), nullptr) ||
-          !C.tables(*S, S->dft_a, LOGM))
-        return false;
-      if (!trans && S->pre &&
-          (!C.span("pass A pre", (uint64_t)S->pre, 0, pre_hi[un.cb], nullptr) ||
-           !C.span("pass A pre table", (uint64_t)S->pre, 0, (uint64_t)N2 * sizeof(Tw), nullptr)))
+          !C.span("pass A mid table", (uint64_t)S->mid, 0, (uint64_t)N1 * N2 * sizeof(double), nullptr) ||
+          !C.tables(S->dft_a, blocked ? D::M : D::M / 2))
         return false;
     }
   return true;
@@ -135,8 +131,7 @@ bool pass_b(Checker &C, const PassLaunch &L) {
   const NttPass &P = L.P;
   const uint32_t M = D::M, N2 = 1u << P.log_n2, gx = N2 / kNttCols;
   if (P.log_n2 != L.log_other || N2 < kNttCols) return C.fail("pass B: bad sides");
-  const bool transposed = P.out_transposed != 0 && P.store != fiona::kStoreF64;
-  const bool rescale = P.store == fiona::kStoreRescale;
+  const bool transposed = P.store == fiona::kStoreU64T, rescale = P.store == fiona::kStoreRescale;
   uint64_t tmp_hi = 0;
   for (uint32_t it = 0; it < D::IT1; ++it)
     for (uint32_t u = 0; u < 16; ++u)
@@ -151,19 +146,22 @@ bool pass_b(Checker &C, const PassLaunch &L) {
         if (!C.grow(post_hi, G::post(o, u), 16, "pass B post")) return false;
         const Off oc = G::col(k2, o, u, N2);
         if (rescale && !C.grow(base_hi[x], oc, 8, "pass B base")) return false;
-        if (!C.grow(out_hi[x], transposed ? G::row_t(k2, o, u) : oc, 8, "pass B output")) return false;
+        if (!C.grow(out_hi[x], transposed ? G::row_t(k2, o, u) : rescale ? oc : G::block(k2, o, u, N2), 8,
+                    "pass B output"))
+          return false;
       }
     }
   }
   for (uint32_t by = 0; by < L.V; ++by) {
     const uint32_t set = by / P.vps, lv = by - set * P.vps;
     const NttSet *S = C.set(P.sets, set);
-    if (!S || !C.tables(*S, S->dft_b, LOGM)) return false;
+    if (!S || !C.tables(S->dft_b, D::M / 2)) return false;
     if (S->post && (!C.span("pass B post", (uint64_t)S->post, 0, post_hi, nullptr) ||
                     !C.span("pass B post table", (uint64_t)S->post, 0, (uint64_t)M * sizeof(Tw), nullptr)))
       return false;
     for (uint32_t x = 0; x < gx; ++x) {
-      const uint64_t tmp_base = (uint64_t)P.tmp + ((uint64_t)by * N2 * M + (uint64_t)x * kNttCols * M) * 8;
+      const uint64_t tmp_base = (uint64_t)P.tmp + ((uint64_t)by * fiona::tmp_words(M, N2) +
+                                                   (uint64_t)x * kNttCols * fiona::tmp_pitch(M)) * 8;
       const uint64_t out_base = (uint64_t)P.out + (set * P.out_set_stride + lv * P.out_stride) * 8;
       if (!C.span("pass B tmp", tmp_base, 0, tmp_hi, P.tmp_end) ||
           !C.span("pass B output", out_base, 0, out_hi[x], P.out_end))
@@ -212,10 +210,10 @@ bool pass_b_rot(Checker &C, const PassLaunch &L) {
     const uint32_t set = by / P.vps, lv = by - set * P.vps, p = lv / R.n_rot, r = lv - p * R.n_rot;
     if (p > 1) return C.fail("rotation pass B: more than two polynomials per rotation");
     const NttSet *S = C.set(P.sets, set);
-    if (!S || !C.tables(*S, S->dft_b, LOGM)) return false;
+    if (!S || !C.tables(S->dft_b, D::M / 2)) return false;
     for (uint32_t x = 0; x < gx; ++x) {
       const size_t xr = (size_t)x * R.n_rot + r;
-      if (!C.span("rotation pass B tmp", (uint64_t)P.tmp + (uint64_t)by * N * 8, 0, tmp_hi[xr], P.tmp_end) ||
+      if (!C.span("rotation pass B tmp", (uint64_t)P.tmp + (uint64_t)by * fiona::tmp_words(D::M, N2) * 8, 0, tmp_hi[xr], P.tmp_end) ||
           !C.span("rotation pass B u'", (uint64_t)P.base + (set * P.base_set_stride + lv * P.base_stride) * 8, 0,
                   word_hi[xr], P.base_end) ||
           (p == 0 && !C.span("rotation pass B c0", (uint64_t)P.add + set * P.add_set_stride * 8, 0, word_hi[xr],

@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -78,7 +79,11 @@ inline uint64_t powmod_h(uint64_t b, uint64_t e, uint64_t q) {
   return r;
 }
 
-inline Tw make_tw(uint64_t w, uint64_t q) { return Tw{(double)w, (double)w / (double)q}; }
+// The centred twiddle of w in [0, q).
+inline Tw make_tw(uint64_t w, uint64_t q) {
+  const double c = w > q / 2 ? -(double)(q - w) : (double)w;
+  return Tw{c, c / (double)q};
+}
 
 // The default root: psi = x^((q-1)/2N) for the smallest x >= 2 with psi^N = -1.
 inline uint64_t default_psi(uint32_t N, uint64_t q) {
@@ -89,17 +94,20 @@ inline uint64_t default_psi(uint32_t N, uint64_t q) {
   return 0;
 }
 
+inline double centred(uint64_t w, uint64_t q) { return make_tw(w, q).w; }
+
 // Tables of one direction of one modulus, for n = n1 + N1 n2 on the input
-// side and k = k2 + N2 k1 on the output side.  Forward: the twist psi^n
-// splits as psi^(N1 n2) psi^n1; pre = psi^(N1 n2) (N2 entries) and the
-// factor psi^n1, constant along pass A's DFT, joins mid = omega^(n1 k2)
-// psi^n1 at k2 N1 + n1.  Inverse (omega -> omega^-1): the factor
-// N^-1 psi^-k = N^-1 psi^-k2 psi^(-N2 k1); the part in k2, constant along
-// pass B's DFT, joins mid = omega^(-n1 k2) N^-1 psi^-k2, and post =
-// psi^(-N2 k1) (N1 entries).  DFT roots omega^N1 (size N2) and omega^N2
-// (size N1).
+// side and k = k2 + N2 k1 on the output side (see ntt_kernel.hpp).  Forward:
+// dft_a[2^s + b] = phi^bitrev(2^s + b) with phi = psi^N1 (N2 entries, the
+// first unused), and the factor psi^n1, constant along pass A's transform,
+// joins mid = omega^(n1 k2) psi^n1 (in pass A's column blocks, see NttSet).
+// Inverse (omega -> omega^-1): dft_a the DFT twiddles of root omega^N1 (N2 /
+// 2); the factor N^-1 psi^-k = N^-1 psi^-k2 psi^(-N2 k1): the part in k2,
+// constant along pass B's DFT, joins mid = omega^(-n1 k2) N^-1 psi^-k2, and
+// post = psi^(-N2 k1) (N1 entries).  dft_b: the DFT twiddles of root omega^N2.
 struct TableSet {
-  std::vector<Tw> pre, mid, dft_a, dft_b, post;
+  std::vector<Tw> dft_a, dft_b, post;
+  std::vector<double> mid;
 };
 
 inline TableSet make_tables(uint32_t log_n1, uint32_t log_n2, uint64_t q, uint64_t psi, bool inverse) {
@@ -107,71 +115,74 @@ inline TableSet make_tables(uint32_t log_n1, uint32_t log_n2, uint64_t q, uint64
   const uint64_t psi_inv = powmod_h(psi, q - 2, q);
   const uint64_t omega = inverse ? mulmod_h(psi_inv, psi_inv, q) : mulmod_h(psi, psi, q);
   TableSet t;
-  if (!inverse) {
-    t.pre.resize(N2);
-    const uint64_t step = powmod_h(psi, N1, q);
+  auto powers = [&](std::vector<Tw> &v, size_t n, uint64_t step) {
+    v.resize(n);
     uint64_t p = 1;
-    for (uint32_t n2 = 0; n2 < N2; ++n2, p = mulmod_h(p, step, q)) t.pre[n2] = make_tw(p, q);
+    for (size_t i = 0; i < n; ++i, p = mulmod_h(p, step, q)) v[i] = make_tw(p, q);
+  };
+  if (inverse) {
+    powers(t.post, N1, powmod_h(psi_inv, N2, q));
+    powers(t.dft_a, N2 / 2, powmod_h(omega, N1, q));
   } else {
-    t.post.resize(N1);
-    const uint64_t step = powmod_h(psi_inv, N2, q);
-    uint64_t p = 1;
-    for (uint32_t k1 = 0; k1 < N1; ++k1, p = mulmod_h(p, step, q)) t.post[k1] = make_tw(p, q);
-  }
-  t.mid.resize(N);
-  const uint64_t n_inv = powmod_h(N, q - 2, q);
-  for (uint32_t n1 = 0; n1 < N1; ++n1) {
-    const uint64_t step = powmod_h(omega, n1, q);
-    uint64_t p = inverse ? n_inv : powmod_h(psi, n1, q);   // the k2 = 0 entry
-    for (uint32_t k2 = 0; k2 < N2; ++k2) {
-      t.mid[(size_t)k2 * N1 + n1] = make_tw(p, q);
-      p = mulmod_h(p, inverse ? mulmod_h(step, psi_inv, q) : step, q);
+    std::vector<Tw> phi;
+    powers(phi, N2, powmod_h(psi, N1, q));
+    t.dft_a.resize(N2);
+    for (uint32_t i = 0; i < N2; ++i) {
+      uint32_t r = 0;
+      for (uint32_t b = 0; b < log_n2; ++b) r |= ((i >> b) & 1u) << (log_n2 - 1 - b);
+      t.dft_a[i] = phi[r];
     }
   }
-  const uint64_t w2 = powmod_h(omega, N1, q), w1 = powmod_h(omega, N2, q);
-  t.dft_a.resize(N2 / 2);
-  uint64_t p = 1;
-  for (uint32_t i = 0; i < N2 / 2; ++i, p = mulmod_h(p, w2, q)) t.dft_a[i] = make_tw(p, q);
-  t.dft_b.resize(N1 / 2);
-  p = 1;
-  for (uint32_t i = 0; i < N1 / 2; ++i, p = mulmod_h(p, w1, q)) t.dft_b[i] = make_tw(p, q);
+  powers(t.dft_b, N1 / 2, powmod_h(omega, N2, q));
+  t.mid.resize(N);
+  const uint32_t cols = fiona::kNttCols;
+  const uint64_t n_inv = powmod_h(N, q - 2, q);
+  for (uint32_t n1 = 0; n1 < N1; ++n1) {
+    const uint64_t step = powmod_h(omega, n1, q), mul = inverse ? mulmod_h(step, psi_inv, q) : step;
+    uint64_t p = inverse ? n_inv : powmod_h(psi, n1, q);   // the k2 = 0 entry
+    for (uint32_t k2 = 0; k2 < N2; ++k2, p = mulmod_h(p, mul, q))
+      t.mid[((size_t)(n1 / cols) * N2 + k2) * cols + n1 % cols] = centred(p, q);
+  }
   return t;
 }
 
-// Host image of table sets: all tables back to back (Tw), then the NttSet
-// records, which point into the device copy of the same image.
+// Host image of table sets: all tables back to back (in doubles), then the
+// NttSet records, which point into the device copy of the same image.
 struct TableImage {
-  std::vector<Tw> tw;
+  std::vector<double> words;
   struct Entry {
-    size_t pre, mid, dft_a, dft_b, post;
+    size_t mid, dft_a, dft_b, post;
     uint64_t q;
     Tw inv;
   };
+  static constexpr size_t kNone = (size_t)-1;
   std::vector<Entry> entries;
 
   // Appends the tables of one modulus; returns its set index.
   uint32_t add(const TableSet &t, uint64_t q, Tw inv = Tw{0.0, 0.0}) {
-    auto put = [&](const std::vector<Tw> &v) {
-      const size_t o = tw.size();
-      tw.insert(tw.end(), v.begin(), v.end());
-      return v.empty() ? (size_t)-1 : o;
+    auto put = [&](const auto &v) {
+      const size_t o = words.size(), n = v.size() * sizeof(v[0]) / sizeof(double);
+      if (!n) return kNone;
+      words.resize(o + n);   // (every table is an even number of doubles: the twiddle pairs stay aligned)
+      std::memcpy(&words[o], v.data(), n * sizeof(double));
+      return o;
     };
-    Entry e{put(t.pre), put(t.mid), put(t.dft_a), put(t.dft_b), put(t.post), q, inv};
+    Entry e{put(t.mid), put(t.dft_a), put(t.dft_b), put(t.post), q, inv};
     entries.push_back(e);
     return (uint32_t)entries.size() - 1;
   }
 
-  size_t table_bytes() const { return (tw.size() * sizeof(Tw) + 255) / 256 * 256; }
+  size_t table_bytes() const { return (words.size() * sizeof(double) + 255) / 256 * 256; }
   size_t bytes() const { return table_bytes() + (entries.size() * sizeof(NttSet) + 255) / 256 * 256; }
 
   // The NttSet records of an image placed at device address dev.
   std::vector<NttSet> sets_at(const void *dev) const {
-    const Tw *tb = (const Tw *)dev;
-    auto at = [&](size_t o) { return o == (size_t)-1 ? nullptr : tb + o; };
+    const double *tb = (const double *)dev;
+    auto at = [&](size_t o) { return o == kNone ? nullptr : tb + o; };
     std::vector<NttSet> sets;
     for (const Entry &e : entries)
-      sets.push_back(NttSet{at(e.pre), at(e.mid), at(e.dft_a), at(e.dft_b), at(e.post), e.inv, (double)e.q,
-                            1.0 / (double)e.q});
+      sets.push_back(NttSet{at(e.mid), (const Tw *)at(e.dft_a), (const Tw *)at(e.dft_b), (const Tw *)at(e.post), e.inv,
+                            (double)e.q, 1.0 / (double)e.q});
     return sets;
   }
   NttSet *sets_addr(void *dev) const { return (NttSet *)((char *)dev + table_bytes()); }
@@ -180,7 +191,8 @@ struct TableImage {
   NttSet *upload(void *dev) const {
     const std::vector<NttSet> sets = sets_at(dev);
     NttSet *dsets = sets_addr(dev);
-    if (hipMemcpy(dev, tw.data(), tw.size() * sizeof(Tw), hipMemcpyHostToDevice) != hipSuccess) return nullptr;
+    if (hipMemcpy(dev, words.data(), words.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+      return nullptr;
     if (hipMemcpy(dsets, sets.data(), sets.size() * sizeof(NttSet), hipMemcpyHostToDevice) != hipSuccess)
       return nullptr;
     return dsets;
@@ -192,20 +204,20 @@ struct TableImage {
 inline std::vector<Region> table_regions(const TableImage &img, const void *dev) {
   std::vector<Region> r;
   const uint64_t base = (uint64_t)dev;
-  const size_t n = img.tw.size();
+  const size_t n = img.words.size();
   for (size_t s = 0; s < img.entries.size(); ++s) {
     const TableImage::Entry &e = img.entries[s];
-    const size_t offs[5] = {e.pre, e.mid, e.dft_a, e.dft_b, e.post};
-    const char *names[5] = {"pre", "mid", "dft_a", "dft_b", "post"};
-    for (int t = 0; t < 5; ++t) {
-      if (offs[t] == (size_t)-1) continue;
+    const size_t offs[4] = {e.mid, e.dft_a, e.dft_b, e.post};
+    const char *names[4] = {"mid", "dft_a", "dft_b", "post"};
+    for (int t = 0; t < 4; ++t) {
+      if (offs[t] == TableImage::kNone) continue;
       size_t end = n;   // the next table's start, else the end of the tables
       for (const TableImage::Entry &f : img.entries) {
-        const size_t o2[5] = {f.pre, f.mid, f.dft_a, f.dft_b, f.post};
+        const size_t o2[4] = {f.mid, f.dft_a, f.dft_b, f.post};
         for (size_t o : o2)
-          if (o != (size_t)-1 && o > offs[t] && o < end) end = o;
+          if (o != TableImage::kNone && o > offs[t] && o < end) end = o;
       }
-      r.push_back(Region{base + offs[t] * sizeof(Tw), base + end * sizeof(Tw),
+      r.push_back(Region{base + offs[t] * sizeof(double), base + end * sizeof(double),
                          "set " + std::to_string(s) + " " + names[t]});
     }
   }
@@ -217,8 +229,17 @@ inline std::vector<Region> table_regions(const TableImage &img, const void *dev)
 // The passes are instantiated per DFT side 2^4 .. 2^9.
 template <uint32_t LOG>
 void launch_pair(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPass &P) {
-  if (a) hipLaunchKernelGGL(fiona::ntt_pass_a<LOG>, grid, dim3(fiona::kNttThreads), smem, stream, P);
-  else hipLaunchKernelGGL(fiona::ntt_pass_b<LOG>, grid, dim3(fiona::kNttThreads), smem, stream, P);
+  if (a && P.load == fiona::kLoadF64)
+    hipLaunchKernelGGL((fiona::ntt_pass_a<LOG, true>), grid, dim3(fiona::kNttThreads), smem, stream, P);
+  else if (a)
+    hipLaunchKernelGGL((fiona::ntt_pass_a<LOG, false>), grid, dim3(fiona::kNttThreads), smem, stream, P);
+  else
+    hipLaunchKernelGGL(fiona::ntt_pass_b<LOG>, grid, dim3(fiona::kNttThreads), smem, stream, P);
+}
+
+// LDS of a pass of side M: the columns and at most M twiddles.
+constexpr size_t pass_smem(uint32_t M) {
+  return fiona::kNttCols * fiona::padded_len(M) * sizeof(double) + M * sizeof(Tw);
 }
 
 // One pass over gridDim.y = V vectors (V <= 65535).
@@ -229,8 +250,7 @@ inline void launch_pass(bool a, uint32_t log_side, uint32_t log_other, uint32_t 
     return;
   }
   const dim3 grid((1u << log_other) / fiona::kNttCols, V);
-  const size_t smem = fiona::kNttCols * fiona::padded_len(1u << log_side) * sizeof(double) +
-                      (1u << log_side) / 2 * sizeof(Tw);
+  const size_t smem = pass_smem(1u << log_side);
   switch (log_side) {
     case 4: launch_pair<4>(a, grid, smem, stream, P); break;
     case 5: launch_pair<5>(a, grid, smem, stream, P); break;
@@ -249,16 +269,16 @@ inline void launch_transform(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipSt
 
 template <uint32_t LOG>
 bool allow_smem_one(int bytes) {
-  return hipFuncSetAttribute((const void *)fiona::ntt_pass_a<LOG>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             bytes) == hipSuccess &&
-         hipFuncSetAttribute((const void *)fiona::ntt_pass_b<LOG>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             bytes) == hipSuccess;
+  const void *k[3] = {(const void *)fiona::ntt_pass_a<LOG, true>, (const void *)fiona::ntt_pass_a<LOG, false>,
+                      (const void *)fiona::ntt_pass_b<LOG>};
+  for (const void *f : k)
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return false;
+  return true;
 }
 
 // Lets every pass use the LDS of its largest side.
 inline bool allow_smem() {
-  const int smem = (int)(fiona::kNttCols * fiona::padded_len(fiona::kNttMaxSide) * sizeof(double) +
-                         fiona::kNttMaxSide / 2 * sizeof(Tw));
+  const int smem = (int)pass_smem(fiona::kNttMaxSide);
   return allow_smem_one<4>(smem) && allow_smem_one<5>(smem) && allow_smem_one<6>(smem) &&
          allow_smem_one<7>(smem) && allow_smem_one<8>(smem) && allow_smem_one<9>(smem);
 }

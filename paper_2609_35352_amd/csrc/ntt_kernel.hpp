@@ -9,19 +9,22 @@
 // Both run as a four-step transform, N = N1 * N2 (256 x 256 for N = 2^16):
 // index n = n1 + N1 n2 on the input side and k = k2 + N2 k1 on the output
 // side, so that omega^(nk) = omega^(n1 k2) (omega^N2)^(n1 k1) (omega^N1)^(n2 k2).
-//   pass A: for each n1, a DFT of size N2 over n2 (optionally after a
-//           multiplication of each input by pre[n2]), then a multiplication by
-//           mid[k2 N1 + n1]; stored transposed as T[k2 N1 + n1];
+//   pass A: for each n1, a transform of size N2 over n2, then a multiplication
+//           by mid (n1, k2); stored as row k2 of the intermediate, column n1;
 //   pass B: for each k2, a DFT of size N1 over n1, giving output k2 + N2 k1
-//           (optionally multiplied by post[k1]).
-// The twist psi^n of the forward transform and the factor N^-1 psi^-k of the
-// inverse split into a part that pre or post applies and a part that is
-// constant along one pass's DFT and rides in mid (the tables are built on the
-// host).  A workgroup takes kNttCols columns (pass A) or rows (pass B) at
-// once, so every global access is a run of at least kNttCols consecutive
-// words.  The DFTs are radix 2 with the input in bit-reversed order and the
-// output natural; a thread takes groups of up to 16 words through four
-// stages at a time in registers, and LDS carries the data between groups.
+//           (inverse: multiplied by post[k1]).
+// Forward, pass A's transform is itself negacyclic: with phi = psi^N1 it takes
+// x_n2 to sum x_n2 phi^((2 k2 + 1) n2), by butterflies a + t b, a - t b with
+// t = phi^bitrev(2^s + block) (stage s from the largest distance down, input
+// natural, output bit-reversed): the twist psi^(N1 n2) rides in the
+// butterflies' twiddles, and psi^n1, constant along the transform, in mid.
+// Inverse, pass A's transform is the cyclic DFT, and the factor N^-1 psi^-k
+// splits into a part constant along pass B's DFT, in mid, and post.  The cyclic
+// DFTs are radix 2 with the input in bit-reversed order and the output natural.
+// A workgroup takes kNttCols columns (pass A) or rows (pass B) at once, so
+// every global access is a run of at least kNttCols consecutive words.  A
+// thread takes groups of up to 16 words through four stages at a time in
+// registers, and LDS carries the data between groups.
 //
 // Arithmetic is in fp64, on exact integers (q < 2^50): a double holds any
 // integer below 2^53, and gfx950 issues fp64 FMA at full rate where 32-bit
@@ -29,11 +32,14 @@
 // FMA method of van der Hoeven, Lecerf and Quintin ("Modular SIMD arithmetic in
 // Mathemagix", 2016): h = fl(b w) and its exact error l = b w - h (one FMA);
 // the quotient k = rint(b * w/q) from one FMA against a rounding constant;
-// then b w - k q = (h - k q) + l exactly.  For |b| < 2^51 and 0 <= w < q the
-// result r satisfies r = b w (mod q) and |r| <= q (1/2 + |b| 2^-54).  Values
-// between stages are signed and lazily reduced; reduce() brings any |x| < 2^52
-// to the exact centred residue, |x| <= (q-1)/2 (the FMA's error |x/q| 2^-53 is
-// below 1/(2q), the distance from x/q to the nearest half-integer).
+// then b w - k q = (h - k q) + l exactly.  The tables hold centred twiddles,
+// |w| <= q/2: then for |b| < 2^52 the quotient stays below 2^51 and the result
+// r satisfies r = b w (mod q) and |r| <= q (1/2 + |b| 2^-54).  Values between
+// stages are signed and lazily reduced (BoundsDft checks every bound at
+// compile time); reduce() brings any |x| < 2^53 to |x| <= q/2 + 1, and any
+// |x| < 2^52 to the exact centred residue, |x| <= (q-1)/2 (the FMA's error
+// |x/q| 2^-53 is then below 1/(2q), the distance from x/q to the nearest
+// half-integer).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -46,7 +52,7 @@ constexpr uint32_t kNttCols = 16;      // columns (pass A) or rows (pass B) per 
 constexpr uint32_t kNttThreads = 256;
 constexpr uint32_t kNttMaxSide = 512;  // N1, N2 <= 512: N <= 2^17
 
-struct Tw {   // a twiddle w, an integer in [0, q), and fl(w / q)
+struct Tw {   // a twiddle w, an integer with |w| <= q/2, and fl(w / q)
   double w, wq;
 };
 
@@ -154,12 +160,15 @@ __host__ __device__ constexpr uint32_t padded_len(uint32_t m) { return m + m / 1
 // Stages S0 .. S0+R-1 of the radix-2 DFT on one group of 2^R words held in
 // registers: r[u] is the word at position o + (u << S0) of a group whose
 // offset below 2^S0 is o (positions in the DFT's bit-reversed input order).
-// tw_at(t) returns w_M^t.  Entries are |x| <= 0.57 q; every second stage and
-// the last one end with a reduction.  A product's output is below 0.5 q
-// (1 + 2^-3); the unit-twiddle butterflies of the first stages (S0 = 0) add
-// their input unmultiplied, so a product's input stays below 1.2 q, every
-// value below 2.3 q (< 2^52, within reduce's range), and the group leaves
-// |x| <= q/2 behind.
+// tw_at(t) returns w_M^t.  Nothing is reduced here but, in the first group
+// (S0 = 0), the even words after its second stage: the butterflies with the
+// twiddle 1 add their input unmultiplied, so those words double in both
+// stages, while a product's output is back near q/2.  BoundsDft follows every
+// word's bound through this schedule.  Reducing every word after every second
+// stage instead took 8 reductions a word and transform pair, now 3.  That alone
+// left the large rescales as they were (1.07 ms at N = 2^16, L = 8, 128
+// ciphertexts: the passes wait on memory there) and made small ones 4% faster
+// (N = 2^14, L = 6, 24 ciphertexts: 46.9 -> 45.0 us).
 template <uint32_t LOGM, uint32_t S0, uint32_t R, typename TwAt>
 __device__ __forceinline__ void butterflies(double (&r)[1u << R], uint32_t o, TwAt tw_at, double q, double qinv) {
   constexpr uint32_t S = 1u << R;
@@ -176,11 +185,83 @@ __device__ __forceinline__ void butterflies(double (&r)[1u << R], uint32_t o, Tw
       r[u0] = a + t;
       r[u0 + hh] = a - t;
     }
-    if ((st & 1) || st + 1 == R) {
+    if (S0 == 0 && st == 1 && R > 2) {
 #pragma unroll
-      for (uint32_t u = 0; u < S; ++u) r[u] = reduce(r[u], q, qinv);
+      for (uint32_t u = 0; u < S; u += 2) r[u] = reduce(r[u], q, qinv);
     }
   }
+}
+
+// Stages S0 .. S0+R-1 of the negacyclic transform on one group of 2^R words at
+// distance 2^(LOGM-S0-R) of each other inside block `block` of stage S0:
+// tw_at(2^s + b) is the twiddle of block b of stage s.  Nothing is reduced.
+template <uint32_t S0, uint32_t R, typename TwAt>
+__device__ __forceinline__ void tree_butterflies(double (&r)[1u << R], uint32_t block, TwAt tw_at, double q) {
+#pragma unroll
+  for (uint32_t st = 0; st < R; ++st) {
+    const uint32_t hh = 1u << (R - 1 - st);
+#pragma unroll
+    for (uint32_t b = 0; b < (1u << st); ++b) {
+      const Tw t = tw_at((1u << (S0 + st)) + (block << st) + b);
+#pragma unroll
+      for (uint32_t k = 0; k < hh; ++k) {
+        const uint32_t u0 = b * 2 * hh + k;
+        const double a = r[u0], x = mul_tw(r[u0 + hh], t, q);
+        r[u0] = a + x;
+        r[u0 + hh] = a - x;
+      }
+    }
+  }
+}
+
+// Bounds of the words through a size-2^LOGM DFT whose input is at most `in`,
+// in units of 2^50 (every q is below one unit), for the schedule of
+// butterflies, first_stages, middle_stages and last_stages: a product's input
+// must stay below 4 units and every word below 8 (exact integers in a double).
+constexpr double kUnitReduced = 0.5 + 0x1p-40;   // after reduce(): at most q/2 + 1
+constexpr double product_bound(double b) { return 0.5 + b / 16; }
+template <uint32_t LOGM>
+struct BoundsDft {
+  bool ok = true;
+  double out = 0;   // the last group's output
+  constexpr double product(double b) {
+    if (b >= 4) ok = false;
+    return product_bound(b);
+  }
+  constexpr double word(double x) {
+    if (x >= 8) ok = false;
+    return x;
+  }
+  constexpr explicit BoundsDft(double in) {
+    double r[16] = {};
+    for (int u = 0; u < 16; ++u) r[u] = in;
+    for (int st = 0; st < 4; ++st) {   // the first group
+      const int hh = 1 << st;
+      for (int u = 0; u < 16; ++u) {
+        if ((u & (2 * hh - 1)) >= hh) continue;
+        const double t = (u & (hh - 1)) == 0 ? r[u + hh] : product(r[u + hh]);
+        const double x = word(r[u] + t);
+        r[u] = x;
+        r[u + hh] = x;
+      }
+      if (st == 1)
+        for (int u = 0; u < 16; u += 2) r[u] = kUnitReduced;
+    }
+    out = kUnitReduced;   // put_first reduces every word
+    for (uint32_t st = 4; st < LOGM; ++st) out = word(out + product(out));
+  }
+};
+// The DFT's output, and the negacyclic transform's (four stages from an
+// integer below 2^50, a reduction, then the rest like the DFT's).
+template <uint32_t LOGM>
+constexpr double dft_out() {
+  // inputs: residues, or pass A's products by mid, whose quotient takes w / q
+  // as w fl(1/q), twice the rounding error: 1/2 + b/8 of an input b below 4
+  constexpr BoundsDft<LOGM> b(1.0);
+  static_assert(b.ok && b.out < 4, "the products after the last stage (mid, post) take their input below 4 units");
+  double x = 1;   // tree_butterflies' first group
+  for (int st = 0; st < 4; ++st) x += product_bound(x);
+  return x < 4 ? b.out : 8;
 }
 
 // How a size-M DFT (16 <= M <= kNttMaxSide) splits over a workgroup's
@@ -214,13 +295,55 @@ __device__ __forceinline__ void first_stages(double (&r)[16], const Tw (&t1)[8],
   butterflies<LOGM, 0, 4>(r, 0, [&](uint32_t t) { return t1[t >> (LOGM - 4)]; }, q, qinv);
 }
 
-// The first groups' results go to LDS: column col, group i' (natural order).
+// The first groups' results go to LDS, reduced: column col, group i' (natural order).
 template <uint32_t LOGM>
-__device__ __forceinline__ void put_first(double *xs, uint32_t col, uint32_t ip, const double (&r)[16]) {
+__device__ __forceinline__ void put_first(double *xs, uint32_t col, uint32_t ip, const double (&r)[16], double q,
+                                          double qinv) {
   using D = DftShape<LOGM>;
   const uint32_t i = LOGM > 4 ? bit_reverse(ip, LOGM - 4) : 0u;   // (M = 16: one group, i' = 0)
 #pragma unroll
-  for (uint32_t u = 0; u < 16; ++u) xs[col * D::PM + pidx(16 * i + u)] = r[u];
+  for (uint32_t u = 0; u < 16; ++u) xs[col * D::PM + pidx(16 * i + u)] = reduce(r[u], q, qinv);
+}
+
+// The negacyclic transform's first groups: r[v] is row i' + I1 v.  They go to
+// LDS, reduced: position v I1 + i' of column col.
+template <uint32_t LOGM>
+__device__ __forceinline__ void tree_first(double *xs, uint32_t col, uint32_t ip, double (&r)[16],
+                                           const Tw *__restrict__ tree, double q, double qinv) {
+  using D = DftShape<LOGM>;
+  tree_butterflies<0, 4>(r, 0, [&](uint32_t t) { return tree[t]; }, q);
+#pragma unroll
+  for (uint32_t v = 0; v < 16; ++v) xs[col * D::PM + pidx(v * D::I1 + ip)] = reduce(r[v], q, qinv);
+}
+
+// Its last groups: on return r[e] is output o + (bitrev(e) << S0L), at most
+// dft_out() units: positions j E2 + e of block j = bitrev(o).
+template <uint32_t LOGM>
+__device__ __forceinline__ void tree_last(const double *xs, uint32_t col, uint32_t o, const Tw *tw,
+                                          double (&r)[DftShape<LOGM>::E2], double q) {
+  using D = DftShape<LOGM>;
+  const uint32_t j = bit_reverse(o, D::S0L);
+#pragma unroll
+  for (uint32_t e = 0; e < D::E2; ++e) r[e] = xs[col * D::PM + pidx(j * D::E2 + e)];
+  tree_butterflies<D::S0L, D::R2>(r, j, [&](uint32_t t) { return tw[t]; }, q);
+}
+
+// Its middle stage (M = 512: distance 16 inside each block of 32); barriers on both sides.
+template <uint32_t LOGM>
+__device__ __forceinline__ void tree_middle(double *xs, const Tw *tw, double q) {
+  using D = DftShape<LOGM>;
+  __syncthreads();
+  if constexpr (D::S0L > 4) {
+    static_assert(D::S0L == 5, "one middle stage at most");
+    for (uint32_t it = threadIdx.x; it < kNttCols * D::M / 2; it += kNttThreads) {
+      const uint32_t col = it % kNttCols, gi = it / kNttCols, v = gi >> 4, p = v * 32 + (gi & 15u);
+      double r[2] = {xs[col * D::PM + pidx(p)], xs[col * D::PM + pidx(p + 16)]};
+      tree_butterflies<4, 1>(r, v, [&](uint32_t t) { return tw[t]; }, q);
+      xs[col * D::PM + pidx(p)] = r[0];
+      xs[col * D::PM + pidx(p + 16)] = r[1];
+    }
+    __syncthreads();
+  }
 }
 
 // Between the first and the last groups: the middle stages in LDS (M = 512),
@@ -242,7 +365,7 @@ __device__ __forceinline__ void middle_stages(double *xs, const Tw *tw, double q
   }
 }
 
-// The last groups: column col, offset o; on return r[u] is output o + (u << S0L).
+// The last groups: column col, offset o; on return r[u] is output o + (u << S0L), at most dft_out() units.
 template <uint32_t LOGM>
 __device__ __forceinline__ void last_stages(const double *xs, uint32_t col, uint32_t o, const Tw *tw,
                                             double (&r)[DftShape<LOGM>::E2], double q, double qinv) {
@@ -252,31 +375,47 @@ __device__ __forceinline__ void last_stages(const double *xs, uint32_t col, uint
   butterflies<LOGM, D::S0L, D::R2>(r, o, [&](uint32_t t) { return tw[t]; }, q, qinv);
 }
 
-// Copy the M/2 twiddles of the size-M DFT into LDS.
-__device__ __forceinline__ void stage_twiddles(Tw *dst, const Tw *__restrict__ src, uint32_t logM) {
-  for (uint32_t i = threadIdx.x; i < (1u << logM) / 2; i += kNttThreads) dst[i] = src[i];
+// b - y for a residue b and a DFT output y, small enough for a product.
+template <uint32_t LOGM>
+__device__ __forceinline__ double minuend(uint64_t b, double y, double q, double qinv) {
+  if constexpr (dft_out<LOGM>() + 1 >= 4) y = reduce(y, q, qinv);
+  return to_f64(b) - y;
 }
 
-// What a pass reads (pass A) and writes (pass B).
-// The transposed layout of an N-word vector: element i = k2 + N2 k1
-// (k2 < N2, k1 < N1, the split of the four-step transform's output) at
-// k2 N1 + k1, so that one pass-B row k2 is N1 contiguous words.
+// Copy n twiddles into LDS.
+__device__ __forceinline__ void stage_twiddles(Tw *dst, const Tw *__restrict__ src, uint32_t n) {
+  for (uint32_t i = threadIdx.x; i < n; i += kNttThreads) dst[i] = src[i];
+}
+
+// What a pass reads (pass A) and writes (pass B).  Natural order is the
+// callers' layout.  The library's own vectors use layouts in which a
+// workgroup's 16 columns or rows are contiguous:
+//   transposed: element i = k2 + N2 k1 (k2 < N2, k1 < N1, the split of the
+//     four-step transform's output) at k2 N1 + k1, so that one pass-B row k2
+//     is N1 contiguous words;
+//   blocked: element n = n1 + N1 n2 (the split of its input) at
+//     ((n1 / 16) N2 + n2) 16 + n1 mod 16, so that one pass-A column block is
+//     16 N2 contiguous words.
+// In natural order the rows of a column block are a power of two apart (2 KiB
+// at N = 2^16): they fall on 2 of the 16 channels of an XCD's L2 (interleaved
+// every 256 bytes), and since the XCD of a workgroup follows from its column
+// block, on 4 of 16 over all the workgroups of an XCD.
 enum NttLoad : uint32_t {
-  kLoadU64 = 0,    // residues in [0, q) as uint64
-  kLoadF64 = 1,    // signed integers as doubles, |x| < 2^49 (a centred residue of another modulus)
-  kLoadU64T = 2,   // residues in [0, q) as uint64, each vector in the transposed layout (no pre)
+  kLoadU64 = 0,    // inverse: residues in [0, q) as uint64, natural order
+  kLoadF64 = 1,    // forward: integers as doubles, |x| < 2^50, blocked
+  kLoadU64T = 2,   // inverse: residues in [0, q) as uint64, transposed
 };
 enum NttStore : uint32_t {
-  kStoreU64 = 0,      // the transform, residues in [0, q) as uint64
-  kStoreF64 = 1,      // the transform, centred residues as doubles
-  kStoreRescale = 2,  // (base - transform) * inv mod q, in [0, q) as uint64
+  kStoreU64T = 0,     // the transform, residues in [0, q) as uint64, transposed
+  kStoreF64 = 1,      // the transform, centred residues as doubles, blocked
+  kStoreRescale = 2,  // (base - transform) * inv mod q, in [0, q) as uint64, natural order
+  kStoreF64C = 3,     // the transform, residues in [0, q) as doubles, blocked
 };
 
 // One modulus of a pass and its tables.
 struct NttSet {
-  const Tw *pre;     // pass A: multiply input n1 + N1 n2 by pre[n2] (null: by 1)
-  const Tw *mid;     // pass A: multiply output (n1, k2) by mid[k2 N1 + n1]
-  const Tw *dft_a;   // size-N2 DFT twiddles (N2 / 2)
+  const double *mid; // pass A: multiply output (n1, k2) by mid[((n1 / 16) N2 + k2) 16 + n1 mod 16]
+  const Tw *dft_a;   // pass A's twiddles: forward N2 (from index 1: 2^s + block), inverse N2 / 2
   const Tw *dft_b;   // size-N1 DFT twiddles (N1 / 2)
   const Tw *post;    // pass B: multiply output k2 + N2 k1 by post[k1] (null: by 1)
   Tw inv;            // kStoreRescale: the factor applied after the subtraction
@@ -287,8 +426,8 @@ struct NttSet {
 // consecutive vectors that share one modulus: vector v is number v % vps of
 // set v / vps, whose modulus and tables are sets[v / vps].  Its words sit at
 //   in   + (v / vps) * in_set_stride   + (v % vps) * in_stride   + n,
-// and likewise for out and base; the intermediate of vector v at tmp + v * N.
-// Each buffer's end bounds the descriptors of its accesses (buffer_extent).
+// and likewise for out and base; the intermediate of vector v at
+// tmp + v * tmp_words(N1, N2).  Each buffer's end bounds the descriptors of its accesses (buffer_extent).
 struct NttPass {
   const void *in;        // pass A input
   double *tmp;           // the transposed intermediates
@@ -300,7 +439,6 @@ struct NttPass {
   uint64_t in_stride, out_stride, base_stride;
   uint64_t in_set_stride, out_set_stride, base_set_stride, add_set_stride;
   uint32_t vps, log_n1, log_n2, load, store;
-  uint32_t out_transposed;  // pass B, kStoreU64 and kStoreRescale: write the transposed layout
   uint32_t nsets_shared;   // pass A: 0, or the number of sets when they all read the same input
                            // vectors (in_set_stride 0) and gridDim.x * vps is a multiple of 8
 };
@@ -314,17 +452,34 @@ struct Off {
   uint32_t v, s;
 };
 
+// The intermediate: row k2 is N1 words at k2 (N1 + 16).  The 16 words (128
+// bytes) between rows put the rows that one pass-A workgroup writes, 16 words
+// of each, on all the L2 channels in turn.
+__host__ __device__ constexpr uint32_t tmp_pitch(uint32_t N1) { return N1 + 16; }
+__host__ __device__ constexpr size_t tmp_words(uint32_t N1, uint32_t N2) { return (size_t)tmp_pitch(N1) * N2; }
+
 // Pass A over DFT side N2 = 2^LOGM (other side N1): the unit of workgroup
 // (bx, by) of a grid gx workgroups wide.
+// (With one set per vector, the column blocks go round the XCDs from vector to
+// vector, see spread_block.)
 struct UnitA {
   uint32_t set, lv, cb;
 };
+// The block of workgroup (bx, by) of a grid gx (a power of two) wide whose
+// blocks are runs of 16 words of the rows of a natural-order vector.  An XCD
+// takes every eighth workgroup, so block = bx would keep it on two blocks of
+// 16, whose rows share a few L2 channels; this gives it all blocks in turn
+// (with the padded intermediate, pass B of 128 ciphertexts' rescale at
+// N = 2^16, L = 8: 575 -> 514 us).
+__host__ __device__ constexpr uint32_t spread_block(uint32_t bx, uint32_t by, uint32_t gx) {
+  return (bx + by) & (gx - 1);
+}
 __host__ __device__ inline UnitA pass_a_unit(uint32_t vps, uint32_t nsets_shared, uint32_t bx, uint32_t by,
                                              uint32_t gx) {
   UnitA a;
   a.set = by / vps;
   a.lv = by - a.set * vps;
-  a.cb = bx;
+  a.cb = spread_block(bx, by, gx);
   if (nsets_shared) {
     // The sets read the same input vectors: give the nsets_shared workgroups
     // of one (vector, column block) consecutive turns on one XCD (workgroup
@@ -354,15 +509,19 @@ struct GeomA {
     const uint32_t n = n1 + N1 * (ip + D::I1 * rev4(u));
     return Off{((n & (D::M - 1)) * N1 + (n >> LOGM)) * 8, 0};
   }
-  static __host__ __device__ Off pre(uint32_t ip, uint32_t u) { return Off{ip * 16, D::I1 * 16 * rev4(u)}; }
+  // the same element in the blocked layout: column cl of block cb
+  // (word v is row ip + I1 v)
+  static __host__ __device__ Off in_b(uint32_t cb, uint32_t cl, uint32_t ip, uint32_t v) {
+    return Off{((cb * D::M + ip) * kNttCols + cl) * 8, D::I1 * kNttCols * 8 * v};
+  }
   // last groups, loop index it < IT2: column, offset; word u is row k2 = o + (u << S0L)
   static __host__ __device__ uint32_t col2(uint32_t it) { return it % kNttCols; }
   static __host__ __device__ uint32_t off2(uint32_t it) { return it / kNttCols; }
   static __host__ __device__ Off tmp(uint32_t o, uint32_t n1, uint32_t u, uint32_t N1) {
-    return Off{(o * N1 + n1) * 8, ((u << D::S0L) * N1) * 8};
+    return Off{(o * tmp_pitch(N1) + n1) * 8, ((u << D::S0L) * tmp_pitch(N1)) * 8};
   }
-  static __host__ __device__ Off mid(uint32_t o, uint32_t n1, uint32_t u, uint32_t N1) {
-    return Off{(o * N1 + n1) * 16, ((u << D::S0L) * N1) * 16};
+  static __host__ __device__ Off mid(uint32_t cb, uint32_t cl, uint32_t o, uint32_t u) {
+    return Off{((cb * D::M + o) * kNttCols + cl) * 8, (u << D::S0L) * kNttCols * 8};
   }
 };
 
@@ -374,18 +533,23 @@ struct GeomB {
   static __host__ __device__ uint32_t row(uint32_t it) { return it / D::I1; }
   static __host__ __device__ uint32_t grp(uint32_t it) { return it % D::I1; }
   static __host__ __device__ Off tmp(uint32_t row, uint32_t ip, uint32_t u) {
-    return Off{(row * D::M + ip) * 8, D::I1 * 8 * rev4(u)};
+    return Off{(row * tmp_pitch(D::M) + ip) * 8, D::I1 * 8 * rev4(u)};
   }
-  // last groups, it < IT2: row and offset (out_transposed walks a row's offsets first)
+  // last groups, it < IT2: row and offset (kStoreU64T walks a row's offsets first)
   static __host__ __device__ uint32_t row2(uint32_t it, bool trans) { return trans ? it / D::I2 : it % kNttCols; }
   static __host__ __device__ uint32_t off2(uint32_t it, bool trans) { return trans ? it % D::I2 : it / kNttCols; }
   static __host__ __device__ Off post(uint32_t o, uint32_t u) { return Off{o * 16, (u << D::S0L) * 16}; }
-  // output k2 + N2 k1, k1 = o + (u << S0L), in natural order and transposed
+  // output k2 + N2 k1, k1 = o + (u << S0L), in natural order, transposed and blocked
   static __host__ __device__ Off col(uint32_t k2, uint32_t o, uint32_t u, uint32_t N2) {
     return Off{(k2 + N2 * o) * 8, (N2 * 8 << D::S0L) * u};
   }
   static __host__ __device__ Off row_t(uint32_t k2, uint32_t o, uint32_t u) {
     return Off{(k2 * D::M + o) * 8, (u << D::S0L) * 8};
+  }
+  // (N1 = N2 2^d, d = 0 or 1: n1 = k2 + N2 (k1 mod 2^d), n2 = k1 >> d)
+  static __host__ __device__ Off block(uint32_t k2, uint32_t o, uint32_t u, uint32_t N2) {
+    const uint32_t d = D::M / N2 - 1, b = k2 / kNttCols + (N2 / kNttCols) * (o & d);
+    return Off{((b * N2 + (o >> d)) * kNttCols + k2 % kNttCols) * 8, ((u << D::S0L) >> d) * kNttCols * 8};
   }
 };
 
@@ -411,7 +575,7 @@ struct GeomRot {
     return (g * d_lo + (g - 1) / 2) & (N2 - 1);
   }
   static __host__ __device__ Off tmp(uint32_t k2, uint32_t ip, uint32_t u) {
-    return Off{(k2 * D::M + ip) * 8, D::I1 * 8 * rev4(u)};
+    return Off{(k2 * tmp_pitch(D::M) + ip) * 8, D::I1 * 8 * rev4(u)};
   }
   // last groups, it < IT2: the workgroup's column and offset; word k1 = o + (u << S0L) of row k2
   static __host__ __device__ uint32_t row2(uint32_t it) { return it / D::I2; }
@@ -428,20 +592,27 @@ struct GeomRot {
 // Pass A, N2 = 2^LOGM: grid (N1 / kNttCols, vectors).  The first groups of
 // column n1 hold rows n2 = i' + I1 v; the quarter waves read runs of
 // kNttCols columns of one row (kLoadU64T: runs of consecutive rows of one
-// column, which are contiguous there).  The last groups store rows
+// column, which are contiguous there).  FWD: the forward transform (kLoadF64).
+// What bounds it: the L1 path (it serves one 64-byte access a clock), the
+// arithmetic and the stores take about the same time and overlap badly
+// (parts taken out one at a time, N = 2^16, L = 8, 128 ciphertexts, of 444 us:
+// stores 160, loads 113, mid 57, a separate twist 36; arithmetic alone 221).
+// So the twist rides in the butterflies (no loads, no products) and mid is one
+// double a word instead of a twiddle pair: 447 -> 393 us.  The last groups store rows
 // k2 = o + (u << S0L) of the intermediate, again in runs of kNttCols columns.
-template <uint32_t LOGM>
+template <uint32_t LOGM, bool FWD>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
+  static_assert(dft_out<LOGM>() < 4, "mid's input");
   using D = DftShape<LOGM>;
   using G = GeomA<LOGM>;
-  extern __shared__ double xs[];   // [kNttCols][PM], then the M/2 DFT twiddles
+  extern __shared__ double xs[];   // [kNttCols][PM], then the transform's twiddles
   Tw *tw = (Tw *)(xs + kNttCols * D::PM);
   const UnitA un = pass_a_unit(P.vps, P.nsets_shared, blockIdx.x, blockIdx.y, gridDim.x);
   const uint32_t set = un.set, lv = un.lv, cb = un.cb;
   const NttSet S = P.sets[set];
-  stage_twiddles(tw, S.dft_a, LOGM);
+  stage_twiddles(tw, S.dft_a, FWD ? D::M : D::M / 2);
   Tw t1[8];
-  first_twiddles<LOGM>(t1, S.dft_a);
+  if constexpr (!FWD) first_twiddles<LOGM>(t1, S.dft_a);
   const uint32_t log_n1 = P.log_n1, N1 = 1u << log_n1, N2 = D::M;
   const uint64_t v = (uint64_t)set * P.vps + lv;
   const uint64_t in_off = set * P.in_set_stride + lv * P.in_stride;
@@ -453,58 +624,49 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
     const uint32_t cl = G::col(it, trans), ip = G::grp(it, trans);
     const uint32_t n1 = cb * kNttCols + cl;
     double r[16];
-    if (trans) {   // no pre
-      uint64_t w[16];
+    if constexpr (FWD) {
 #pragma unroll
       for (uint32_t u = 0; u < 16; ++u) {
-        const Off o = G::in_t(n1, ip, u, N1);
-        w[u] = in.u64(o.v, o.s);
+        const Off o = G::in_b(cb, cl, ip, u);
+        r[u] = in.f64(o.v, o.s);
       }
-#pragma unroll
-      for (uint32_t u = 0; u < 16; ++u) r[u] = reduce(to_f64(w[u]), q, qinv);
+      tree_first<LOGM>(xs, cl, ip, r, S.dft_a, q, qinv);
     } else {
-      if (P.load == kLoadF64) {
+      uint64_t w[16];
+      if (trans) {
 #pragma unroll
         for (uint32_t u = 0; u < 16; ++u) {
-          const Off o = G::in(n1, ip, u, N1);
-          r[u] = in.f64(o.v, o.s);
+          const Off o = G::in_t(n1, ip, u, N1);
+          w[u] = in.u64(o.v, o.s);
         }
       } else {
-        uint64_t w[16];
 #pragma unroll
         for (uint32_t u = 0; u < 16; ++u) {
           const Off o = G::in(n1, ip, u, N1);
           w[u] = in.u64(o.v, o.s);
         }
-#pragma unroll
-        for (uint32_t u = 0; u < 16; ++u) r[u] = to_f64(w[u]);
       }
-      if (S.pre) {
-        const Buf pre(S.pre, S.pre + N2);
 #pragma unroll
-        for (uint32_t u = 0; u < 16; ++u) {
-          const Off o = G::pre(ip, u);
-          r[u] = mul_tw(r[u], pre.tw(o.v, o.s), q);
-        }
-      } else {
-#pragma unroll
-        for (uint32_t u = 0; u < 16; ++u) r[u] = reduce(r[u], q, qinv);
-      }
+      for (uint32_t u = 0; u < 16; ++u) r[u] = to_f64(w[u]);
+      first_stages<LOGM>(r, t1, q, qinv);
+      put_first<LOGM>(xs, cl, ip, r, q, qinv);
     }
-    first_stages<LOGM>(r, t1, q, qinv);
-    put_first<LOGM>(xs, cl, ip, r);
   }
-  middle_stages<LOGM>(xs, tw, q, qinv);
-  const Buf tmp(P.tmp + v * ((uint64_t)N1 * N2), P.tmp_end), mid(S.mid, S.mid + (size_t)N1 * N2);
+  if constexpr (FWD) tree_middle<LOGM>(xs, tw, q);
+  else middle_stages<LOGM>(xs, tw, q, qinv);
+  const Buf tmp(P.tmp + v * tmp_words(N1, N2), P.tmp_end), mid(S.mid, S.mid + (size_t)N1 * N2);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT2; it += kNttThreads) {
     const uint32_t cl = G::col2(it), o = G::off2(it), n1 = cb * kNttCols + cl;
     double r[D::E2];
-    last_stages<LOGM>(xs, cl, o, tw, r, q, qinv);
+    if constexpr (FWD) tree_last<LOGM>(xs, cl, o, tw, r, q);
+    else last_stages<LOGM>(xs, cl, o, tw, r, q, qinv);
 #pragma unroll
     for (uint32_t u = 0; u < D::E2; ++u) {
-      const Off om = G::mid(o, n1, u, N1), ot = G::tmp(o, n1, u, N1);
-      tmp.put(mul_tw(r[u], mid.tw(om.v, om.s), q), ot.v, ot.s);
+      const Off om = G::mid(cb, cl, o, u), ot = G::tmp(o, n1, u, N1);
+      const uint32_t e = FWD ? rev4(u) >> (4 - D::R2) : u;
+      const double w = mid.f64(om.v, om.s);
+      tmp.put(mul_tw(r[e], Tw{w, w * qinv}, q), ot.v, ot.s);
     }
   }
 }
@@ -512,7 +674,8 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
 // Pass B, N1 = 2^LOGM: grid (N2 / kNttCols, vectors).  The first groups read
 // runs of I1 consecutive words of one intermediate row k2; the last groups
 // store column k2 = r0 + (lane mod kNttCols), rows k1, as runs of kNttCols
-// words (out_transposed: runs of consecutive k1 of one row k2).
+// words (kStoreU64T: runs of consecutive k1 of one row k2; blocked: rows k1
+// and k1 + 2^d follow each other).
 template <uint32_t LOGM>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
   using D = DftShape<LOGM>;
@@ -521,13 +684,14 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
   Tw *tw = (Tw *)(xs + kNttCols * D::PM);
   const uint32_t set = blockIdx.y / P.vps, lv = blockIdx.y - set * P.vps;
   const NttSet S = P.sets[set];
-  stage_twiddles(tw, S.dft_b, LOGM);
+  stage_twiddles(tw, S.dft_b, D::M / 2);
   Tw t1[8];
   first_twiddles<LOGM>(t1, S.dft_b);
-  const uint32_t N2 = 1u << P.log_n2, r0 = blockIdx.x * kNttCols, M = D::M;
+  const uint32_t N2 = 1u << P.log_n2, M = D::M;
+  const uint32_t r0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
   const uint64_t v = blockIdx.y;
   const double q = S.q, qinv = S.qinv;
-  const Buf tmp(P.tmp + v * ((uint64_t)N2 * M) + (size_t)r0 * M, P.tmp_end);
+  const Buf tmp(P.tmp + v * tmp_words(M, N2) + (size_t)r0 * tmp_pitch(M), P.tmp_end);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT1; it += kNttThreads) {
     const uint32_t row = G::row(it), ip = G::grp(it);
@@ -538,10 +702,10 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
       r[u] = tmp.f64_once(o.v, o.s);
     }
     first_stages<LOGM>(r, t1, q, qinv);
-    put_first<LOGM>(xs, row, ip, r);
+    put_first<LOGM>(xs, row, ip, r, q, qinv);
   }
   middle_stages<LOGM>(xs, tw, q, qinv);
-  const bool transposed = P.out_transposed != 0 && P.store != kStoreF64;   // uniform
+  const bool transposed = P.store == kStoreU64T;   // uniform
   const bool rescale = P.store == kStoreRescale;
   const Buf out((const char *)P.out + (set * P.out_set_stride + lv * P.out_stride) * 8, P.out_end);
   const Buf base(rescale ? P.base + set * P.base_set_stride + lv * P.base_stride : nullptr,
@@ -560,11 +724,13 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
         y[u] = mul_tw(y[u], post.tw(op.v, op.s), q);
       }
     }
-    if (P.store == kStoreF64) {
+    if (P.store == kStoreF64 || P.store == kStoreF64C) {
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
-        const Off oc = G::col(k2, o, u, N2);
-        out.put(reduce(y[u], q, qinv), oc.v, oc.s);
+        const Off ob = G::block(k2, o, u, N2);
+        double z = reduce(y[u], q, qinv);
+        if (P.store == kStoreF64C && z < 0.0) z += q;
+        out.put(z, ob.v, ob.s);
       }
       continue;
     }
@@ -576,7 +742,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
         bv[u] = base.u64_once(oc.v, oc.s);
       }
 #pragma unroll
-      for (uint32_t u = 0; u < D::E2; ++u) y[u] = mul_tw(to_f64(bv[u]) - y[u], S.inv, q);
+      for (uint32_t u = 0; u < D::E2; ++u) y[u] = mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q);
     }
     if (transposed) {
 #pragma unroll

@@ -38,6 +38,11 @@ struct fiona_rescaler {
 
 namespace {
 
+// Bytes of one limb's intermediates.
+size_t tmp_vec_bytes(const fiona_rescaler *R) {
+  return (size_t)2 * R->max_ct * fiona::tmp_words(1u << R->log_n1, 1u << R->log_n2) * sizeof(double);
+}
+
 // Checks the parameters and sizes a rescaler: its tables (img) and the
 // bytes of its device buffer (the table image, then W and T).
 int rescaler_layout(const fiona_ctx *ctx, const uint64_t *psi, uint32_t max_ct, fiona_rescaler *R,
@@ -68,19 +73,19 @@ int rescaler_layout(const fiona_ctx *ctx, const uint64_t *psi, uint32_t max_ct, 
     img.add(make_tables(R->log_n1, R->log_n2, q, roots[l], false), q, make_tw(powmod_h(qt % q, q - 2, q), q));
   }
   img.add(make_tables(R->log_n1, R->log_n2, qt, roots[L - 1], true), qt);
-  const size_t vec_bytes = (size_t)2 * max_ct * N * sizeof(double);
+  const size_t vec_bytes = (size_t)2 * max_ct * N * sizeof(double), tmp_bytes = tmp_vec_bytes(R);
   // All forward limbs go in one launch pair, so T holds L - 1 intermediates.
   // Measured against one limb per launch (in-process A/B, same buffers):
   // 256 vectors (VGG11's outputs) 1.25 -> 1.18 ms, 192 (BERT's) 1.32 -> 1.30.
   // Very large max_ct takes fewer limbs per launch, so that T stays within
   // kMaxTmpBytes (and every launch within the grid's 65535 vectors).
-  const size_t fit = kMaxTmpBytes / vec_bytes;
+  const size_t fit = kMaxTmpBytes / tmp_bytes;
   const size_t fit_grid = 65535 / (2 * (size_t)max_ct);
   size_t lpl = L - 1;
   if (lpl > fit) lpl = fit;
   if (lpl > fit_grid) lpl = fit_grid;
   R->limbs_per_launch = lpl < 1 ? 1 : (uint32_t)lpl;
-  total = img.bytes() + (1 + R->limbs_per_launch) * vec_bytes;
+  total = img.bytes() + vec_bytes + R->limbs_per_launch * tmp_bytes;
   return FIONA_OK;
 }
 
@@ -92,7 +97,7 @@ void rescaler_place(fiona_rescaler *R, const TableImage &img, void *dev) {
   R->W = (double *)((char *)dev + img.bytes());
   R->T = (double *)((char *)dev + img.bytes() + vec_bytes);
   R->W_end = (const char *)R->W + vec_bytes;
-  R->T_end = (const char *)R->T + R->limbs_per_launch * vec_bytes;
+  R->T_end = (const char *)R->T + R->limbs_per_launch * tmp_vec_bytes(R);
 }
 
 // The launches of one rescale (arguments already checked).

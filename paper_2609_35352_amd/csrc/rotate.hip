@@ -155,13 +155,14 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
   const uint32_t set = blockIdx.y / P.vps, lv = blockIdx.y - set * P.vps;
   const uint32_t p = lv / R.n_rot, r = lv - p * R.n_rot;
   const NttSet S = P.sets[set];
-  stage_twiddles(tw, S.dft_b, LOGM);
+  stage_twiddles(tw, S.dft_b, M / 2);
   Tw t1[8];
   first_twiddles<LOGM>(t1, S.dft_b);
   const uint32_t log_n2 = P.log_n2, N2 = 1u << log_n2, N = M << log_n2;   // M = N1
-  const uint32_t g = R.g[r], cg = (g - 1) / 2, o0 = blockIdx.x * kNttCols;
+  const uint32_t g = R.g[r], cg = (g - 1) / 2;
+  const uint32_t o0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
   const double q = S.q, qinv = S.qinv;
-  const Buf tmp(P.tmp + (uint64_t)blockIdx.y * N, P.tmp_end);
+  const Buf tmp(P.tmp + (uint64_t)blockIdx.y * tmp_words(M, N2), P.tmp_end);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT1; it += kNttThreads) {
     const uint32_t row = G::row(it), ip = G::grp(it);
@@ -173,7 +174,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
       x[u] = tmp.f64_once(ot.v, ot.s);
     }
     first_stages<LOGM>(x, t1, q, qinv);
-    put_first<LOGM>(xs, row, ip, x);
+    put_first<LOGM>(xs, row, ip, x, q, qinv);
   }
   middle_stages<LOGM>(xs, tw, q, qinv);
   const Buf base(P.base + set * P.base_set_stride + lv * P.base_stride, P.base_end),
@@ -193,7 +194,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
       bv[u] = base.u64_once(ow.v, ow.s);
     }
 #pragma unroll
-    for (uint32_t u = 0; u < D::E2; ++u) y[u] = canonical(mul_tw(to_f64(bv[u]) - y[u], S.inv, q), q, qinv);
+    for (uint32_t u = 0; u < D::E2; ++u) y[u] = canonical(mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q), q, qinv);
     if (p == 0) {
       uint64_t av[D::E2];
 #pragma unroll
@@ -265,11 +266,11 @@ struct fiona_rotator {
   const NttSet *down_sets = nullptr;   // [L] forward transforms of q_0 .. q_{L-1}, inv = P^-1 mod q_l
   const NttSet *p_inv_set = nullptr;   // [1] inverse transform of P
   const fiona::LimbConst *limbs = nullptr;   // [L + 1] on the device
-  uint64_t *D = nullptr;               // [L][N] digits
+  double *D = nullptr;                 // [L][N] digits, blocked layout
   uint64_t *Dhat = nullptr;            // [L][L + 1][N], transposed layout
   uint64_t *c0t = nullptr;             // [L][N] c0 of the call, transposed layout
   double *T = nullptr;                 // NTT intermediates: max(L (L + 1), 2 L max_rot) vectors
-  double *W = nullptr;                 // [2 max_rot][N] centred coefficients of u'_P
+  double *W = nullptr;                 // [2 max_rot][N] centred coefficients of u'_P, blocked layout
   uint64_t *U = nullptr;               // [2][n_rot][L + 1][N], transposed layout
   const void *D_end = nullptr, *Dhat_end = nullptr, *c0t_end = nullptr, *T_end = nullptr, *W_end = nullptr,
              *U_end = nullptr;
@@ -277,6 +278,11 @@ struct fiona_rotator {
 };
 
 namespace {
+
+// Bytes of one intermediate.
+size_t tmp_vec_bytes(const fiona_rotator *R) {
+  return fiona::tmp_words(1u << R->log_n1, 1u << R->log_n2) * sizeof(double);
+}
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 
@@ -293,8 +299,7 @@ void launch_rot_pass_b(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipStream_t
     return;
   }
   const dim3 grid((1u << log_n2) / fiona::kNttCols, V);
-  const size_t smem = fiona::kNttCols * fiona::padded_len(1u << log_n1) * sizeof(double) +
-                      (1u << log_n1) / 2 * sizeof(Tw);
+  const size_t smem = pass_smem(1u << log_n1);
   switch (log_n1) {
     case 4: launch_rot_b<4>(grid, smem, stream, P, G); break;
     case 5: launch_rot_b<5>(grid, smem, stream, P, G); break;
@@ -364,7 +369,7 @@ int rotator_layout(const fiona_ctx *ctx, uint64_t special_prime, const uint64_t 
   R->limb_bytes = round256((L + 1) * sizeof(fiona::LimbConst));
   const size_t t_vectors = std::max((size_t)L * (L + 1), (size_t)2 * L * max_rot);
   total = img.bytes() + R->limb_bytes + round256(L * vec) + round256((size_t)L * (L + 1) * vec) +
-          round256(L * vec) + round256(t_vectors * vec) + round256((size_t)2 * max_rot * vec) +
+          round256(L * vec) + round256(t_vectors * tmp_vec_bytes(R)) + round256((size_t)2 * max_rot * vec) +
           round256((size_t)max_rot * 2 * (L + 1) * vec);
   return FIONA_OK;
 }
@@ -389,10 +394,10 @@ void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
   };
   const void *limbs_end = nullptr;
   R->limbs = (const fiona::LimbConst *)take((L + 1) * sizeof(fiona::LimbConst), limbs_end);
-  R->D = (uint64_t *)take(L * vec, R->D_end);
+  R->D = (double *)take(L * vec, R->D_end);
   R->Dhat = (uint64_t *)take((size_t)L * (L + 1) * vec, R->Dhat_end);
   R->c0t = (uint64_t *)take(L * vec, R->c0t_end);
-  R->T = (double *)take(t_vectors * vec, R->T_end);
+  R->T = (double *)take(t_vectors * tmp_vec_bytes(R), R->T_end);
   R->W = (double *)take((size_t)2 * R->max_rot * vec, R->W_end);
   R->U = (uint64_t *)take((size_t)R->max_rot * 2 * (L + 1) * vec, R->U_end);
 }
@@ -420,7 +425,7 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   A.out_end = R->D_end;
   A.out_set_stride = N;
   A.load = fiona::kLoadU64;
-  A.store = fiona::kStoreU64;
+  A.store = fiona::kStoreF64C;
   launch_transform(R->log_n1, R->log_n2, L, stream, A);
   NttPass B{};
   B.sets = R->fwd_sets;
@@ -436,9 +441,8 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   B.out_end = R->Dhat_end;
   B.out_stride = (size_t)M * N;
   B.out_set_stride = N;
-  B.load = fiona::kLoadU64;
-  B.store = fiona::kStoreU64;
-  B.out_transposed = 1;
+  B.load = fiona::kLoadF64;
+  B.store = fiona::kStoreU64T;
   B.nsets_shared = ((1u << R->log_n1) / fiona::kNttCols * L) % 8 == 0 ? M : 0;   // every modulus reads D_j
   launch_transform(R->log_n1, R->log_n2, L * M, stream, B);
   // transpose_kernel: reads limbs 0 .. L-1 of c0, writes L vectors of c0t
@@ -618,8 +622,7 @@ int fiona_rotator_create(const fiona_ctx *ctx, uint64_t special_prime, const uin
       return FIONA_ERR_HIP;
     }
     const int ks_smem = (int)fiona::ks_lds_bytes(R->L, fiona::ks_round(R->L));
-    const int nt_smem = (int)(fiona::kNttCols * fiona::padded_len(fiona::kNttMaxSide) * sizeof(double) +
-                              fiona::kNttMaxSide / 2 * sizeof(Tw));
+    const int nt_smem = (int)pass_smem(fiona::kNttMaxSide);
     if (!allow_smem() || !allow_rot_smem(nt_smem) ||
         hipFuncSetAttribute((const void *)fiona::ks_inner_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             ks_smem) != hipSuccess ||

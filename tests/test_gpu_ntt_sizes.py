@@ -1,0 +1,94 @@
+"""GPU parity of the NTT passes at every side they are built for: rescales and
+rotations at N = 2^8 .. 2^17 (both splits, even and odd log N), with uniform
+residues, residues at the ends of their range and moduli of very different
+sizes, bit-exact against the oracle's integer arithmetic."""
+import sys
+
+import numpy as np
+import pytest
+
+import synth
+import paper_2609_35352_amd as fiona
+from oracle import rescale as rs
+from oracle import rotate as ro
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    fiona.lib()
+    return torch.device("cuda:0")
+
+
+def _moduli(N, mixed):
+    """Three moduli: the largest below 2^50, or a small one, a large one and a large last one."""
+    big = synth.ntt_primes(N, 3)
+    return big if not mixed else [synth.ntt_primes(N, 1, bits=26)[0], big[0], big[1]]
+
+
+def _cts(N, moduli, n_ct, seed):
+    rng = np.random.default_rng(seed)
+    cts = np.zeros((n_ct, 2, len(moduli), N), dtype=np.uint64)
+    for l, q in enumerate(moduli):
+        cts[:, :, l] = rng.integers(0, q, (n_ct, 2, N), dtype=np.uint64)
+        cts[0, 0, l] = q - 1                                        # the ends of the range
+        cts[0, 1, l, ::2] = q - 1
+        cts[0, 1, l, 1::2] = 0
+    return cts
+
+
+def _t(a, dev):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a).reshape(-1).view(np.int64)).to(dev)
+
+
+@pytest.mark.parametrize("log_n", range(8, 18))
+@pytest.mark.parametrize("mixed", [False, True])
+def test_rescale_every_size(dev, log_n, mixed):
+    import torch
+    N, n_ct = 1 << log_n, 2 if log_n > 14 else 3
+    _say("[ntt sizes] rescale N=2^%d mixed=%s" % (log_n, mixed))
+    moduli = _moduli(N, mixed)
+    cts = _cts(N, moduli, n_ct, log_n)
+    r = fiona.Rescaler(fiona.Ctx(N, 3, moduli), n_ct)
+    out = torch.full((n_ct * 2 * 2 * N,), -1, dtype=torch.int64, device=dev)
+    fiona.rescale(r, _t(cts, dev), n_ct, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().view(np.uint64).reshape(n_ct, 2, 2, N)
+    for c in range(n_ct if log_n <= 14 else 1):
+        assert np.array_equal(got[c], rs.rescale(cts[c], moduli)), "ciphertext %d differs" % c
+
+
+@pytest.mark.parametrize("log_n", [8, 9, 10, 13, 14, 15])
+def test_rotate_every_size(dev, log_n):
+    import torch
+    N, L = 1 << log_n, 2
+    _say("[ntt sizes] rotate N=2^%d" % log_n)
+    chain = _moduli(N, False)
+    moduli, P = chain[:2], chain[2]
+    ct = _cts(N, moduli, 1, 40 + log_n)[0]
+    rng = np.random.default_rng(log_n)
+    galois = [5, 2 * N - 1, 1]
+    ctx = fiona.Ctx(N, L, moduli)
+    rot = fiona.Rotator(ctx, P, len(galois))
+    keys = np.zeros((len(galois), L, 2, L + 1, N), dtype=np.uint64)
+    for m, q in enumerate(chain):
+        keys[:, :, :, m] = rng.integers(0, q, (len(galois), L, 2, N), dtype=np.uint64)
+    lib = torch.empty(keys.size, dtype=torch.int64, device=dev)
+    for r, g in enumerate(galois):
+        fiona.rotation_key_layout(rot, g, _t(keys[r], dev), lib[r * rot.key_words():(r + 1) * rot.key_words()])
+    out = torch.full((len(galois) * 2 * L * N,), -1, dtype=torch.int64, device=dev)
+    fiona.hoisted_rotate(rot, _t(ct, dev), galois, lib, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().view(np.uint64).reshape(len(galois), 2, L, N)
+    for r, g in enumerate(galois):
+        assert np.array_equal(got[r], ro.rotate(ct, g, keys[r], moduli, P)), "rotation by element %d differs" % g
