@@ -52,11 +52,18 @@ typedef uint64_t ks_q2 __attribute__((ext_vector_type(2)));
 __host__ __device__ constexpr size_t ks_lds_bytes(uint32_t L, uint32_t round) {
   return (size_t)(L + 1) * kKsTile * sizeof(uint2) + (size_t)round * 2 * kKsTile * sizeof(uint64_t);
 }
-// The most rotations per round that fit the LDS next to the digits.
-inline uint32_t ks_round(uint32_t L) {
+// Rotations per round of a call with n_rot rotations: the fewest rounds whose
+// outputs fit the LDS next to the digits, of equal size.  A call with fewer
+// rotations takes less LDS, so more workgroups share a CU: 34 rotations at
+// N = 2^15, L = 9 585 -> 531 us, 23 at N = 2^14, L = 6 147 -> 137, 7 at
+// N = 2^13, L = 4 48.0 -> 45.3, against the LDS of a full round of 64 for
+// every call.
+inline uint32_t ks_round(uint32_t L, uint32_t n_rot) {
   const size_t free = kKsLdsMax - ks_lds_bytes(L, 0);
-  const size_t r = free / (2 * kKsTile * sizeof(uint64_t));
-  return r < kKsRoundMax ? (uint32_t)r : kKsRoundMax;
+  const size_t fit = free / (2 * kKsTile * sizeof(uint64_t));
+  const uint32_t most = fit < kKsRoundMax ? (uint32_t)fit : kKsRoundMax;
+  const uint32_t rounds = (n_rot + most - 1) / most;
+  return (n_rot + rounds - 1) / rounds;
 }
 
 // Step 2.  Workgroup = (modulus m, tile of 128 coefficients); lane l takes
@@ -71,8 +78,8 @@ inline uint32_t ks_round(uint32_t L) {
 // (writes mixed one by one into the key stream cost more: 2-3% measured).
 // Measured against one coefficient per lane (512-byte loads, 2 workgroups
 // per CU): VGG11's 63 rotations 1.75 -> 1.58 ms, BERT's 31 1.67 -> 1.50 ms,
-// Large's 127 10.0 -> 9.5 ms; with one workgroup per CU here (the LDS of a
-// 64-rotation round).
+// Large's 127 10.0 -> 9.5 ms; with one workgroup per CU at 64 rotations a
+// round.
 template <uint32_t JB>
 __global__ void __launch_bounds__(kKsWaves * 64) ks_inner_kernel(const uint64_t *__restrict__ dhat,
                                                                   const uint64_t *__restrict__ keys,
@@ -457,7 +464,7 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   // 2. the inner products of every rotation (transposed layout, pi^-1 frame)
   //    (batches of 8 digits, or of 4 where that pads fewer: L = 8, 16 take 8, L = 10, 12 take 4)
   const dim3 ks_grid(M * (N / fiona::kKsTile));
-  const uint32_t round = fiona::ks_round(L);
+  const uint32_t round = fiona::ks_round(L, n_rot);
   const size_t ks_smem = fiona::ks_lds_bytes(L, round);
   const uint32_t pad8 = (L + 7) / 8 * 8 - L, pad4 = (L + 3) / 4 * 4 - L;
   // ks_inner_kernel: digits (j < L, m < M, 16 bytes per lane pair), keys of
@@ -621,7 +628,7 @@ int fiona_rotator_create(const fiona_ctx *ctx, uint64_t special_prime, const uin
       fiona_rotator_destroy(R);
       return FIONA_ERR_HIP;
     }
-    const int ks_smem = (int)fiona::ks_lds_bytes(R->L, fiona::ks_round(R->L));
+    const int ks_smem = (int)fiona::ks_lds_bytes(R->L, fiona::ks_round(R->L, fiona::kKsRoundMax));
     const int nt_smem = (int)pass_smem(fiona::kNttMaxSide);
     if (!allow_smem() || !allow_rot_smem(nt_smem) ||
         hipFuncSetAttribute((const void *)fiona::ks_inner_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,

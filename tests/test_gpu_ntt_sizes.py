@@ -70,14 +70,24 @@ def test_rescale_every_size(dev, log_n, mixed):
 
 @pytest.mark.parametrize("log_n", [8, 9, 10, 13, 14, 15])
 def test_rotate_every_size(dev, log_n):
+    _rotate(dev, log_n, [5, 2 * (1 << log_n) - 1, 1], range(3))
+
+
+@pytest.mark.parametrize("n_rot", [64, 65, 130])
+def test_rotate_round_edges(dev, n_rot):
+    """The inner product's rounds of buffered outputs: one of 64, 33 + 32, 44 + 43 + 43."""
+    galois = [pow(5, 1 + r, 512) for r in range(n_rot)]
+    _rotate(dev, 8, galois, [r for r in (0, 32, 33, 43, 44, 63, 64, 87, 88, 129) if r < n_rot])
+
+
+def _rotate(dev, log_n, galois, check):
     import torch
     N, L = 1 << log_n, 2
-    _say("[ntt sizes] rotate N=2^%d" % log_n)
+    _say("[ntt sizes] rotate N=2^%d, %d rotations" % (log_n, len(galois)))
     chain = _moduli(N, False)
     moduli, P = chain[:2], chain[2]
     ct = _cts(N, moduli, 1, 40 + log_n)[0]
     rng = np.random.default_rng(log_n)
-    galois = [5, 2 * N - 1, 1]
     ctx = fiona.Ctx(N, L, moduli)
     rot = fiona.Rotator(ctx, P, len(galois))
     keys = np.zeros((len(galois), L, 2, L + 1, N), dtype=np.uint64)
@@ -90,5 +100,6 @@ def test_rotate_every_size(dev, log_n):
     fiona.hoisted_rotate(rot, _t(ct, dev), galois, lib, out)
     torch.cuda.synchronize()
     got = out.cpu().numpy().view(np.uint64).reshape(len(galois), 2, L, N)
-    for r, g in enumerate(galois):
-        assert np.array_equal(got[r], ro.rotate(ct, g, keys[r], moduli, P)), "rotation by element %d differs" % g
+    for r in check:
+        want = ro.rotate(ct, galois[r], keys[r], moduli, P)
+        assert np.array_equal(got[r], want), "rotation %d (element %d) differs" % (r, galois[r])
