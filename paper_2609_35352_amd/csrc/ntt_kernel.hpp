@@ -598,7 +598,11 @@ struct GeomRot {
 // (parts taken out one at a time, N = 2^16, L = 8, 128 ciphertexts, of 444 us:
 // stores 160, loads 113, mid 57, a separate twist 36; arithmetic alone 221).
 // So the twist rides in the butterflies (no loads, no products) and mid is one
-// double a word instead of a twiddle pair: 447 -> 393 us.  The last groups store rows
+// double a word instead of a twiddle pair: 447 -> 393 us.  The input is issued
+// before the set record and the twiddles are read, and mid (pass B: the
+// minuends) before the barrier, so that their latencies overlap: the whole
+// rescale 980 -> 932 us (loads that pass B issued ahead of its input instead
+// cost 1%: they return in order).  The last groups store rows
 // k2 = o + (u << S0L) of the intermediate, again in runs of kNttCols columns.
 template <uint32_t LOGM, bool FWD>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
@@ -609,64 +613,74 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
   Tw *tw = (Tw *)(xs + kNttCols * D::PM);
   const UnitA un = pass_a_unit(P.vps, P.nsets_shared, blockIdx.x, blockIdx.y, gridDim.x);
   const uint32_t set = un.set, lv = un.lv, cb = un.cb;
+  const uint32_t log_n1 = P.log_n1, N1 = 1u << log_n1, N2 = D::M;
+  const uint64_t v = (uint64_t)set * P.vps + lv;
+  const uint64_t in_off = set * P.in_set_stride + lv * P.in_stride;
+  const bool trans = P.load == kLoadU64T;   // uniform
+  const Buf in((const char *)P.in + in_off * 8, P.in_end);
+  uint64_t w[16];   // the words of a first group, as loaded
+  auto load = [&](uint32_t it) {
+    const uint32_t cl = G::col(it, trans), ip = G::grp(it, trans), n1 = cb * kNttCols + cl;
+    if (!FWD && !trans) {
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u) {
+        const Off o = G::in(n1, ip, u, N1);
+        w[u] = in.u64(o.v, o.s);
+      }
+    } else {
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u) {
+        const Off o = FWD ? G::in_b(cb, cl, ip, u) : G::in_t(n1, ip, u, N1);
+        w[u] = in.u64(o.v, o.s);
+      }
+    }
+  };
+  if (threadIdx.x < D::IT1) load(threadIdx.x);   // in flight while the set record and the twiddles arrive
   const NttSet S = P.sets[set];
   stage_twiddles(tw, S.dft_a, FWD ? D::M : D::M / 2);
   Tw t1[8];
   if constexpr (!FWD) first_twiddles<LOGM>(t1, S.dft_a);
-  const uint32_t log_n1 = P.log_n1, N1 = 1u << log_n1, N2 = D::M;
-  const uint64_t v = (uint64_t)set * P.vps + lv;
-  const uint64_t in_off = set * P.in_set_stride + lv * P.in_stride;
   const double q = S.q, qinv = S.qinv;
-  const bool trans = P.load == kLoadU64T;   // uniform
-  const Buf in((const char *)P.in + in_off * 8, P.in_end);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT1; it += kNttThreads) {
     const uint32_t cl = G::col(it, trans), ip = G::grp(it, trans);
-    const uint32_t n1 = cb * kNttCols + cl;
+    if (D::IT1 > kNttThreads && it != threadIdx.x) load(it);
     double r[16];
     if constexpr (FWD) {
 #pragma unroll
-      for (uint32_t u = 0; u < 16; ++u) {
-        const Off o = G::in_b(cb, cl, ip, u);
-        r[u] = in.f64(o.v, o.s);
-      }
+      for (uint32_t u = 0; u < 16; ++u) r[u] = __builtin_bit_cast(double, w[u]);
       tree_first<LOGM>(xs, cl, ip, r, S.dft_a, q, qinv);
     } else {
-      uint64_t w[16];
-      if (trans) {
-#pragma unroll
-        for (uint32_t u = 0; u < 16; ++u) {
-          const Off o = G::in_t(n1, ip, u, N1);
-          w[u] = in.u64(o.v, o.s);
-        }
-      } else {
-#pragma unroll
-        for (uint32_t u = 0; u < 16; ++u) {
-          const Off o = G::in(n1, ip, u, N1);
-          w[u] = in.u64(o.v, o.s);
-        }
-      }
 #pragma unroll
       for (uint32_t u = 0; u < 16; ++u) r[u] = to_f64(w[u]);
       first_stages<LOGM>(r, t1, q, qinv);
       put_first<LOGM>(xs, cl, ip, r, q, qinv);
     }
   }
+  const Buf tmp(P.tmp + v * tmp_words(N1, N2), P.tmp_end), mid(S.mid, S.mid + (size_t)N1 * N2);
+  double m[D::E2];   // mid of a last group
+  auto load_mid = [&](uint32_t it) {
+#pragma unroll
+    for (uint32_t u = 0; u < D::E2; ++u) {
+      const Off om = G::mid(cb, G::col2(it), G::off2(it), u);
+      m[u] = mid.f64(om.v, om.s);
+    }
+  };
+  load_mid(threadIdx.x);   // in flight over the barrier and the last stages
   if constexpr (FWD) tree_middle<LOGM>(xs, tw, q);
   else middle_stages<LOGM>(xs, tw, q, qinv);
-  const Buf tmp(P.tmp + v * tmp_words(N1, N2), P.tmp_end), mid(S.mid, S.mid + (size_t)N1 * N2);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT2; it += kNttThreads) {
     const uint32_t cl = G::col2(it), o = G::off2(it), n1 = cb * kNttCols + cl;
+    if (D::IT2 > kNttThreads && it != threadIdx.x) load_mid(it);
     double r[D::E2];
     if constexpr (FWD) tree_last<LOGM>(xs, cl, o, tw, r, q);
     else last_stages<LOGM>(xs, cl, o, tw, r, q, qinv);
 #pragma unroll
     for (uint32_t u = 0; u < D::E2; ++u) {
-      const Off om = G::mid(cb, cl, o, u), ot = G::tmp(o, n1, u, N1);
+      const Off ot = G::tmp(o, n1, u, N1);
       const uint32_t e = FWD ? rev4(u) >> (4 - D::R2) : u;
-      const double w = mid.f64(om.v, om.s);
-      tmp.put(mul_tw(r[e], Tw{w, w * qinv}, q), ot.v, ot.s);
+      tmp.put(mul_tw(r[e], Tw{m[u], m[u] * qinv}, q), ot.v, ot.s);
     }
   }
 }
@@ -683,37 +697,49 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
   extern __shared__ double xs[];   // [kNttCols][PM], then the M/2 DFT twiddles
   Tw *tw = (Tw *)(xs + kNttCols * D::PM);
   const uint32_t set = blockIdx.y / P.vps, lv = blockIdx.y - set * P.vps;
+  const uint32_t N2 = 1u << P.log_n2, M = D::M;
+  const uint32_t r0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
+  const uint64_t v = blockIdx.y;
+  const Buf tmp(P.tmp + v * tmp_words(M, N2) + (size_t)r0 * tmp_pitch(M), P.tmp_end);
+  double x[16];   // a first group, as loaded
+  auto load = [&](uint32_t it) {
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u) {
+      const Off o = G::tmp(G::row(it), G::grp(it), u);
+      x[u] = tmp.f64_once(o.v, o.s);
+    }
+  };
+  if (threadIdx.x < D::IT1) load(threadIdx.x);   // in flight while the set record and the twiddles arrive
   const NttSet S = P.sets[set];
   stage_twiddles(tw, S.dft_b, D::M / 2);
   Tw t1[8];
   first_twiddles<LOGM>(t1, S.dft_b);
-  const uint32_t N2 = 1u << P.log_n2, M = D::M;
-  const uint32_t r0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
-  const uint64_t v = blockIdx.y;
   const double q = S.q, qinv = S.qinv;
-  const Buf tmp(P.tmp + v * tmp_words(M, N2) + (size_t)r0 * tmp_pitch(M), P.tmp_end);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT1; it += kNttThreads) {
-    const uint32_t row = G::row(it), ip = G::grp(it);
-    double r[16];
-#pragma unroll
-    for (uint32_t u = 0; u < 16; ++u) {
-      const Off o = G::tmp(row, ip, u);
-      r[u] = tmp.f64_once(o.v, o.s);
-    }
-    first_stages<LOGM>(r, t1, q, qinv);
-    put_first<LOGM>(xs, row, ip, r, q, qinv);
+    if (D::IT1 > kNttThreads && it != threadIdx.x) load(it);
+    first_stages<LOGM>(x, t1, q, qinv);
+    put_first<LOGM>(xs, G::row(it), G::grp(it), x, q, qinv);
   }
-  middle_stages<LOGM>(xs, tw, q, qinv);
-  const bool transposed = P.store == kStoreU64T;   // uniform
-  const bool rescale = P.store == kStoreRescale;
+  const bool transposed = P.store == kStoreU64T, rescale = P.store == kStoreRescale;   // uniform
   const Buf out((const char *)P.out + (set * P.out_set_stride + lv * P.out_stride) * 8, P.out_end);
   const Buf base(rescale ? P.base + set * P.base_set_stride + lv * P.base_stride : nullptr,
                  rescale ? P.base_end : nullptr);
+  uint64_t bv[D::E2];   // the minuends of a last group
+  auto load_base = [&](uint32_t it) {
+#pragma unroll
+    for (uint32_t u = 0; u < D::E2; ++u) {
+      const Off oc = G::col(r0 + G::row2(it, false), G::off2(it, false), u, N2);
+      bv[u] = base.u64_once(oc.v, oc.s);
+    }
+  };
+  if (rescale) load_base(threadIdx.x);   // in flight over the barrier and the last stages
+  middle_stages<LOGM>(xs, tw, q, qinv);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT2; it += kNttThreads) {
     const uint32_t row = G::row2(it, transposed), o = G::off2(it, transposed);
     const uint32_t k2 = r0 + row;   // output k2 + N2 k1, k1 = o + (u << S0L)
+    if (D::IT2 > kNttThreads && rescale && it != threadIdx.x) load_base(it);
     double y[D::E2];
     last_stages<LOGM>(xs, row, o, tw, y, q, qinv);
     if (S.post) {
@@ -732,29 +758,18 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
         if (P.store == kStoreF64C && z < 0.0) z += q;
         out.put(z, ob.v, ob.s);
       }
-      continue;
-    }
-    if (rescale) {
-      uint64_t bv[D::E2];
+    } else if (rescale) {
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
         const Off oc = G::col(k2, o, u, N2);
-        bv[u] = base.u64_once(oc.v, oc.s);
-      }
-#pragma unroll
-      for (uint32_t u = 0; u < D::E2; ++u) y[u] = mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q);
-    }
-    if (transposed) {
-#pragma unroll
-      for (uint32_t u = 0; u < D::E2; ++u) {
-        const Off ot = G::row_t(k2, o, u);
-        out.put(to_u64(canonical(y[u], q, qinv)), ot.v, ot.s);
+        const double z = mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q);
+        out.put(to_u64(canonical(z, q, qinv)), oc.v, oc.s);
       }
     } else {
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
-        const Off oc = G::col(k2, o, u, N2);
-        out.put(to_u64(canonical(y[u], q, qinv)), oc.v, oc.s);
+        const Off ot = G::row_t(k2, o, u);
+        out.put(to_u64(canonical(y[u], q, qinv)), ot.v, ot.s);
       }
     }
   }

@@ -161,47 +161,56 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
   Tw *tw = (Tw *)(xs + kNttCols * PM);
   const uint32_t set = blockIdx.y / P.vps, lv = blockIdx.y - set * P.vps;
   const uint32_t p = lv / R.n_rot, r = lv - p * R.n_rot;
+  const uint32_t log_n2 = P.log_n2, N2 = 1u << log_n2, N = M << log_n2;   // M = N1
+  const uint32_t g = R.g[r], cg = (g - 1) / 2;
+  const uint32_t o0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
+  const Buf tmp(P.tmp + (uint64_t)blockIdx.y * tmp_words(M, N2), P.tmp_end);
+  double x[16];   // a first group, as loaded
+  auto load = [&](uint32_t it) {
+    const uint32_t k2 = G::src_row(g, o0 + G::row(it), N2);
+#pragma unroll
+    for (uint32_t u = 0; u < 16; ++u) {
+      const Off ot = G::tmp(k2, G::grp(it), u);
+      x[u] = tmp.f64_once(ot.v, ot.s);
+    }
+  };
+  if (threadIdx.x < D::IT1) load(threadIdx.x);   // in flight while the set record and the twiddles arrive
   const NttSet S = P.sets[set];
   stage_twiddles(tw, S.dft_b, M / 2);
   Tw t1[8];
   first_twiddles<LOGM>(t1, S.dft_b);
-  const uint32_t log_n2 = P.log_n2, N2 = 1u << log_n2, N = M << log_n2;   // M = N1
-  const uint32_t g = R.g[r], cg = (g - 1) / 2;
-  const uint32_t o0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
   const double q = S.q, qinv = S.qinv;
-  const Buf tmp(P.tmp + (uint64_t)blockIdx.y * tmp_words(M, N2), P.tmp_end);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT1; it += kNttThreads) {
-    const uint32_t row = G::row(it), ip = G::grp(it);
-    const uint32_t k2 = G::src_row(g, o0 + row, N2);
-    double x[16];
-#pragma unroll
-    for (uint32_t u = 0; u < 16; ++u) {
-      const Off ot = G::tmp(k2, ip, u);
-      x[u] = tmp.f64_once(ot.v, ot.s);
-    }
+    if (D::IT1 > kNttThreads && it != threadIdx.x) load(it);
     first_stages<LOGM>(x, t1, q, qinv);
-    put_first<LOGM>(xs, row, ip, x, q, qinv);
+    put_first<LOGM>(xs, G::row(it), G::grp(it), x, q, qinv);
   }
-  middle_stages<LOGM>(xs, tw, q, qinv);
   const Buf base(P.base + set * P.base_set_stride + lv * P.base_stride, P.base_end),
       add(P.add + set * P.add_set_stride, P.add_end);
+  uint64_t bv[D::E2];   // u' of a last group
+  auto load_base = [&](uint32_t it) {
+    const uint32_t k2c = G::src_row(g, o0 + G::row2(it), N2);
+#pragma unroll
+    for (uint32_t u = 0; u < D::E2; ++u) {
+      const Off ow = G::word(k2c, G::off2(it), u);
+      bv[u] = base.u64_once(ow.v, ow.s);
+    }
+  };
+  load_base(threadIdx.x);   // in flight over the barrier and the last stages
+  middle_stages<LOGM>(xs, tw, q, qinv);
   // row cc of the workgroup (k2 of destination column o0 + cc), outputs k1:
   // (u' - transform) * P^-1, plus c0 for the first polynomial, into LDS
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT2; it += kNttThreads) {
     const uint32_t cc = G::row2(it), o = G::off2(it);
     const uint32_t k2c = G::src_row(g, o0 + cc, N2);
+    if (D::IT2 > kNttThreads && it != threadIdx.x) load_base(it);
     double y[D::E2];
     last_stages<LOGM>(xs, cc, o, tw, y, q, qinv);
-    uint64_t bv[D::E2];
 #pragma unroll
-    for (uint32_t u = 0; u < D::E2; ++u) {
-      const Off ow = G::word(k2c, o, u);
-      bv[u] = base.u64_once(ow.v, ow.s);
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < D::E2; ++u) y[u] = canonical(mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q), q, qinv);
+    for (uint32_t u = 0; u < D::E2; ++u)
+      y[u] = canonical(mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q), q, qinv);
     if (p == 0) {
       uint64_t av[D::E2];
 #pragma unroll
