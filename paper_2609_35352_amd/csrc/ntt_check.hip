@@ -185,12 +185,14 @@ bool pass_b_rot(Checker &C, const PassLaunch &L) {
   if (P.log_n2 != L.log_other || N2 < kNttCols || R.n_rot == 0 || R.n_rot > fiona::kRotMax)
     return C.fail("rotation pass B: bad shape");
   // per (column block, rotation): the rows read depend on the Galois element
-  std::vector<uint64_t> tmp_hi((size_t)gx * R.n_rot, 0), word_hi((size_t)gx * R.n_rot, 0), out_hi(gx, 0);
+  std::vector<uint64_t> tmp_hi((size_t)gx * R.n_rot, 0), word_hi((size_t)gx * R.n_rot, 0), add_hi((size_t)gx * R.n_rot, 0),
+      out_hi(gx, 0);
   for (uint32_t x = 0; x < gx; ++x) {
     const uint32_t o0 = x * kNttCols;
     for (uint32_t r = 0; r < R.n_rot; ++r) {
       const uint32_t g = R.g[r];
-      uint64_t &th = tmp_hi[(size_t)x * R.n_rot + r], &wh = word_hi[(size_t)x * R.n_rot + r];
+      uint64_t &th = tmp_hi[(size_t)x * R.n_rot + r], &wh = word_hi[(size_t)x * R.n_rot + r],
+               &ah = add_hi[(size_t)x * R.n_rot + r];
       for (uint32_t it = 0; it < D::IT1; ++it) {
         const uint32_t k2 = G::src_row(g, o0 + G::row(it), N2);
         for (uint32_t u = 0; u < 16; ++u)
@@ -199,7 +201,10 @@ bool pass_b_rot(Checker &C, const PassLaunch &L) {
       for (uint32_t it = 0; it < D::IT2; ++it) {
         const uint32_t k2c = G::src_row(g, o0 + G::row2(it), N2);
         for (uint32_t u = 0; u < D::E2; ++u)
-          if (!C.grow(wh, G::word(k2c, G::off2(it), u), 8, "rotation pass B u'/c0")) return false;
+          if (!C.grow(wh, G::word(k2c, G::off2(it), u), 8, "rotation pass B u'") ||
+              !C.grow(ah, R.c0_natural ? G::natural(k2c, G::off2(it), u, N2) : G::word(k2c, G::off2(it), u), 8,
+                      "rotation pass B c0"))
+            return false;
       }
     }
     for (uint32_t t = 0; t < fiona::kNttThreads; ++t)
@@ -216,7 +221,7 @@ bool pass_b_rot(Checker &C, const PassLaunch &L) {
       if (!C.span("rotation pass B tmp", (uint64_t)P.tmp + (uint64_t)by * fiona::tmp_words(D::M, N2) * 8, 0, tmp_hi[xr], P.tmp_end) ||
           !C.span("rotation pass B u'", (uint64_t)P.base + (set * P.base_set_stride + lv * P.base_stride) * 8, 0,
                   word_hi[xr], P.base_end) ||
-          (p == 0 && !C.span("rotation pass B c0", (uint64_t)P.add + set * P.add_set_stride * 8, 0, word_hi[xr],
+          (p == 0 && !C.span("rotation pass B c0", (uint64_t)P.add + set * P.add_set_stride * 8, 0, add_hi[xr],
                              P.add_end)) ||
           !C.span("rotation pass B output", (uint64_t)P.out + (((uint64_t)r * 2 + p) * R.L + set) * N * 8, 0,
                   out_hi[x], P.out_end))

@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "ntt_kernel.hpp"
@@ -226,6 +227,18 @@ inline std::vector<Region> table_regions(const TableImage &img, const void *dev)
   return r;
 }
 
+// f(integral_constant<uint32_t, log_n>) for 8 <= log_n <= MAX.
+template <uint32_t MAX, uint32_t LN = 8, typename F>
+void for_log_n(uint32_t log_n, F &&f) {
+  if (log_n == LN) f(std::integral_constant<uint32_t, LN>());
+  else if constexpr (LN < MAX) for_log_n<MAX, LN + 1>(log_n, f);
+}
+
+// Lets a kernel use bytes of dynamic LDS.
+inline bool allow_lds(const void *kernel, size_t bytes) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+}
+
 // The passes are instantiated per DFT side 2^4 .. 2^9.
 template <uint32_t LOG>
 void launch_pair(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPass &P) {
@@ -268,17 +281,17 @@ inline void launch_transform(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipSt
 }
 
 template <uint32_t LOG>
-bool allow_smem_one(int bytes) {
+bool allow_smem_one(size_t bytes) {
   const void *k[3] = {(const void *)fiona::ntt_pass_a<LOG, true>, (const void *)fiona::ntt_pass_a<LOG, false>,
                       (const void *)fiona::ntt_pass_b<LOG>};
   for (const void *f : k)
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return false;
+    if (!allow_lds(f, bytes)) return false;
   return true;
 }
 
 // Lets every pass use the LDS of its largest side.
 inline bool allow_smem() {
-  const int smem = (int)pass_smem(fiona::kNttMaxSide);
+  const size_t smem = pass_smem(fiona::kNttMaxSide);
   return allow_smem_one<4>(smem) && allow_smem_one<5>(smem) && allow_smem_one<6>(smem) &&
          allow_smem_one<7>(smem) && allow_smem_one<8>(smem) && allow_smem_one<9>(smem);
 }

@@ -561,6 +561,7 @@ constexpr uint32_t kRotMax = 256;   // rotations per call (their Galois elements
 struct RotArgs {
   uint32_t g[kRotMax];
   uint32_t n_rot, L;
+  uint32_t c0_natural;   // NttPass::add is in natural order, not transposed
 };
 
 template <uint32_t LOGM>
@@ -582,6 +583,10 @@ struct GeomRot {
   static __host__ __device__ uint32_t off2(uint32_t it) { return it % D::I2; }
   static __host__ __device__ Off word(uint32_t k2, uint32_t o, uint32_t u) {
     return Off{(k2 * D::M + o) * 8, (u << D::S0L) * 8};
+  }
+  // the same word in natural order
+  static __host__ __device__ Off natural(uint32_t k2, uint32_t o, uint32_t u, uint32_t N2) {
+    return Off{(k2 + N2 * o) * 8, (N2 * 8 << D::S0L) * u};
   }
   // store j of thread t: column o0 + t mod 16, destination row d_hi = t / 16 + 16 j
   static __host__ __device__ Off out(uint32_t o0, uint32_t t, uint32_t j, uint32_t N2) {

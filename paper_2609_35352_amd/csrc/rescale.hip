@@ -18,6 +18,7 @@
 #include "fiona.h"
 #include "fiona_ctx.hpp"
 #include "ntt_host.hpp"
+#include "ntt_whole.hpp"
 
 using namespace fiona_host;
 
@@ -37,6 +38,16 @@ struct fiona_rescaler {
 };
 
 namespace {
+
+// Whether V vectors go as one launch of whole transforms (ntt_whole.hpp): up
+// to N = 2^13 always; at 2^14, where a workgroup fills a CU, from 160 forward
+// transforms on (L = 6, 16 ciphertexts, 160 of them: 32.5 us in passes, 31.9
+// whole; 128 ciphertexts 186 and 116; but 4, 40 of them, 21.2 and 28.9).
+constexpr uint32_t kWholeAlways = 13, kWholeMax = 14, kWholeTransforms = 160;
+bool use_whole(const fiona_rescaler *R, uint32_t V) {
+  const uint32_t log_n = R->log_n1 + R->log_n2;
+  return log_n <= kWholeAlways || (log_n <= kWholeMax && (uint64_t)V * (R->L - 1) >= kWholeTransforms);
+}
 
 // Bytes of one limb's intermediates.
 size_t tmp_vec_bytes(const fiona_rescaler *R) {
@@ -85,7 +96,7 @@ int rescaler_layout(const fiona_ctx *ctx, const uint64_t *psi, uint32_t max_ct, 
   if (lpl > fit) lpl = fit;
   if (lpl > fit_grid) lpl = fit_grid;
   R->limbs_per_launch = lpl < 1 ? 1 : (uint32_t)lpl;
-  total = img.bytes() + vec_bytes + R->limbs_per_launch * tmp_bytes;
+  total = img.bytes() + (logN <= kWholeAlways ? 0 : vec_bytes + R->limbs_per_launch * tmp_bytes);
   return FIONA_OK;
 }
 
@@ -96,8 +107,30 @@ void rescaler_place(fiona_rescaler *R, const TableImage &img, void *dev) {
   R->sets = img.sets_addr(dev);
   R->W = (double *)((char *)dev + img.bytes());
   R->T = (double *)((char *)dev + img.bytes() + vec_bytes);
+  if (R->log_n1 + R->log_n2 <= kWholeAlways) {   // no workspace: every call is whole
+    R->W = R->T = nullptr;
+    return;
+  }
   R->W_end = (const char *)R->W + vec_bytes;
   R->T_end = (const char *)R->T + R->limbs_per_launch * tmp_vec_bytes(R);
+}
+
+void launch_whole(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t V, uint64_t *out_cts, hipStream_t stream) {
+  const uint32_t L = R->L;
+  const size_t in_words = (size_t)V * L * R->N, out_words = (size_t)V * (L - 1) * R->N;
+  if (launch_recorder()) {   // every word of the input and of the output, once; every set's tables
+    record_span("whole rescale: in_cts", in_cts, 0, in_words * 8);
+    record_span("whole rescale: out_cts", out_cts, 0, out_words * 8);
+    record_span("whole rescale: sets", R->sets, 0, L * sizeof(NttSet));
+    return;
+  }
+  for_log_n<kWholeMax>(R->log_n1 + R->log_n2, [&](auto ln) {
+    constexpr uint32_t LN = decltype(ln)::value;
+    const uint32_t groups = fiona::whole_groups<LN>(V, L - 1);
+    hipLaunchKernelGGL(fiona::whole_rescale_kernel<LN>, dim3(V * groups), dim3(fiona::Whole<LN>::T),
+                       fiona::whole_smem<LN>(), stream, in_cts, out_cts, R->sets, L, groups,
+                       (const void *)(in_cts + in_words), (const void *)(out_cts + out_words));
+  });
 }
 
 // The launches of one rescale (arguments already checked).
@@ -105,6 +138,7 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
                      hipStream_t stream) {
   const size_t N = R->N, L = R->L;
   const uint32_t V = 2 * n_ct;
+  if (use_whole(R, V)) return launch_whole(R, in_cts, V, out_cts, stream);
   const void *in_end = in_cts + (size_t)n_ct * 2 * L * N, *out_end = out_cts + (size_t)n_ct * 2 * (L - 1) * N;
 
   // 1. the last limb back to its coefficients, kept as centred residues mod q_t
@@ -231,7 +265,9 @@ int fiona_rescaler_create(const fiona_ctx *ctx, const uint64_t *psi, uint32_t ma
       return FIONA_ERR_NOMEM;
     }
     rescaler_place(R, img, dev);
-    if (!img.upload(R->dev) || !allow_smem()) {
+    if (!img.upload(R->dev) || !allow_smem() ||
+        !allow_lds((const void *)fiona::whole_rescale_kernel<13>, fiona::whole_smem<13>()) ||
+        !allow_lds((const void *)fiona::whole_rescale_kernel<14>, fiona::whole_smem<14>())) {
       fiona_rescaler_destroy(R);
       return FIONA_ERR_HIP;
     }

@@ -34,6 +34,7 @@
 #include "fiona_ctx.hpp"
 #include "modarith.hpp"
 #include "ntt_host.hpp"
+#include "ntt_whole.hpp"
 
 using namespace fiona_host;
 
@@ -215,8 +216,8 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
       uint64_t av[D::E2];
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
-        const Off ow = G::word(k2c, o, u);
-        av[u] = add.u64(ow.v, ow.s);
+        const Off oa = R.c0_natural ? G::natural(k2c, o, u, N2) : G::word(k2c, o, u);
+        av[u] = add.u64(oa.v, oa.s);
       }
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
@@ -418,15 +419,67 @@ void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
   R->U = (uint64_t *)take((size_t)R->max_rot * 2 * (L + 1) * vec, R->U_end);
 }
 
-// The launches of one call (arguments already checked).
-void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, const uint32_t *galois,
-                    const uint64_t *keys, uint64_t *out_cts, hipStream_t stream) {
-  const uint32_t N = R->N, L = R->L;
-  const uint32_t M = L + 1;
-  const void *ct_end = ct + (size_t)2 * L * N, *out_end = out_cts + (size_t)n_rot * 2 * L * N;
+// Which steps of a call go as launches of whole transforms (ntt_whole.hpp).
+// The digits up to N = 2^12 (one rotation at 2^12, L = 6: 42.6 us in passes,
+// 34.5 whole; at 2^13 within 3% of each other, 7 rotations at L = 4 44.8 and
+// 46.3; at 2^14 51.6 and 61.1: a workgroup's chain of two transforms).  The division by P up to N = 2^12, and at 2^13
+// from 256 forward transforms on (L = 6, 64 rotations, 768 of them: 170 us in
+// passes, 158 whole; 4 rotations, 48 of them, 45.3 and 49.5).
+constexpr uint32_t kDigitsMax = 12, kDivideAlways = 12, kDivideMax = 13, kDivideTransforms = 256;
+bool whole_digits(const fiona_rotator *R) { return R->log_n1 + R->log_n2 <= kDigitsMax; }
+bool whole_divide(const fiona_rotator *R, uint32_t V) {
+  const uint32_t log_n = R->log_n1 + R->log_n2;
+  return log_n <= kDivideAlways || (log_n <= kDivideMax && V * R->L >= kDivideTransforms);
+}
 
-  // 1. digits of c1, once: D_j = INTT_{q_j}(c1_j), then Dhat[j][m] = NTT_m(D_j)
-  //    (transposed layout); c0 transposed for step 3
+// The passes' division reads c0 in natural order, words sqrt(N) apart, while
+// it has few words to read that way; more than these take a transposed copy, a
+// launch of 4 us that then pays (L = 6, N = 2^13: 4 rotations 45.5 us with the
+// copy, 43.4 without; 2^14: 7 71.1 and 69.0, 16 103.5 and 107.4; 2^16: 1 102.9
+// and 98.9, 4 139.0 and 140.0).
+constexpr uint64_t kC0NaturalWords = 1u << 17;
+
+// Digits: reads c1, writes every digit's transforms.
+void launch_whole_digits(const fiona_rotator *R, const uint64_t *ct, hipStream_t stream) {
+  const uint32_t N = R->N, L = R->L;
+  if (launch_recorder()) {
+    record_span("whole digits: c1", ct, (uint64_t)L * N * 8, (uint64_t)2 * L * N * 8);
+    record_span("whole digits: Dhat", R->Dhat, 0, (uint64_t)L * (L + 1) * N * 8);
+    record_span("whole digits: sets", R->inv_sets, 0, (2 * L + 1) * sizeof(NttSet));
+    return;
+  }
+  for_log_n<kDigitsMax>(R->log_n1 + R->log_n2, [&](auto ln) {
+    constexpr uint32_t LN = decltype(ln)::value;
+    const uint32_t groups = fiona::whole_groups<LN>(L, L + 1);
+    hipLaunchKernelGGL(fiona::whole_digits_kernel<LN>, dim3(L * groups), dim3(fiona::Whole<LN>::T),
+                       fiona::whole_smem<LN>(), stream, ct + (size_t)L * N, R->Dhat, R->inv_sets, R->fwd_sets, L,
+                       groups, (const void *)(ct + (size_t)2 * L * N), R->Dhat_end);
+  });
+}
+// Division: reads u' of the call's V vectors and c0, writes every output.
+void launch_whole_divide(const fiona_rotator *R, const uint64_t *ct, uint64_t *out, uint32_t V, const fiona::RotArgs &G,
+                         hipStream_t stream) {
+  const uint32_t N = R->N, L = R->L;
+  if (launch_recorder()) {
+    record_span("whole division: U", R->U, 0, (uint64_t)V * (L + 1) * N * 8);
+    record_span("whole division: c0", ct, 0, (uint64_t)L * N * 8);
+    record_span("whole division: out_cts", out, 0, (uint64_t)V * L * N * 8);
+    record_span("whole division: sets", R->down_sets, 0, (L + 1) * sizeof(NttSet));
+    return;
+  }
+  for_log_n<kDivideMax>(R->log_n1 + R->log_n2, [&](auto ln) {
+    constexpr uint32_t LN = decltype(ln)::value;
+    const uint32_t groups = fiona::whole_groups<LN>(V, L);
+    hipLaunchKernelGGL(fiona::whole_divide_kernel<LN>, dim3(V * groups), dim3(fiona::Whole<LN>::T),
+                       fiona::whole_smem<LN>(), stream, R->U, ct, out, R->p_inv_set, R->down_sets, groups, R->U_end,
+                       (const void *)(ct + (size_t)2 * L * N), (const void *)(out + (size_t)V * L * N), G);
+  });
+}
+
+// The digits as two transforms of two passes each.
+void digits_by_passes(const fiona_rotator *R, const uint64_t *ct, hipStream_t stream) {
+  const uint32_t N = R->N, L = R->L, M = L + 1;
+  const void *ct_end = ct + (size_t)2 * L * N;
   NttPass A{};
   A.sets = R->inv_sets;
   A.vps = 1;
@@ -461,13 +514,29 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   B.store = fiona::kStoreU64T;
   B.nsets_shared = ((1u << R->log_n1) / fiona::kNttCols * L) % 8 == 0 ? M : 0;   // every modulus reads D_j
   launch_transform(R->log_n1, R->log_n2, L * M, stream, B);
-  // transpose_kernel: reads limbs 0 .. L-1 of c0, writes L vectors of c0t
-  if (launch_recorder()) {
-    record_span("transpose: c0", ct, 0, (uint64_t)L * N * 8);
-    record_span("transpose: c0t", R->c0t, 0, (uint64_t)L * N * 8);
-  } else {
-    hipLaunchKernelGGL(fiona::transpose_kernel, dim3((N + 255) / 256, L), dim3(256), 0, stream, ct, R->c0t,
-                       R->log_n1, R->log_n2);
+}
+
+// The launches of one call (arguments already checked).
+void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, const uint32_t *galois,
+                    const uint64_t *keys, uint64_t *out_cts, hipStream_t stream) {
+  const uint32_t N = R->N, L = R->L;
+  const uint32_t M = L + 1;
+  const void *out_end = out_cts + (size_t)n_rot * 2 * L * N;
+  const uint32_t V = 2 * n_rot;
+  // 1. digits of c1, once: D_j = INTT_{q_j}(c1_j), then Dhat[j][m] = NTT_m(D_j)
+  //    (transposed layout); c0 transposed for the fused pass of step 3 (see kC0NaturalWords)
+  if (whole_digits(R)) launch_whole_digits(R, ct, stream);
+  else digits_by_passes(R, ct, stream);
+  const bool c0_natural = (uint64_t)n_rot * N <= kC0NaturalWords;
+  if (!whole_divide(R, V) && !c0_natural) {
+    // transpose_kernel: reads limbs 0 .. L-1 of c0, writes L vectors of c0t
+    if (launch_recorder()) {
+      record_span("transpose: c0", ct, 0, (uint64_t)L * N * 8);
+      record_span("transpose: c0t", R->c0t, 0, (uint64_t)L * N * 8);
+    } else {
+      hipLaunchKernelGGL(fiona::transpose_kernel, dim3((N + 255) / 256, L), dim3(256), 0, stream, ct, R->c0t,
+                         R->log_n1, R->log_n2);
+    }
   }
 
   // 2. the inner products of every rotation (transposed layout, pi^-1 frame)
@@ -496,7 +565,12 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   // 3. the division by P: u'_P back to centred coefficients (W), then per
   //    data limb its transform, the subtraction from u', the product with
   //    P^-1, c0 for the first polynomials and the automorphism, written to out
-  const uint32_t V = 2 * n_rot;
+  fiona::RotArgs G{};
+  for (uint32_t r = 0; r < n_rot; ++r) G.g[r] = galois[r];
+  G.n_rot = n_rot;
+  G.L = L;
+  G.c0_natural = c0_natural;
+  if (whole_divide(R, V)) return launch_whole_divide(R, ct, out_cts, V, G, stream);
   NttPass C{};
   C.sets = R->p_inv_set;
   C.vps = V;
@@ -529,17 +603,13 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   Q.base_end = R->U_end;
   Q.base_stride = (size_t)M * N;
   Q.base_set_stride = N;
-  Q.add = R->c0t;
-  Q.add_end = R->c0t_end;
+  Q.add = c0_natural ? ct : R->c0t;
+  Q.add_end = c0_natural ? (const void *)(ct + (size_t)2 * L * N) : R->c0t_end;
   Q.add_set_stride = N;
   Q.load = fiona::kLoadF64;
   const uint32_t col_blocks = (1u << R->log_n1) / fiona::kNttCols;
   Q.nsets_shared = L > 1 && (col_blocks * V) % 8 == 0 ? L : 0;
   launch_pass(true, R->log_n2, R->log_n1, L * V, stream, Q);
-  fiona::RotArgs G{};
-  for (uint32_t r = 0; r < n_rot; ++r) G.g[r] = galois[r];
-  G.n_rot = n_rot;
-  G.L = L;
   launch_rot_pass_b(R->log_n1, R->log_n2, L * V, stream, Q, G);
 }
 
@@ -639,7 +709,8 @@ int fiona_rotator_create(const fiona_ctx *ctx, uint64_t special_prime, const uin
     }
     const int ks_smem = (int)fiona::ks_lds_bytes(R->L, fiona::ks_round(R->L, fiona::kKsRoundMax));
     const int nt_smem = (int)pass_smem(fiona::kNttMaxSide);
-    if (!allow_smem() || !allow_rot_smem(nt_smem) ||
+    if (!allow_lds((const void *)fiona::whole_divide_kernel<13>, fiona::whole_smem<13>()) ||
+        !allow_smem() || !allow_rot_smem(nt_smem) ||
         hipFuncSetAttribute((const void *)fiona::ks_inner_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             ks_smem) != hipSuccess ||
         hipFuncSetAttribute((const void *)fiona::ks_inner_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize,

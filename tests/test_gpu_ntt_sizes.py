@@ -103,3 +103,28 @@ def _rotate(dev, log_n, galois, check):
     for r in check:
         want = ro.rotate(ct, galois[r], keys[r], moduli, P)
         assert np.array_equal(got[r], want), "rotation %d (element %d) differs" % (r, galois[r])
+
+
+@pytest.mark.parametrize("log_n,L,n_ct", [(8, 2, 1), (9, 4, 40), (10, 7, 3), (12, 6, 33), (13, 3, 1), (14, 3, 39), (14, 3, 40)])
+def test_rescale_groups_of_limbs(dev, log_n, L, n_ct):
+    """Whole transforms with one and several limbs a workgroup, and the edge
+    of their use at N = 2^14 (160 forward transforms)."""
+    import torch
+    N = 1 << log_n
+    _say("[ntt sizes] rescale N=2^%d L=%d n_ct=%d" % (log_n, L, n_ct))
+    moduli = synth.ntt_primes(N, L)
+    cts = _cts(N, moduli, n_ct, 7 * log_n + L)
+    r = fiona.Rescaler(fiona.Ctx(N, L, moduli), n_ct)
+    out = torch.full((n_ct * 2 * (L - 1) * N,), -1, dtype=torch.int64, device=dev)
+    fiona.rescale(r, _t(cts, dev), n_ct, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().view(np.uint64).reshape(n_ct, 2, L - 1, N)
+    for c in sorted({0, n_ct // 2, n_ct - 1}):
+        assert np.array_equal(got[c], rs.rescale(cts[c], moduli)), "ciphertext %d differs" % c
+
+
+@pytest.mark.parametrize("log_n,n_rot", [(12, 3), (13, 63), (13, 64)])
+def test_rotate_division_edges(dev, log_n, n_rot):
+    """The division whole up to N = 2^12, and at 2^13 from 256 forward transforms on (L = 2: 64 rotations)."""
+    galois = [pow(5, 1 + r, 2 << log_n) for r in range(n_rot)]
+    _rotate(dev, log_n, galois, sorted({0, n_rot // 2, n_rot - 1}))
