@@ -310,9 +310,10 @@ int fiona_hybrid_linear_static(const fiona_plan *plan, const uint64_t *in_cts, c
  * of unity mod q_l.
  *
  * fiona_rescaler_create: the NTT twiddle tables of every limb (device) and a
- * workspace for up to max_ct ciphertexts: none up to N = 2^13, else about
- * 2 * max_ct * N * 8 * (1 + k (1 + 16 / sqrt(N))) bytes, k = L - 1 limbs per
- * launch, fewer when that would pass 8 GiB or 65535 vectors.
+ * workspace: none up to N = 2^13, else about
+ * 2 * c * N * 8 * (1 + (L - 1) (1 + 16 / sqrt(N))) bytes, c = max_ct or the
+ * ciphertexts whose intermediates fill 256 MiB if those are fewer (a call over
+ * more takes them in chunks).
  *   psi     host [L] roots psi_l, or NULL for the default: psi_l =
  *           x^((q_l - 1) / 2N) for the smallest x >= 2 with psi_l^N = -1
  * Requires N a power of two in [2^8, 2^17], L >= 2, every q_l = 1 mod 2N and
@@ -360,8 +361,9 @@ int fiona_rescale(const fiona_rescaler *rescaler, const uint64_t *in_cts, uint32
  *
  * fiona_rotator_create: NTT tables of q_0 .. q_{L-1} and P, and a workspace
  * for up to max_rot rotations per call (max_rot <= 256; about
- * 8 N (2 L (L + 1) + 2 L + max_rot (4 L + 4)) bytes, the NTT intermediates'
- * share of it 1 + 16 / sqrt(N) times that).
+ * 8 N (2 L (L + 1) + 2 L + max_rot (4 L + 4)) bytes and 1 + 16 / sqrt(N) times
+ * the NTT intermediates' share of it, at most: the division by P has
+ * intermediates of at most 416 MiB, a call with more takes it in chunks).
  *   special_prime  P with 2^20 < P < 2^50, P = 1 mod 2N, unequal to every q_l
  *   psi            host [L + 1] roots (the data moduli, then P) or NULL for
  *                  the defaults of fiona_rescaler_create

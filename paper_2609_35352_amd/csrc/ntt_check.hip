@@ -153,14 +153,15 @@ bool pass_b(Checker &C, const PassLaunch &L) {
     }
   }
   for (uint32_t by = 0; by < L.V; ++by) {
-    const uint32_t set = by / P.vps, lv = by - set * P.vps;
+    const fiona::UnitB un = fiona::pass_b_unit(P.vps, L.V, by);
+    const uint32_t set = un.set, lv = un.lv;
     const NttSet *S = C.set(P.sets, set);
     if (!S || !C.tables(S->dft_b, D::M / 2)) return false;
     if (S->post && (!C.span("pass B post", (uint64_t)S->post, 0, post_hi, nullptr) ||
                     !C.span("pass B post table", (uint64_t)S->post, 0, (uint64_t)M * sizeof(Tw), nullptr)))
       return false;
     for (uint32_t x = 0; x < gx; ++x) {
-      const uint64_t tmp_base = (uint64_t)P.tmp + ((uint64_t)by * fiona::tmp_words(M, N2) +
+      const uint64_t tmp_base = (uint64_t)P.tmp + (((uint64_t)set * P.vps + lv) * fiona::tmp_words(M, N2) +
                                                    (uint64_t)x * kNttCols * fiona::tmp_pitch(M)) * 8;
       const uint64_t out_base = (uint64_t)P.out + (set * P.out_set_stride + lv * P.out_stride) * 8;
       if (!C.span("pass B tmp", tmp_base, 0, tmp_hi, P.tmp_end) ||
@@ -212,13 +213,14 @@ bool pass_b_rot(Checker &C, const PassLaunch &L) {
         if (!C.grow(out_hi[x], G::out(o0, t, j, N2), 8, "rotation pass B output")) return false;
   }
   for (uint32_t by = 0; by < L.V; ++by) {
-    const uint32_t set = by / P.vps, lv = by - set * P.vps, p = lv / R.n_rot, r = lv - p * R.n_rot;
+    const fiona::UnitB un = fiona::pass_b_unit(P.vps, L.V, by);
+    const uint32_t set = un.set, lv = un.lv, p = (R.lv0 + lv) / R.n_rot, r = R.lv0 + lv - p * R.n_rot;
     if (p > 1) return C.fail("rotation pass B: more than two polynomials per rotation");
     const NttSet *S = C.set(P.sets, set);
     if (!S || !C.tables(S->dft_b, D::M / 2)) return false;
     for (uint32_t x = 0; x < gx; ++x) {
       const size_t xr = (size_t)x * R.n_rot + r;
-      if (!C.span("rotation pass B tmp", (uint64_t)P.tmp + (uint64_t)by * fiona::tmp_words(D::M, N2) * 8, 0, tmp_hi[xr], P.tmp_end) ||
+      if (!C.span("rotation pass B tmp", (uint64_t)P.tmp + ((uint64_t)set * P.vps + lv) * fiona::tmp_words(D::M, N2) * 8, 0, tmp_hi[xr], P.tmp_end) ||
           !C.span("rotation pass B u'", (uint64_t)P.base + (set * P.base_set_stride + lv * P.base_stride) * 8, 0,
                   word_hi[xr], P.base_end) ||
           (p == 0 && !C.span("rotation pass B c0", (uint64_t)P.add + set * P.add_set_stride * 8, 0, add_hi[xr],

@@ -255,6 +255,16 @@ constexpr size_t pass_smem(uint32_t M) {
   return fiona::kNttCols * fiona::padded_len(M) * sizeof(double) + M * sizeof(Tw);
 }
 
+// A call whose intermediates pass a limit (the rescale's and the division's
+// own) goes in chunks, each with its launches, so that pass B finds pass A's
+// words in the memory-side cache and the next chunk overwrites them there.
+// The chunk size of n vectors (or pairs) of which `fit` are within the limit:
+// as few chunks as that allows, of equal size.
+inline uint32_t chunk_size(uint32_t n, size_t fit) {
+  const uint32_t most = fit < 1 ? 1 : fit > n ? n : (uint32_t)fit, chunks = (n + most - 1) / most;
+  return (n + chunks - 1) / chunks;
+}
+
 // One pass over gridDim.y = V vectors (V <= 65535).
 inline void launch_pass(bool a, uint32_t log_side, uint32_t log_other, uint32_t V, hipStream_t stream,
                         const NttPass &P) {

@@ -117,8 +117,7 @@ struct Buf {
     return __builtin_bit_cast(double, u64(voff, soff));
   }
   // Nontemporal loads (cache policy 2) for words read once: pass B's
-  // intermediate and the words it subtracts from (rescale VGG11 / BERT /
-  // Large a further 0.5 / 2 / 1% faster).
+  // intermediate and the words it subtracts from.
   __device__ __forceinline__ uint64_t u64_once(uint32_t voff, uint32_t soff) const {
     const nv2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, 2);
     return (uint64_t)w.x | ((uint64_t)w.y << 32);
@@ -131,14 +130,17 @@ struct Buf {
     return Tw{__builtin_bit_cast(double, (uint64_t)w.x | ((uint64_t)w.y << 32)),
               __builtin_bit_cast(double, (uint64_t)w.z | ((uint64_t)w.w << 32))};
   }
-  // Stores are nontemporal (cache policy 2): measured against the default
-  // policy, the rescale of VGG11's outputs 1.11 -> 1.08 ms, BERT's 1.25 ->
-  // 1.19, Large's 2.29 -> 2.16; the rotations 0-2% faster.
+  // Stores of the callers' words are nontemporal (cache policy 2).
   __device__ __forceinline__ void put(uint64_t x, uint32_t voff, uint32_t soff) const {
     __builtin_amdgcn_raw_buffer_store_b64((nv2){(uint32_t)x, (uint32_t)(x >> 32)}, rs, voff, soff, 2);
   }
+  // Stores of intermediates and remainders take the default policy, under which
+  // the 256 MiB memory-side cache keeps them for the pass that reads them: a
+  // loop of writes and reads over 128 MiB moves 7.1 TB/s, with nontemporal
+  // stores 5.6, over 1 GiB 5.4 and 5.2.
   __device__ __forceinline__ void put(double y, uint32_t voff, uint32_t soff) const {
-    put(__builtin_bit_cast(uint64_t, y), voff, soff);
+    const uint64_t x = __builtin_bit_cast(uint64_t, y);
+    __builtin_amdgcn_raw_buffer_store_b64((nv2){(uint32_t)x, (uint32_t)(x >> 32)}, rs, voff, soff, 0);
   }
 };
 
@@ -494,6 +496,16 @@ __host__ __device__ inline UnitA pass_a_unit(uint32_t vps, uint32_t nsets_shared
   return a;
 }
 
+// Pass B's vector of workgroup row by of a grid of nv rows: all sets of a local
+// vector in turn, the order in which pass A with shared inputs writes them.
+struct UnitB {
+  uint32_t set, lv;
+};
+__host__ __device__ inline UnitB pass_b_unit(uint32_t vps, uint32_t nv, uint32_t by) {
+  const uint32_t nsets = nv / vps, lv = by / nsets;
+  return UnitB{by - lv * nsets, lv};
+}
+
 template <uint32_t LOGM>
 struct GeomA {
   using D = DftShape<LOGM>;
@@ -561,6 +573,7 @@ constexpr uint32_t kRotMax = 256;   // rotations per call (their Galois elements
 struct RotArgs {
   uint32_t g[kRotMax];
   uint32_t n_rot, L;
+  uint32_t lv0;          // the launch's vectors are numbers lv0, lv0 + 1, ... of the 2 n_rot
   uint32_t c0_natural;   // NttPass::add is in natural order, not transposed
 };
 
@@ -701,10 +714,11 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
   using G = GeomB<LOGM>;
   extern __shared__ double xs[];   // [kNttCols][PM], then the M/2 DFT twiddles
   Tw *tw = (Tw *)(xs + kNttCols * D::PM);
-  const uint32_t set = blockIdx.y / P.vps, lv = blockIdx.y - set * P.vps;
+  const UnitB un = pass_b_unit(P.vps, gridDim.y, blockIdx.y);
+  const uint32_t set = un.set, lv = un.lv;
   const uint32_t N2 = 1u << P.log_n2, M = D::M;
   const uint32_t r0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
-  const uint64_t v = blockIdx.y;
+  const uint64_t v = (uint64_t)set * P.vps + lv;
   const Buf tmp(P.tmp + v * tmp_words(M, N2) + (size_t)r0 * tmp_pitch(M), P.tmp_end);
   double x[16];   // a first group, as loaded
   auto load = [&](uint32_t it) {

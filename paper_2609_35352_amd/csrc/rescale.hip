@@ -22,18 +22,24 @@
 
 using namespace fiona_host;
 
-constexpr size_t kMaxTmpBytes = (size_t)8 << 30;   // cap on the intermediates of one launch pair
-
+// Intermediates of one launch pair, at most (chunk_size): the memory-side
+// cache's 256 MiB.  Limits of 128 / 192 / 256 / 320 / 416 MiB and none, us:
+// N = 2^16, L = 8, 128 ciphertexts 884 / 849 / 821 / 837 / 840 / 892; L = 16,
+// 128: 1776 / 1683 / 1619 / 1628 / 1677 / 1817; L = 12, 96: 1032 / 935 / 921 /
+// 911 / 934 / 1007; N = 2^15, L = 16, 128: 891 / 852 / 813 / 819 / 833 / 915;
+// N = 2^15, L = 8, 64 (one chunk from 256 on): 226 / 228 / 211 / 211 / 211 /
+// 208.  Of these the first was 932 and the last 249 with nontemporal stores,
+// one launch pair and pass B's vectors set by set.
+constexpr size_t kTmpBytes = (size_t)256 << 20;
 
 struct fiona_rescaler {
   const fiona_ctx *ctx = nullptr;
   uint32_t N = 0, L = 0, log_n1 = 0, log_n2 = 0, max_ct = 0;
-  uint32_t limbs_per_launch = 1;   // forward limbs transformed together (room for them in T)
   int device = -1;
   void *dev = nullptr;
   const NttSet *sets = nullptr;  // limbs 0 .. L-2 forward (inv = q_t^-1 mod q_l), then limb L-1 inverse
-  double *W = nullptr;           // the centred remainders [INTT_t(in_t)], one vector per polynomial
-  double *T = nullptr;           // the transposed intermediate of the passes
+  double *W = nullptr;           // the centred remainders [INTT_t(in_t)] of a chunk, one vector per polynomial
+  double *T = nullptr;           // the transposed intermediates of a chunk
   const void *W_end = nullptr, *T_end = nullptr;
 };
 
@@ -49,9 +55,13 @@ bool use_whole(const fiona_rescaler *R, uint32_t V) {
   return log_n <= kWholeAlways || (log_n <= kWholeMax && (uint64_t)V * (R->L - 1) >= kWholeTransforms);
 }
 
-// Bytes of one limb's intermediates.
-size_t tmp_vec_bytes(const fiona_rescaler *R) {
-  return (size_t)2 * R->max_ct * fiona::tmp_words(1u << R->log_n1, 1u << R->log_n2) * sizeof(double);
+// Bytes of a ciphertext's intermediates, and the ciphertexts of which a launch pair holds them.
+size_t tmp_ct_bytes(const fiona_rescaler *R) {
+  return (size_t)2 * (R->L - 1) * fiona::tmp_words(1u << R->log_n1, 1u << R->log_n2) * sizeof(double);
+}
+uint32_t chunk_max(const fiona_rescaler *R) {
+  const size_t fit = kTmpBytes / tmp_ct_bytes(R);
+  return fit < 1 ? 1 : fit < R->max_ct ? (uint32_t)fit : R->max_ct;
 }
 
 // Checks the parameters and sizes a rescaler: its tables (img) and the
@@ -59,7 +69,7 @@ size_t tmp_vec_bytes(const fiona_rescaler *R) {
 int rescaler_layout(const fiona_ctx *ctx, const uint64_t *psi, uint32_t max_ct, fiona_rescaler *R,
                     TableImage &img, size_t &total) {
   if (max_ct == 0) return FIONA_ERR_ARG;
-  if (2ull * max_ct > 65535) return FIONA_ERR_UNSUPPORTED;   // a launch holds at most 65535 vectors
+  if (2ull * max_ct > 65535) return FIONA_ERR_UNSUPPORTED;   // (a transform takes two vectors a ciphertext)
   const uint32_t N = ctx->N, L = ctx->L;
   uint32_t logN = 0;
   while ((1u << logN) < N) ++logN;
@@ -84,25 +94,14 @@ int rescaler_layout(const fiona_ctx *ctx, const uint64_t *psi, uint32_t max_ct, 
     img.add(make_tables(R->log_n1, R->log_n2, q, roots[l], false), q, make_tw(powmod_h(qt % q, q - 2, q), q));
   }
   img.add(make_tables(R->log_n1, R->log_n2, qt, roots[L - 1], true), qt);
-  const size_t vec_bytes = (size_t)2 * max_ct * N * sizeof(double), tmp_bytes = tmp_vec_bytes(R);
-  // All forward limbs go in one launch pair, so T holds L - 1 intermediates.
-  // Measured against one limb per launch (in-process A/B, same buffers):
-  // 256 vectors (VGG11's outputs) 1.25 -> 1.18 ms, 192 (BERT's) 1.32 -> 1.30.
-  // Very large max_ct takes fewer limbs per launch, so that T stays within
-  // kMaxTmpBytes (and every launch within the grid's 65535 vectors).
-  const size_t fit = kMaxTmpBytes / tmp_bytes;
-  const size_t fit_grid = 65535 / (2 * (size_t)max_ct);
-  size_t lpl = L - 1;
-  if (lpl > fit) lpl = fit;
-  if (lpl > fit_grid) lpl = fit_grid;
-  R->limbs_per_launch = lpl < 1 ? 1 : (uint32_t)lpl;
-  total = img.bytes() + (logN <= kWholeAlways ? 0 : vec_bytes + R->limbs_per_launch * tmp_bytes);
+  const uint32_t chunk = chunk_max(R);
+  total = img.bytes() + (logN <= kWholeAlways ? 0 : chunk * ((size_t)2 * N * sizeof(double) + tmp_ct_bytes(R)));
   return FIONA_OK;
 }
 
 // Points the rescaler's parts into its device buffer at dev.
 void rescaler_place(fiona_rescaler *R, const TableImage &img, void *dev) {
-  const size_t vec_bytes = (size_t)2 * R->max_ct * R->N * sizeof(double);
+  const size_t vec_bytes = (size_t)2 * chunk_max(R) * R->N * sizeof(double);
   R->dev = dev;
   R->sets = img.sets_addr(dev);
   R->W = (double *)((char *)dev + img.bytes());
@@ -112,7 +111,7 @@ void rescaler_place(fiona_rescaler *R, const TableImage &img, void *dev) {
     return;
   }
   R->W_end = (const char *)R->W + vec_bytes;
-  R->T_end = (const char *)R->T + R->limbs_per_launch * tmp_vec_bytes(R);
+  R->T_end = (const char *)R->T + chunk_max(R) * tmp_ct_bytes(R);
 }
 
 void launch_whole(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t V, uint64_t *out_cts, hipStream_t stream) {
@@ -141,35 +140,37 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
   if (use_whole(R, V)) return launch_whole(R, in_cts, V, out_cts, stream);
   const void *in_end = in_cts + (size_t)n_ct * 2 * L * N, *out_end = out_cts + (size_t)n_ct * 2 * (L - 1) * N;
 
-  // 1. the last limb back to its coefficients, kept as centred residues mod q_t
-  NttPass P{};
-  P.sets = R->sets + (L - 1);
-  P.vps = V;
-  P.log_n1 = R->log_n1;
-  P.log_n2 = R->log_n2;
-  P.in = in_cts + (L - 1) * N;
-  P.in_end = in_end;
-  P.in_stride = L * N;
-  P.tmp = R->T;
-  P.tmp_end = R->T_end;
-  P.out = R->W;
-  P.out_end = R->W_end;
-  P.out_stride = N;
-  P.load = fiona::kLoadU64;
-  P.store = fiona::kStoreF64;
-  launch_transform(R->log_n1, R->log_n2, V, stream, P);
+  const uint32_t chunk = chunk_size(n_ct, kTmpBytes / tmp_ct_bytes(R));
+  for (uint32_t c = 0; c < n_ct; c += chunk) {
+    const uint32_t n = 2 * (n_ct - c < chunk ? n_ct - c : chunk);
+    const uint64_t *in = in_cts + (size_t)c * 2 * L * N;
+    // 1. the last limb back to its coefficients, kept as centred residues mod q_t
+    NttPass P{};
+    P.sets = R->sets + (L - 1);
+    P.vps = n;
+    P.log_n1 = R->log_n1;
+    P.log_n2 = R->log_n2;
+    P.in = in + (L - 1) * N;
+    P.in_end = in_end;
+    P.in_stride = L * N;
+    P.tmp = R->T;
+    P.tmp_end = R->T_end;
+    P.out = R->W;
+    P.out_end = R->W_end;
+    P.out_stride = N;
+    P.load = fiona::kLoadU64;
+    P.store = fiona::kStoreF64;
+    launch_transform(R->log_n1, R->log_n2, n, stream, P);
 
-  // 2. every other limb: the centred remainder (a signed integer, so its
-  //    residue mod q_l comes with the first product) into its NTT domain,
-  //    subtracted, multiplied by q_t^-1; all limbs in one launch pair (one
-  //    set per limb, the vectors of a set share its modulus), pass A in the
-  //    order that fetches each input block once per XCD
-  const uint32_t lpl = R->limbs_per_launch;
-  for (uint32_t l0 = 0; l0 + 1 < L; l0 += lpl) {
-    const uint32_t nl = (uint32_t)(L - 1 - l0) < lpl ? (uint32_t)(L - 1 - l0) : lpl;
+    // 2. every other limb: the centred remainder (a signed integer, so its
+    //    residue mod q_l comes with the first product) into its NTT domain,
+    //    subtracted, multiplied by q_t^-1; all limbs in one launch pair (one
+    //    set per limb, the vectors of a set share its modulus), pass A in the
+    //    order that fetches each input block once per XCD
+    const uint32_t nl = (uint32_t)L - 1;
     NttPass Q{};
-    Q.sets = R->sets + l0;
-    Q.vps = V;
+    Q.sets = R->sets;
+    Q.vps = n;
     Q.log_n1 = R->log_n1;
     Q.log_n2 = R->log_n2;
     Q.in = R->W;
@@ -177,19 +178,19 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
     Q.in_stride = N;
     Q.tmp = R->T;
     Q.tmp_end = R->T_end;
-    Q.out = out_cts + l0 * N;
+    Q.out = out_cts + (size_t)c * 2 * (L - 1) * N;
     Q.out_end = out_end;
     Q.out_stride = (L - 1) * N;
     Q.out_set_stride = N;
-    Q.base = in_cts + l0 * N;
+    Q.base = in;
     Q.base_end = in_end;
     Q.base_stride = L * N;
     Q.base_set_stride = N;
     Q.load = fiona::kLoadF64;
     Q.store = fiona::kStoreRescale;
     const uint32_t col_blocks = (1u << R->log_n1) / fiona::kNttCols;
-    Q.nsets_shared = nl > 1 && (col_blocks * V) % 8 == 0 ? nl : 0;
-    launch_transform(R->log_n1, R->log_n2, nl * V, stream, Q);
+    Q.nsets_shared = nl > 1 && (col_blocks * n) % 8 == 0 ? nl : 0;
+    launch_transform(R->log_n1, R->log_n2, nl * n, stream, Q);
   }
 }
 

@@ -152,7 +152,7 @@ __global__ void __launch_bounds__(kKsWaves * 64) ks_inner_kernel(const uint64_t 
 // (contiguous rows of N1 words), finishes the division there (u' and c0 are
 // in the transposed layout, so row k2 is contiguous too), and then stores
 // each destination row d_hi as a run of 16 words, picking k1 in LDS.
-// Vectors: set = data limb l, vector lv = p n_rot + r in the set.
+// Vectors: set = data limb l, vector lv0 + lv = p n_rot + r in the set.
 template <uint32_t LOGM>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, const RotArgs R) {
   using D = DftShape<LOGM>;
@@ -160,12 +160,13 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
   constexpr uint32_t M = D::M, PM = D::PM, PER = G::PER;
   extern __shared__ double xs[];   // [kNttCols][PM], then the M/2 DFT twiddles
   Tw *tw = (Tw *)(xs + kNttCols * PM);
-  const uint32_t set = blockIdx.y / P.vps, lv = blockIdx.y - set * P.vps;
-  const uint32_t p = lv / R.n_rot, r = lv - p * R.n_rot;
+  const UnitB un = pass_b_unit(P.vps, gridDim.y, blockIdx.y);
+  const uint32_t set = un.set, lv = un.lv;
+  const uint32_t p = (R.lv0 + lv) / R.n_rot, r = R.lv0 + lv - p * R.n_rot;
   const uint32_t log_n2 = P.log_n2, N2 = 1u << log_n2, N = M << log_n2;   // M = N1
   const uint32_t g = R.g[r], cg = (g - 1) / 2;
   const uint32_t o0 = spread_block(blockIdx.x, blockIdx.y, gridDim.x) * kNttCols;
-  const Buf tmp(P.tmp + (uint64_t)blockIdx.y * tmp_words(M, N2), P.tmp_end);
+  const Buf tmp(P.tmp + ((uint64_t)set * P.vps + lv) * tmp_words(M, N2), P.tmp_end);
   double x[16];   // a first group, as loaded
   auto load = [&](uint32_t it) {
     const uint32_t k2 = G::src_row(g, o0 + G::row(it), N2);
@@ -286,8 +287,8 @@ struct fiona_rotator {
   double *D = nullptr;                 // [L][N] digits, blocked layout
   uint64_t *Dhat = nullptr;            // [L][L + 1][N], transposed layout
   uint64_t *c0t = nullptr;             // [L][N] c0 of the call, transposed layout
-  double *T = nullptr;                 // NTT intermediates: max(L (L + 1), 2 L max_rot) vectors
-  double *W = nullptr;                 // [2 max_rot][N] centred coefficients of u'_P, blocked layout
+  double *T = nullptr;                 // NTT intermediates: of the digits and of a chunk of the division
+  double *W = nullptr;                 // [chunk][N] centred coefficients of u'_P, blocked layout
   uint64_t *U = nullptr;               // [2][n_rot][L + 1][N], transposed layout
   const void *D_end = nullptr, *Dhat_end = nullptr, *c0t_end = nullptr, *T_end = nullptr, *W_end = nullptr,
              *U_end = nullptr;
@@ -299,6 +300,27 @@ namespace {
 // Bytes of one intermediate.
 size_t tmp_vec_bytes(const fiona_rotator *R) {
   return fiona::tmp_words(1u << R->log_n1, 1u << R->log_n2) * sizeof(double);
+}
+
+// Intermediates of one chunk of the division, at most: more than the rescale's
+// (rescale.hip), as here only the division's launches repeat and u' passes
+// through the memory-side cache as well.  Limits of 192 / 256 / 416 MiB and
+// none, us: 63 rotations at N = 2^16, L = 8 1425 / 1433 / 1408 / 1470 (1487
+// with nontemporal stores and pass B's vectors set by set); 100 at 2^15, L = 5
+// 711 / 710 / 699 / 691; 31 at 2^16, L = 12 1437 / 1411 / 1414 / 1417.
+constexpr size_t kTmpBytes = (size_t)416 << 20;
+
+// Vectors of the division by P that one chunk holds, of a call's V.
+uint32_t divide_chunk(const fiona_rotator *R, uint32_t V) {
+  return chunk_size(V, kTmpBytes / (R->L * tmp_vec_bytes(R)));
+}
+// (the fullest chunk of any call: chunk_size() of V vectors is at most this)
+uint32_t divide_chunk_max(const fiona_rotator *R) {
+  const size_t fit = kTmpBytes / (R->L * tmp_vec_bytes(R)), all = (size_t)2 * R->max_rot;
+  return (uint32_t)std::max<size_t>(1, std::min(fit, all));
+}
+size_t tmp_vectors(const fiona_rotator *R) {
+  return std::max((size_t)R->L * (R->L + 1), (size_t)R->L * divide_chunk_max(R));
 }
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
@@ -384,9 +406,9 @@ int rotator_layout(const fiona_ctx *ctx, uint64_t special_prime, const uint64_t 
   img.add(make_tables(R->log_n1, R->log_n2, P, roots[L], true), P);
   const size_t vec = (size_t)N * 8;
   R->limb_bytes = round256((L + 1) * sizeof(fiona::LimbConst));
-  const size_t t_vectors = std::max((size_t)L * (L + 1), (size_t)2 * L * max_rot);
   total = img.bytes() + R->limb_bytes + round256(L * vec) + round256((size_t)L * (L + 1) * vec) +
-          round256(L * vec) + round256(t_vectors * tmp_vec_bytes(R)) + round256((size_t)2 * max_rot * vec) +
+          round256(L * vec) + round256(tmp_vectors(R) * tmp_vec_bytes(R)) +
+          round256(divide_chunk_max(R) * vec) +
           round256((size_t)max_rot * 2 * (L + 1) * vec);
   return FIONA_OK;
 }
@@ -395,7 +417,6 @@ int rotator_layout(const fiona_ctx *ctx, uint64_t special_prime, const uint64_t 
 void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
   const uint32_t L = R->L;
   const size_t vec = (size_t)R->N * 8;
-  const size_t t_vectors = std::max((size_t)L * (L + 1), (size_t)2 * L * R->max_rot);
   R->dev = dev;
   const NttSet *sets = img.sets_addr(dev);
   R->inv_sets = sets;
@@ -414,8 +435,8 @@ void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
   R->D = (double *)take(L * vec, R->D_end);
   R->Dhat = (uint64_t *)take((size_t)L * (L + 1) * vec, R->Dhat_end);
   R->c0t = (uint64_t *)take(L * vec, R->c0t_end);
-  R->T = (double *)take(t_vectors * tmp_vec_bytes(R), R->T_end);
-  R->W = (double *)take((size_t)2 * R->max_rot * vec, R->W_end);
+  R->T = (double *)take(tmp_vectors(R) * tmp_vec_bytes(R), R->T_end);
+  R->W = (double *)take(divide_chunk_max(R) * vec, R->W_end);
   R->U = (uint64_t *)take((size_t)R->max_rot * 2 * (L + 1) * vec, R->U_end);
 }
 
@@ -571,46 +592,52 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
   G.L = L;
   G.c0_natural = c0_natural;
   if (whole_divide(R, V)) return launch_whole_divide(R, ct, out_cts, V, G, stream);
-  NttPass C{};
-  C.sets = R->p_inv_set;
-  C.vps = V;
-  C.log_n1 = R->log_n1;
-  C.log_n2 = R->log_n2;
-  C.in = R->U + (size_t)L * N;
-  C.in_end = R->U_end;
-  C.in_stride = (size_t)M * N;
-  C.tmp = R->T;
-  C.tmp_end = R->T_end;
-  C.out = R->W;
-  C.out_end = R->W_end;
-  C.out_stride = N;
-  C.load = fiona::kLoadU64T;
-  C.store = fiona::kStoreF64;
-  launch_transform(R->log_n1, R->log_n2, V, stream, C);
-  NttPass Q{};
-  Q.sets = R->down_sets;
-  Q.vps = V;
-  Q.log_n1 = R->log_n1;
-  Q.log_n2 = R->log_n2;
-  Q.in = R->W;
-  Q.in_end = R->W_end;
-  Q.in_stride = N;
-  Q.tmp = R->T;
-  Q.tmp_end = R->T_end;
-  Q.out = out_cts;
-  Q.out_end = out_end;
-  Q.base = R->U;
-  Q.base_end = R->U_end;
-  Q.base_stride = (size_t)M * N;
-  Q.base_set_stride = N;
-  Q.add = c0_natural ? ct : R->c0t;
-  Q.add_end = c0_natural ? (const void *)(ct + (size_t)2 * L * N) : R->c0t_end;
-  Q.add_set_stride = N;
-  Q.load = fiona::kLoadF64;
-  const uint32_t col_blocks = (1u << R->log_n1) / fiona::kNttCols;
-  Q.nsets_shared = L > 1 && (col_blocks * V) % 8 == 0 ? L : 0;
-  launch_pass(true, R->log_n2, R->log_n1, L * V, stream, Q);
-  launch_rot_pass_b(R->log_n1, R->log_n2, L * V, stream, Q, G);
+  const uint32_t chunk = divide_chunk(R, V);
+  for (uint32_t v0 = 0; v0 < V; v0 += chunk) {
+    const uint32_t n = std::min(chunk, V - v0);
+    const uint64_t *u = R->U + (size_t)v0 * M * N;
+    G.lv0 = v0;
+    NttPass C{};
+    C.sets = R->p_inv_set;
+    C.vps = n;
+    C.log_n1 = R->log_n1;
+    C.log_n2 = R->log_n2;
+    C.in = u + (size_t)L * N;
+    C.in_end = R->U_end;
+    C.in_stride = (size_t)M * N;
+    C.tmp = R->T;
+    C.tmp_end = R->T_end;
+    C.out = R->W;
+    C.out_end = R->W_end;
+    C.out_stride = N;
+    C.load = fiona::kLoadU64T;
+    C.store = fiona::kStoreF64;
+    launch_transform(R->log_n1, R->log_n2, n, stream, C);
+    NttPass Q{};
+    Q.sets = R->down_sets;
+    Q.vps = n;
+    Q.log_n1 = R->log_n1;
+    Q.log_n2 = R->log_n2;
+    Q.in = R->W;
+    Q.in_end = R->W_end;
+    Q.in_stride = N;
+    Q.tmp = R->T;
+    Q.tmp_end = R->T_end;
+    Q.out = out_cts;
+    Q.out_end = out_end;
+    Q.base = u;
+    Q.base_end = R->U_end;
+    Q.base_stride = (size_t)M * N;
+    Q.base_set_stride = N;
+    Q.add = c0_natural ? ct : R->c0t;
+    Q.add_end = c0_natural ? (const void *)(ct + (size_t)2 * L * N) : R->c0t_end;
+    Q.add_set_stride = N;
+    Q.load = fiona::kLoadF64;
+    const uint32_t col_blocks = (1u << R->log_n1) / fiona::kNttCols;
+    Q.nsets_shared = L > 1 && (col_blocks * n) % 8 == 0 ? L : 0;
+    launch_pass(true, R->log_n2, R->log_n1, L * n, stream, Q);
+    launch_rot_pass_b(R->log_n1, R->log_n2, L * n, stream, Q, G);
+  }
 }
 
 }  // namespace

@@ -128,3 +128,53 @@ def test_rotate_division_edges(dev, log_n, n_rot):
     """The division whole up to N = 2^12, and at 2^13 from 256 forward transforms on (L = 2: 64 rotations)."""
     galois = [pow(5, 1 + r, 2 << log_n) for r in range(n_rot)]
     _rotate(dev, log_n, galois, sorted({0, n_rot // 2, n_rot - 1}))
+
+
+def _residues(moduli, shape, seed, dev):
+    """Uniform residues [...][limb][N] on the device."""
+    import torch
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    x = torch.empty(shape, dtype=torch.int64, device=dev)
+    for l, q in enumerate(moduli):
+        x[..., l, :].random_(0, q, generator=gen)
+    return x
+
+
+def _np(x):
+    return x.cpu().numpy().view(np.uint64)
+
+
+@pytest.mark.parametrize("n_ct", [240, 243])
+def test_rescale_chunks(dev, n_ct):
+    """Intermediates of just within 256 MiB (one chunk) and just over (chunks of 122 and 121 ciphertexts)."""
+    import torch
+    N, L = 1 << 15, 3
+    _say("[ntt sizes] rescale chunks n_ct=%d" % n_ct)
+    moduli = _moduli(N, False)
+    cts = _residues(moduli, (n_ct, 2, L, N), n_ct, dev)
+    out = torch.full((n_ct, 2, L - 1, N), -1, dtype=torch.int64, device=dev)
+    fiona.rescale(fiona.Rescaler(fiona.Ctx(N, L, moduli), n_ct), cts, n_ct, out)
+    torch.cuda.synchronize()
+    for c in (0, 121, 122, n_ct - 1):
+        assert np.array_equal(_np(out[c]), rs.rescale(_np(cts[c]), moduli)), "ciphertext %d differs" % c
+
+
+def test_rotate_division_chunks(dev):
+    """The division in three chunks of 132, 132 and 130 vectors, the second over both polynomials."""
+    import torch
+    N, L, n_rot = 1 << 15, 8, 197
+    _say("[ntt sizes] rotate chunks")
+    chain = synth.ntt_primes(N, L + 1)
+    ct = _residues(chain[:L], (2, L, N), 5, dev)
+    key = _residues(chain, (L, 2, L + 1, N), 6, dev)
+    rot = fiona.Rotator(fiona.Ctx(N, L, chain[:L]), chain[L], n_rot)
+    galois = [pow(5, 1 + r, 2 * N) for r in range(n_rot)]
+    keys = torch.empty(n_rot, rot.key_words(), dtype=torch.int64, device=dev)   # one key under every element
+    for r, g in enumerate(galois):
+        fiona.rotation_key_layout(rot, g, key, keys[r])
+    out = torch.full((n_rot, 2, L, N), -1, dtype=torch.int64, device=dev)
+    fiona.hoisted_rotate(rot, ct, galois, keys, out)
+    torch.cuda.synchronize()
+    for r in (0, 66, 67, 131, 132, 196):   # vectors r and 197 + r
+        assert np.array_equal(_np(out[r]), ro.rotate(_np(ct), galois[r], _np(key), chain[:L], chain[L])), \
+            "rotation %d differs" % r
