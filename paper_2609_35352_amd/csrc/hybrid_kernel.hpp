@@ -41,6 +41,7 @@ constexpr uint32_t kInlineSum = 0xFFFFFFFFu;
 constexpr uint32_t kRawBatch = 8;         // plaintext loads per batch; two batches in flight
 constexpr uint32_t kRawBatches = kChunkTerms / kRawBatch;   // batches per chunk of raw records
 constexpr uint32_t kChunkSlots = 64;      // records per chunk block; the last one is the header
+constexpr uint32_t kStageInputs = 4;      // inputs per wavefront whose loads are in flight together
 constexpr uint32_t kSumBatch = 4;         // member reads issued before their additions
 constexpr uint32_t kSumBatches = kMaxMembers / kSumBatch;
 constexpr uint32_t kSumWords = 64;        // words per block: 4 header words + member rows
@@ -348,12 +349,24 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
   const size_t LN = (size_t)S.L * S.N;
   const LimbConst lc = limbs[limb];
 
-  // 1. stage this tile of every input ciphertext (read once)
-  for (uint32_t i = wave; i < S.n_in; i += NW) {
-    const uint64_t *src = in + ((size_t)i * 2 * S.L + limb) * S.N + k0;
-    const uint64_t a = __builtin_nontemporal_load(src + lane_off);
-    const uint64_t b = __builtin_nontemporal_load(src + LN + lane_off);
-    lds[i * kTile + lane] = make_uint4(lo_digit(a), hi_digit(a), lo_digit(b), hi_digit(b));
+  // 1. stage this tile of every input ciphertext (read once), the loads of
+  // kStageInputs of them in flight: waiting for each in turn is a chain of
+  // memory latencies, with nothing else on the CU where one workgroup fills its
+  // LDS (320 inputs in passes of 107, 16 wavefronts, N = 2^14, L = 6: 655 ->
+  // 600 us; 8 in flight 597; 200 inputs, N = 2^15, L = 4: 1275 -> 1196)
+  for (uint32_t i = wave; i < S.n_in; i += kStageInputs * NW) {
+    uint64_t a[kStageInputs], b[kStageInputs];
+#pragma unroll
+    for (uint32_t u = 0; u < kStageInputs; ++u)
+      if (i + u * NW < S.n_in) {
+        const uint64_t *src = in + ((size_t)(i + u * NW) * 2 * S.L + limb) * S.N + k0;
+        a[u] = __builtin_nontemporal_load(src + lane_off);
+        b[u] = __builtin_nontemporal_load(src + LN + lane_off);
+      }
+#pragma unroll
+    for (uint32_t u = 0; u < kStageInputs; ++u)
+      if (i + u * NW < S.n_in)
+        lds[(i + u * NW) * kTile + lane] = make_uint4(lo_digit(a[u]), hi_digit(a[u]), lo_digit(b[u]), hi_digit(b[u]));
   }
   if (wave == NW - 1) lds[S.zero_row * kTile + lane] = make_uint4(0, 0, 0, 0);   // padding row
   __syncthreads();
