@@ -888,6 +888,7 @@ int build_plan(const fiona_ctx *ctx, const fiona_layer_desc *d, uint64_t pitch, 
   k.n_levels = P->n_levels;
   for (uint32_t l = 0; l < fiona::kMaxLevels; ++l) k.level_end[l] = P->part_levels[l];
   k.tiles = P->tiles;
+  k.xcd_runs = (ctx->N | pitch) % 16 != 0;   // rows of 16 words are whole lines
   if (!(d->flags & FIONA_PLAN_HOST_ONLY)) {
     rc = upload_plan(P);
     if (rc != FIONA_OK) {

@@ -82,7 +82,20 @@ struct PackParams {
 struct KShape {
   uint32_t N, L, n_in, n_part, n_levels, n_mat, zero_row, tiles, n_rounds, obuf_row, use_block0;
   uint32_t level_end[kMaxLevels];
+  uint32_t xcd_runs;   // the tiles' order: xcd_run_unit
 };
+
+// The tile of workgroup b of n where each XCD takes a run of consecutive tiles
+// (workgroups b, b + 8, ... run on one XCD): a permutation of 0 .. n - 1.  Where
+// rows do not start on a 128-byte line, neighbouring tiles' slices share their
+// end lines, and tiles dealt out one by one fetch those into two L2s (a slice of
+// 512 bytes then moves 640).  N = 12001, L = 5, 37 inputs: 237 -> 218 us;
+// N = 33001, L = 6: 2327 -> 2194; N = 5001, L = 4: 69 -> 65.  With aligned rows
+// the runs lose instead (3x3 convolution, N = 2^16, L = 8: 3160 -> 3237).
+__host__ __device__ constexpr uint32_t xcd_run_unit(uint32_t b, uint32_t n) {
+  const uint32_t xcd = b & 7u, full = n >> 3, rem = n & 7u;
+  return xcd * full + (xcd < rem ? xcd : rem) + (b >> 3);
+}
 
 __device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
 
@@ -340,8 +353,9 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t lane16 = lane * 16u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t limb = blockIdx.x / S.tiles;
-  const uint32_t tile = blockIdx.x - limb * S.tiles;
+  const uint32_t unit = S.xcd_runs ? xcd_run_unit(blockIdx.x, gridDim.x) : blockIdx.x;
+  const uint32_t limb = unit / S.tiles;
+  const uint32_t tile = unit - limb * S.tiles;
   const uint32_t k0 = tile * kTile;
   const uint32_t k = k0 + lane;
   // lanes past N (partial last tile) read a valid coefficient and store nothing
