@@ -691,10 +691,12 @@ int upload_plan(fiona_plan *P) {
   if (hipMemcpy(P->dev, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) return FIONA_ERR_HIP;
   // the kernels' LDS limit, set on the current device with every plan (cheap,
   // and correct whatever device the plan lives on)
-  const void *kernels[4] = {(const void *)fiona::hybrid_linear_kernel<8, false>,
-                            (const void *)fiona::hybrid_linear_kernel<16, false>,
-                            (const void *)fiona::hybrid_linear_kernel<8, true>,
-                            (const void *)fiona::hybrid_linear_kernel<16, true>};
+  const void *kernels[6] = {(const void *)fiona::hybrid_linear_kernel<8, false, false>,
+                            (const void *)fiona::hybrid_linear_kernel<16, false, false>,
+                            (const void *)fiona::hybrid_linear_kernel<8, true, false>,
+                            (const void *)fiona::hybrid_linear_kernel<16, true, false>,
+                            (const void *)fiona::hybrid_linear_kernel<8, false, true>,
+                            (const void *)fiona::hybrid_linear_kernel<16, false, true>};
   for (const void *k : kernels)
     if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes) != hipSuccess)
       return FIONA_ERR_HIP;
@@ -772,28 +774,50 @@ int check_call(const fiona_plan *plan, const uint64_t *in_cts, const uint64_t *p
   return FIONA_OK;
 }
 
+// Whether the workgroups pack the word blocks themselves, each into its LDS,
+// which saves the launch of pack_members_kernel (2 to 3 us of a call): where the
+// blocks a wavefront packs, times the turns of workgroups a CU takes, are at most
+// kOwnPacks, and their LDS leaves as many workgroups on a CU.  64 inputs, one
+// output, N = 2^12, L = 3 (1 pack, 1 turn) 11.5 -> 9.0 us; 16 inputs, 4 outputs
+// (2, 1) 11.3 -> 8.7; N = 2^13, L = 4 (1, 1) 16.7 -> 14.0; but N = 2^13, L = 8
+// (2, 2) 32.8 -> 34.0, N = 2^14, L = 6 (2, 3) 30.3 -> 32.8, N = 2^12, L = 6
+// (8, 1) 29.9 -> 31.6.
+constexpr uint32_t kOwnPacks = 2;
+uint32_t own_words_bytes(const fiona_plan *plan) {
+  return (uint32_t)(plan->blocks.size() * fiona::kSumWords * sizeof(uint32_t));
+}
+bool own_words(const fiona_plan *plan) {
+  const size_t bytes = plan->lds_bytes + own_words_bytes(plan);
+  const uint32_t per_cu = plan->nw == 8 && plan->lds_bytes * 2 <= kLdsBytes ? 2 : 1;
+  if (plan->accumulate || plan->blocks.empty() || bytes * per_cu > kLdsBytes) return false;
+  const uint64_t packs = (plan->blocks.size() + plan->nw - 1) / plan->nw, slots = 256ull * per_cu;
+  return packs * ((plan->grid + slots - 1) / slots) <= kOwnPacks;
+}
+
 // The launches of one call: the sign-packing kernel writes this call's word
 // blocks at words (plan->blocks.size() blocks of kSumWords words), then the
 // main kernel reads them.
 int enqueue_one(const fiona_plan *plan, const uint64_t *in_cts, const uint64_t *pt_diags,
                   const int8_t *ternary_groups, const uint64_t *scales, uint64_t *out_cts, uint32_t *words,
                   const CallBytes &b, hipStream_t stream) {
-  const uint32_t n_blocks = (uint32_t)plan->blocks.size();
-  if (n_blocks) {   // this call's signs and scales: the word blocks
-    PackParams pp;
-    pp.signs = ternary_groups;
-    pp.members = plan->d_members;
-    pp.blocks = plan->d_blocks;
-    pp.words = words;
-    pp.scales = scales;
-    pp.n_blocks = n_blocks;
-    hipLaunchKernelGGL(fiona::pack_members_kernel, dim3((n_blocks + 3) / 4), dim3(256), 0, stream, pp);
+  PackParams pp;   // this call's signs and scales: the word blocks
+  pp.signs = ternary_groups;
+  pp.members = plan->d_members;
+  pp.blocks = plan->d_blocks;
+  pp.words = words;
+  pp.scales = scales;
+  pp.n_blocks = (uint32_t)plan->blocks.size();
+  const bool own = own_words(plan);
+  if (pp.n_blocks && !own) {
+    hipLaunchKernelGGL(fiona::pack_members_kernel, dim3((pp.n_blocks + 3) / 4), dim3(256), 0, stream, pp);
     if (hipGetLastError() != hipSuccess) return FIONA_ERR_HIP;
   }
-  auto kernel = plan->nw == 16 ? (plan->accumulate ? fiona::hybrid_linear_kernel<16, true>
-                                                  : fiona::hybrid_linear_kernel<16, false>)
-                                : (plan->accumulate ? fiona::hybrid_linear_kernel<8, true>
-                                                    : fiona::hybrid_linear_kernel<8, false>);
+  auto kernel = plan->nw == 16 ? (plan->accumulate ? fiona::hybrid_linear_kernel<16, true, false>
+                                  : own            ? fiona::hybrid_linear_kernel<16, false, true>
+                                                   : fiona::hybrid_linear_kernel<16, false, false>)
+                               : (plan->accumulate ? fiona::hybrid_linear_kernel<8, true, false>
+                                  : own            ? fiona::hybrid_linear_kernel<8, false, true>
+                                                   : fiona::hybrid_linear_kernel<8, false, false>);
   fiona::KPlan kp;
   kp.limbs = plan->d_limbs;
   kp.items = plan->d_items;
@@ -804,8 +828,8 @@ int enqueue_one(const fiona_plan *plan, const uint64_t *in_cts, const uint64_t *
   kp.splits = plan->d_splits;
   kp.pm = plan->d_pm;
   kp.words = words;
-  hipLaunchKernelGGL(kernel, dim3(plan->grid), dim3(plan->nw * 64), plan->lds_bytes, stream, in_cts, pt_diags,
-                     out_cts, kp, plan->shape, (const void *)((const char *)pt_diags + b.pt),
+  hipLaunchKernelGGL(kernel, dim3(plan->grid), dim3(plan->nw * 64), plan->lds_bytes + (own ? own_words_bytes(plan) : 0),
+                     stream, in_cts, pt_diags, out_cts, kp, plan->shape, pp, (const void *)((const char *)pt_diags + b.pt),
                      (const void *)((const char *)out_cts + b.out));
   if (hipGetLastError() != hipSuccess) return FIONA_ERR_HIP;
   return FIONA_OK;
@@ -883,6 +907,7 @@ int build_plan(const fiona_ctx *ctx, const fiona_layer_desc *d, uint64_t pitch, 
   k.zero_row = P->n_in + P->n_part + P->n_mat + P->n_seg_slots;
   k.n_rounds = P->n_rounds;
   k.obuf_row = k.zero_row + 1;
+  k.words_row = k.obuf_row + P->obuf_rows;
   k.use_block0 = P->n_part + P->n_mat;
   k.n_part = P->n_part;
   k.n_levels = P->n_levels;

@@ -80,7 +80,7 @@ struct PackParams {
 // produced in n_rounds rounds; each round ends with a barrier after which the
 // round's buffered outputs and split outputs are written out together.
 struct KShape {
-  uint32_t N, L, n_in, n_part, n_levels, n_mat, zero_row, tiles, n_rounds, obuf_row, use_block0;
+  uint32_t N, L, n_in, n_part, n_levels, n_mat, zero_row, tiles, n_rounds, obuf_row, use_block0, words_row;
   uint32_t level_end[kMaxLevels];
   uint32_t xcd_runs;   // the tiles' order: xcd_run_unit
 };
@@ -107,10 +107,7 @@ __device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) { return ((
 // whose run-time sign is 0 are left out (Sec. 3 Obs. 2, the skip).  A common
 // partial sum takes its signs relative to its first member's, so it is the
 // same term in every sum that contains it.  One wavefront per block.
-__global__ void __launch_bounds__(256) pack_members_kernel(const PackParams P) {
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= P.n_blocks) return;
+__device__ __forceinline__ void pack_block(const PackParams &P, uint32_t b, uint32_t lane, uint32_t *w) {
   const uint4 bk = P.blocks[b];
   const uint32_t cnt = bk.y & 0xFFFFu;
   const int32_t h0 = (bk.y & kNormaliseSigns) ? (int32_t)P.signs[P.members[bk.x].y] : 1;
@@ -124,7 +121,6 @@ __global__ void __launch_bounds__(256) pack_members_kernel(const PackParams P) {
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   const uint64_t b0 = __ballot(cls == 0), b1 = __ballot(cls == 1);
   const uint32_t n0 = __popcll(b0), n1 = __popcll(b1);
-  uint32_t *w = P.words + (size_t)b * kSumWords;
   if (cls == 0) w[kAddWord + __popcll(b0 & below)] = row * kRowBytes;
   if (cls == 1) w[kSumWords - 1 - __popcll(b1 & below)] = row * kRowBytes;
   if (lane == 0) w[0] = n0 | (n1 << 16);
@@ -138,6 +134,12 @@ __global__ void __launch_bounds__(256) pack_members_kernel(const PackParams P) {
     w[2] = (uint32_t)sc;
   }
   if (lane == 3) w[3] = 0;
+}
+
+__global__ void __launch_bounds__(256) pack_members_kernel(const PackParams P) {
+  const uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (b >= P.n_blocks) return;
+  pack_block(P, b, threadIdx.x & 63u, P.words + (size_t)b * kSumWords);
 }
 
 __device__ __forceinline__ const uint4 &lds_row(const uint4 *lds, uint32_t row_bytes, uint32_t lane_bytes) {
@@ -159,6 +161,19 @@ __device__ __forceinline__ u32x4 sload4(const void *p) { return *(cu32x4p)p; }
 __device__ __forceinline__ u32x8 sload8(const void *p) { return *(cu32x8p)p; }
 __device__ __forceinline__ uint4 as_uint4(u32x4 v) { return make_uint4(v.x, v.y, v.z, v.w); }
 __device__ __forceinline__ uint2 as_uint2(u32x2 v) { return make_uint2(v.x, v.y); }
+
+// Four words of a word block (uniform address): by a scalar load, or OWN: from
+// the workgroup's own blocks in LDS, the same in every lane.  Words that steer
+// control flow go through readfirstlane there.
+template <bool OWN>
+__device__ __forceinline__ u32x4 words4(const uint32_t *p) {
+  if constexpr (OWN) return *(const u32x4 *)p;
+  else return sload4(p);
+}
+template <bool OWN>
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+  return OWN ? (uint32_t)__builtin_amdgcn_readfirstlane(x) : x;
+}
 
 // Adds the kSumBatch rows whose LDS byte offsets are in r into the packed digit sums.
 __device__ __forceinline__ void sum_batch(uint64_t &a, uint64_t &b, u32x4 r, const uint4 *lds, uint32_t lane16) {
@@ -201,17 +216,18 @@ __device__ __forceinline__ void sum_tail(uint64_t &a, uint64_t &b, u32x4 r, uint
 // lists to whole batches with the zero row cost about three extra row reads
 // per sum (BERT: a fifth of all LDS reads); exact counts measured 0.8-1.4%
 // faster on BERT and the kernel's code 40% smaller (rolled batch loops).
+template <bool OWN>
 __device__ __forceinline__ uint4 signed_sum(const uint32_t *blk, uint32_t hdr, const uint4 *lds, uint32_t lane16) {
   const uint32_t np = hdr & 0xFFFFu, nn = hdr >> 16;
   uint64_t pa = 0, pb = 0, na = 0, nb = 0;
   uint32_t k = 0;
-  for (; (k + 1) * kSumBatch <= np; ++k) sum_batch(pa, pb, sload4(blk + kAddWord + k * kSumBatch), lds, lane16);
-  if (k * kSumBatch < np) sum_tail(pa, pb, sload4(blk + kAddWord + k * kSumBatch), np - k * kSumBatch, true, lds, lane16);
+  for (; (k + 1) * kSumBatch <= np; ++k) sum_batch(pa, pb, words4<OWN>(blk + kAddWord + k * kSumBatch), lds, lane16);
+  if (k * kSumBatch < np) sum_tail(pa, pb, words4<OWN>(blk + kAddWord + k * kSumBatch), np - k * kSumBatch, true, lds, lane16);
   k = 0;
   for (; (k + 1) * kSumBatch <= nn; ++k)
-    sum_batch(na, nb, sload4(blk + kSumWords - (k + 1) * kSumBatch), lds, lane16);
+    sum_batch(na, nb, words4<OWN>(blk + kSumWords - (k + 1) * kSumBatch), lds, lane16);
   if (k * kSumBatch < nn)
-    sum_tail(na, nb, sload4(blk + kSumWords - (k + 1) * kSumBatch), nn - k * kSumBatch, false, lds, lane16);
+    sum_tail(na, nb, words4<OWN>(blk + kSumWords - (k + 1) * kSumBatch), nn - k * kSumBatch, false, lds, lane16);
   return make_uint4((uint32_t)pa - (uint32_t)na, (uint32_t)(pa >> 32) - (uint32_t)(na >> 32),
                     (uint32_t)pb - (uint32_t)nb, (uint32_t)(pb >> 32) - (uint32_t)(nb >> 32));
 }
@@ -340,16 +356,20 @@ struct KPlan {
 
 // pt_end, out_end: the ends of the plaintext table and of the output array.
 // ADD: a later pass over an input range, which adds its sums to the outputs.
-template <int NW, bool ADD>
+// OWN: the workgroup packs the call's word blocks (pack) into its own LDS, from
+// row words_row on, instead of reading those of pack_members_kernel.
+template <int NW, bool ADD, bool OWN>
 __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) hybrid_linear_kernel(
     const uint64_t *__restrict__ in, const uint64_t *__restrict__ pt, uint64_t *__restrict__ out, const KPlan K,
-    const KShape S, const void *pt_end, const void *out_end) {
-  extern __shared__ uint4 lds[];   // [n_in + n_part + n_mat + segment slots + zero row + output buffer][kTile]
+    const KShape S, const PackParams pack, const void *pt_end, const void *out_end) {
+  // [n_in + n_part + n_mat + segment slots + zero row + output buffer][kTile], OWN: then the word blocks
+  extern __shared__ uint4 lds[];
   const LimbConst *__restrict__ limbs = K.limbs;
   const uint4 *__restrict__ items = K.items;
   const uint32_t *__restrict__ dest = K.dest;
   const uint2 *__restrict__ pm = K.pm;
-  const uint32_t *__restrict__ words = K.words;
+  uint32_t *own = (uint32_t *)(lds + (size_t)S.words_row * kTile);
+  const uint32_t *words = OWN ? own : K.words;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t lane16 = lane * 16u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -382,6 +402,8 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
       if (i + u * NW < S.n_in)
         lds[(i + u * NW) * kTile + lane] = make_uint4(lo_digit(a[u]), hi_digit(a[u]), lo_digit(b[u]), hi_digit(b[u]));
   }
+  if constexpr (OWN)
+    for (uint32_t b = wave; b < pack.n_blocks; b += NW) pack_block(pack, b, lane, own + b * kSumWords);
   if (wave == NW - 1) lds[S.zero_row * kTile + lane] = make_uint4(0, 0, 0, 0);   // padding row
   __syncthreads();
 
@@ -392,7 +414,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
     const uint32_t p1 = S.level_end[lv];
     for (uint32_t p = p0 + wave; p < p1; p += NW) {
       const uint32_t *blk = words + (size_t)p * kSumWords;
-      const uint4 U = signed_sum(blk, sload1(blk), lds, lane16);
+      const uint4 U = signed_sum<OWN>(blk, uniform<OWN>(words4<OWN>(blk).x), lds, lane16);
       const uint64_t v0 = reduce_i64((int64_t)(int32_t)U.x + ((int64_t)(int32_t)U.y << 25), lc.q, lc.qinv);
       const uint64_t v1 = reduce_i64((int64_t)(int32_t)U.z + ((int64_t)(int32_t)U.w << 25), lc.q, lc.qinv);
       parts[p * kTile + lane] = make_uint4(lo_digit(v0), hi_digit(v0), lo_digit(v1), hi_digit(v1));
@@ -406,7 +428,7 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
   if (S.n_mat) {   // uniform over the workgroup
     for (uint32_t s = wave; s < S.n_mat; s += NW) {
       const uint32_t *blk = words + (size_t)(S.n_part + s) * kSumWords;
-      sums[s * kTile + lane] = signed_sum(blk, sload1(blk), lds, lane16);
+      sums[s * kTile + lane] = signed_sum<OWN>(blk, uniform<OWN>(words4<OWN>(blk).x), lds, lane16);
     }
     __syncthreads();
   }
@@ -434,8 +456,10 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
     auto use_one = [&]() {
       if (u && u % kFoldUses == 0) fold(a0, a1, r0, r1, lc);
       const uint32_t *blk = ub + (size_t)u * kSumWords;
-      const u32x4 hd = sload4(blk);   // row counts, resident slot or kInlineSum, signed scale
-      const uint4 U = hd.y != kInlineSum ? sums[hd.y * kTile + lane] : signed_sum(blk, hd.x, lds, lane16);
+      const u32x4 hd = words4<OWN>(blk);   // row counts, resident slot or kInlineSum, signed scale
+      const uint32_t slot = uniform<OWN>(hd.y);
+      const uint4 U = slot != kInlineSum ? sums[slot * kTile + lane]
+                                         : signed_sum<OWN>(blk, uniform<OWN>(hd.x), lds, lane16);
       const int32_t c = (int32_t)hd.z;
       smac(a0, c, (int32_t)U.x, (int32_t)U.y);
       smac(a1, c, (int32_t)U.z, (int32_t)U.w);

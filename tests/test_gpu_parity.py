@@ -116,6 +116,9 @@ SMALL = {
     "wide_partial": synth.LayerConfig("wide_partial", N=128, L=2, n_in=200, n_out=48, T=400, g=40, ternary=0.95),
     "wide_repeat": synth.LayerConfig("wide_repeat", N=96, L=2, n_in=170, n_out=8, T=800, g=200, ternary=0.5),
     # ragged N; 320 inputs, terms on the first 64 only: the other input ranges get no pass
+    # 16 wavefronts: 32 word blocks, which the workgroups pack themselves, and 33, which they do not
+    "word_blocks_32": synth.LayerConfig("word_blocks_32", N=130, L=2, n_in=8, n_out=9, T=12, g=4, ternary=1.0),
+    "word_blocks_33": synth.LayerConfig("word_blocks_33", N=130, L=2, n_in=8, n_out=5, T=24, g=4, ternary=1.0),
     # rows off the 128-byte lines, 1, 19 and 591 tiles (fewer than, and no multiple of, the 8 XCDs); rows on them
     "ragged_1_tile": synth.LayerConfig("ragged_1_tile", N=37, L=1, n_in=5, n_out=3, T=20, g=5, ternary=0.5),
     "ragged_19_tiles": synth.LayerConfig("ragged_19_tiles", N=1201, L=1, n_in=9, n_out=5, T=40, g=5, ternary=0.5),
