@@ -247,6 +247,10 @@ bool replay_one(Checker &C, const PassLaunch &L) {
 std::string check_launches(const LaunchRecord &rec, const std::vector<Region> &regions, uint64_t sets_dev,
                            const std::vector<NttSet> &sets_host) {
   Checker C{regions, sets_dev, sets_host, std::string()};
+  for (const LdsUse &u : rec.lds)
+    if (u.bytes > u.most)
+      return std::string(u.what) + ": " + std::to_string(u.bytes) + " bytes of LDS, its limit is " +
+             std::to_string(u.most);
   for (const SpanAccess &s : rec.spans)
     if (!C.span(s.what, s.base, s.lo, s.hi, nullptr)) return C.err;
   for (const PassLaunch &L : rec.passes) {

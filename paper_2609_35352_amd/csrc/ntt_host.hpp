@@ -34,9 +34,14 @@ struct SpanAccess {   // a kernel that is not an NTT pass: bytes [lo, hi) of the
   const char *what;
   uint64_t base, lo, hi;
 };
+struct LdsUse {   // the LDS a launch asks for, and the most its kernel may
+  const char *what;
+  uint64_t bytes, most;
+};
 struct LaunchRecord {
   std::vector<PassLaunch> passes;
   std::vector<SpanAccess> spans;
+  std::vector<LdsUse> lds;
 };
 inline LaunchRecord *&launch_recorder() {
   static thread_local LaunchRecord *rec = nullptr;

@@ -43,7 +43,7 @@ namespace fiona {
 constexpr uint32_t kKsTile = 128;   // coefficients per workgroup of the inner product (two per lane)
 constexpr uint32_t kKsWaves = 8;    // wavefronts per workgroup; rotations are dealt out to them
 constexpr uint32_t kKsRoundMax = 64;   // rotations whose outputs are buffered in LDS per round, at most
-constexpr size_t kKsLdsMax = 160 * 1024;
+constexpr size_t kKsLdsMax = 160 * 1024;   // LDS of its workgroups at most, and the limit set for its kernels
 
 typedef uint32_t ks_u4 __attribute__((ext_vector_type(4)));
 typedef uint64_t ks_q2 __attribute__((ext_vector_type(2)));
@@ -575,6 +575,7 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
     record_span("ks_inner: keys", keys, 0, (uint64_t)n_rot * key_words * 8);
     record_span("ks_inner: U", R->U, 0, (uint64_t)2 * n_rot * M * N * 8);
     record_span("ks_inner: limbs", R->limbs, 0, (uint64_t)M * sizeof(fiona::LimbConst));
+    launch_recorder()->lds.push_back(LdsUse{"ks_inner", ks_smem, fiona::kKsLdsMax});
   } else if (pad8 <= pad4) {
     hipLaunchKernelGGL(fiona::ks_inner_kernel<8>, ks_grid, dim3(fiona::kKsWaves * 64), ks_smem, stream, R->Dhat, keys,
                        R->U, R->limbs, N, L, n_rot, round);
@@ -734,14 +735,12 @@ int fiona_rotator_create(const fiona_ctx *ctx, uint64_t special_prime, const uin
       fiona_rotator_destroy(R);
       return FIONA_ERR_HIP;
     }
-    const int ks_smem = (int)fiona::ks_lds_bytes(R->L, fiona::ks_round(R->L, fiona::kKsRoundMax));
+    // (the inner product's limit is every rotator's: a call's rounds, so its LDS, follow its own n_rot and L)
     const int nt_smem = (int)pass_smem(fiona::kNttMaxSide);
     if (!allow_lds((const void *)fiona::whole_divide_kernel<13>, fiona::whole_smem<13>()) ||
         !allow_smem() || !allow_rot_smem(nt_smem) ||
-        hipFuncSetAttribute((const void *)fiona::ks_inner_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            ks_smem) != hipSuccess ||
-        hipFuncSetAttribute((const void *)fiona::ks_inner_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            ks_smem) != hipSuccess) {
+        !allow_lds((const void *)fiona::ks_inner_kernel<8>, fiona::kKsLdsMax) ||
+        !allow_lds((const void *)fiona::ks_inner_kernel<4>, fiona::kKsLdsMax)) {
       fiona_rotator_destroy(R);
       return FIONA_ERR_HIP;
     }

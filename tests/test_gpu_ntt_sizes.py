@@ -80,12 +80,18 @@ def test_rotate_round_edges(dev, n_rot):
     _rotate(dev, 8, galois, [r for r in (0, 32, 33, 43, 44, 63, 64, 87, 88, 129) if r < n_rot])
 
 
-def _rotate(dev, log_n, galois, check):
+@pytest.mark.parametrize("n_rot", [33, 63])
+def test_rotate_long_chain(dev, n_rot):
+    """L = 32: 63 rotations fill the inner product's LDS (33 and 63 take more of it than 64, two rounds of 32)."""
+    _rotate(dev, 8, [pow(5, 1 + r, 512) for r in range(n_rot)], [0, n_rot - 1], L=32)
+
+
+def _rotate(dev, log_n, galois, check, L=2):
     import torch
-    N, L = 1 << log_n, 2
-    _say("[ntt sizes] rotate N=2^%d, %d rotations" % (log_n, len(galois)))
-    chain = _moduli(N, False)
-    moduli, P = chain[:2], chain[2]
+    N = 1 << log_n
+    _say("[ntt sizes] rotate N=2^%d, L=%d, %d rotations" % (log_n, L, len(galois)))
+    chain = synth.ntt_primes(N, L + 1)
+    moduli, P = chain[:L], chain[L]
     ct = _cts(N, moduli, 1, 40 + log_n)[0]
     rng = np.random.default_rng(log_n)
     ctx = fiona.Ctx(N, L, moduli)

@@ -49,6 +49,16 @@ def test_rotate_accesses_in_bounds(N, L, max_rot, n_rot):
     assert rc == 0, msg
 
 
+@pytest.mark.parametrize("L", [1, 8, 16, 31, 32, 48, 63])
+@pytest.mark.parametrize("n_rot", [1, 33, 63, 64, 127, 256])
+def test_inner_product_lds_within_limit(L, n_rot):
+    """The LDS of the rotations' inner product depends on the call's number of
+    rotations (rounds of equal size, as few as fit): from L = 32 on fewer than 64
+    rotations fit one round, and 63 then take more than half of 64."""
+    rc, msg = fiona.check_ntt_offsets("rotate", 256, L, synth.ntt_primes(256, L + 1), 256, n_rot)
+    assert rc == 0, msg
+
+
 @pytest.mark.parametrize("op,N,L,cap,n", [("rescale", 256, 2, 3, 2), ("rescale", 1 << 16, 8, 128, 128),
                                            ("rotate", 256, 2, 2, 2), ("rotate", 1 << 16, 8, 63, 63)])
 def test_replay_finds_an_overrun(op, N, L, cap, n):
