@@ -157,6 +157,7 @@ bool pass_b(Checker &C, const PassLaunch &L) {
     const uint32_t set = un.set, lv = un.lv;
     const NttSet *S = C.set(P.sets, set);
     if (!S || !C.tables(S->dft_b, D::M / 2)) return false;
+    if (inverse_b(P) != (S->post != nullptr)) return C.fail("pass B: post table and direction differ");
     if (S->post && (!C.span("pass B post", (uint64_t)S->post, 0, post_hi, nullptr) ||
                     !C.span("pass B post table", (uint64_t)S->post, 0, (uint64_t)M * sizeof(Tw), nullptr)))
       return false;

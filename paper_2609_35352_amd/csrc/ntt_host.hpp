@@ -244,6 +244,9 @@ inline bool allow_lds(const void *kernel, size_t bytes) {
   return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
 }
 
+// Whether a pass B ends an inverse transform.
+inline bool inverse_b(const NttPass &P) { return P.store == fiona::kStoreF64 || P.store == fiona::kStoreF64C; }
+
 // The passes are instantiated per DFT side 2^4 .. 2^9.
 template <uint32_t LOG>
 void launch_pair(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPass &P) {
@@ -251,8 +254,10 @@ void launch_pair(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPa
     hipLaunchKernelGGL((fiona::ntt_pass_a<LOG, true>), grid, dim3(fiona::kNttThreads), smem, stream, P);
   else if (a)
     hipLaunchKernelGGL((fiona::ntt_pass_a<LOG, false>), grid, dim3(fiona::kNttThreads), smem, stream, P);
+  else if (inverse_b(P))
+    hipLaunchKernelGGL((fiona::ntt_pass_b<LOG, true>), grid, dim3(fiona::kNttThreads), smem, stream, P);
   else
-    hipLaunchKernelGGL(fiona::ntt_pass_b<LOG>, grid, dim3(fiona::kNttThreads), smem, stream, P);
+    hipLaunchKernelGGL((fiona::ntt_pass_b<LOG, false>), grid, dim3(fiona::kNttThreads), smem, stream, P);
 }
 
 // LDS of a pass of side M: the columns and at most M twiddles.
@@ -297,8 +302,8 @@ inline void launch_transform(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipSt
 
 template <uint32_t LOG>
 bool allow_smem_one(size_t bytes) {
-  const void *k[3] = {(const void *)fiona::ntt_pass_a<LOG, true>, (const void *)fiona::ntt_pass_a<LOG, false>,
-                      (const void *)fiona::ntt_pass_b<LOG>};
+  const void *k[4] = {(const void *)fiona::ntt_pass_a<LOG, true>, (const void *)fiona::ntt_pass_a<LOG, false>,
+                      (const void *)fiona::ntt_pass_b<LOG, true>, (const void *)fiona::ntt_pass_b<LOG, false>};
   for (const void *f : k)
     if (!allow_lds(f, bytes)) return false;
   return true;

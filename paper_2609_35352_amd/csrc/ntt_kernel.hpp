@@ -419,7 +419,7 @@ struct NttSet {
   const double *mid; // pass A: multiply output (n1, k2) by mid[((n1 / 16) N2 + k2) 16 + n1 mod 16]
   const Tw *dft_a;   // pass A's twiddles: forward N2 (from index 1: 2^s + block), inverse N2 / 2
   const Tw *dft_b;   // size-N1 DFT twiddles (N1 / 2)
-  const Tw *post;    // pass B: multiply output k2 + N2 k1 by post[k1] (null: by 1)
+  const Tw *post;    // inverse pass B: multiply output k2 + N2 k1 by post[k1] (forward: null)
   Tw inv;            // kStoreRescale: the factor applied after the subtraction
   double q, qinv;    // the modulus and fl(1 / q)
 };
@@ -707,8 +707,16 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
 // runs of I1 consecutive words of one intermediate row k2; the last groups
 // store column k2 = r0 + (lane mod kNttCols), rows k1, as runs of kNttCols
 // words (kStoreU64T: runs of consecutive k1 of one row k2; blocked: rows k1
-// and k1 + 2^d follow each other).
-template <uint32_t LOGM>
+// and k1 + 2^d follow each other).  INV: the inverse transform (post, centred or
+// residues as doubles), else the forward one (to residues, kStoreRescale or
+// kStoreU64T).  Two kernels: in a common one the minuends held over the barrier
+// left the compiler no registers for post, and its 16 loads waited one for
+// another (inverse passes B of 4 / 12 ciphertexts' rescales at L = 3 17.6 us at
+// N = 2^17 and 8.7 at 2^15, before the minuends were moved 12.2 and 7.7).  With
+// post ahead of the barrier as well, rescales in us, common -> two kernels:
+// N = 2^17, L = 3, 4 ciphertexts 52.0 -> 45.1; 2^16, L = 6, 4 42.2 -> 39.2,
+// L = 16, 4 67.4 -> 64.0; 2^15, L = 3, 12 37.1 -> 34.4.
+template <uint32_t LOGM, bool INV>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
   using D = DftShape<LOGM>;
   using G = GeomB<LOGM>;
@@ -740,7 +748,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
     first_stages<LOGM>(x, t1, q, qinv);
     put_first<LOGM>(xs, G::row(it), G::grp(it), x, q, qinv);
   }
-  const bool transposed = P.store == kStoreU64T, rescale = P.store == kStoreRescale;   // uniform
+  const bool transposed = !INV && P.store == kStoreU64T, rescale = !INV && !transposed;   // uniform
   const Buf out((const char *)P.out + (set * P.out_set_stride + lv * P.out_stride) * 8, P.out_end);
   const Buf base(rescale ? P.base + set * P.base_set_stride + lv * P.base_stride : nullptr,
                  rescale ? P.base_end : nullptr);
@@ -752,24 +760,32 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
       bv[u] = base.u64_once(oc.v, oc.s);
     }
   };
-  if (rescale) load_base(threadIdx.x);   // in flight over the barrier and the last stages
+  const Buf post(S.post, INV ? S.post + M : S.post);
+  double pw[D::E2];   // post of a last group (w only, half the registers of the pair; w / q as w fl(1/q), like mid's)
+  auto load_post = [&](uint32_t it) {
+#pragma unroll
+    for (uint32_t u = 0; u < D::E2; ++u) {
+      const Off op = G::post(G::off2(it, false), u);
+      pw[u] = post.f64(op.v, op.s);
+    }
+  };
+  // in flight over the barrier and the last stages
+  if constexpr (INV) load_post(threadIdx.x);
+  else if (rescale) load_base(threadIdx.x);
   middle_stages<LOGM>(xs, tw, q, qinv);
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT2; it += kNttThreads) {
     const uint32_t row = G::row2(it, transposed), o = G::off2(it, transposed);
     const uint32_t k2 = r0 + row;   // output k2 + N2 k1, k1 = o + (u << S0L)
-    if (D::IT2 > kNttThreads && rescale && it != threadIdx.x) load_base(it);
+    if (D::IT2 > kNttThreads && it != threadIdx.x) {
+      if constexpr (INV) load_post(it);
+      else if (rescale) load_base(it);
+    }
     double y[D::E2];
     last_stages<LOGM>(xs, row, o, tw, y, q, qinv);
-    if (S.post) {
-      const Buf post(S.post, S.post + M);
+    if constexpr (INV) {
 #pragma unroll
-      for (uint32_t u = 0; u < D::E2; ++u) {
-        const Off op = G::post(o, u);
-        y[u] = mul_tw(y[u], post.tw(op.v, op.s), q);
-      }
-    }
-    if (P.store == kStoreF64 || P.store == kStoreF64C) {
+      for (uint32_t u = 0; u < D::E2; ++u) y[u] = mul_tw(y[u], Tw{pw[u], pw[u] * qinv}, q);
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
         const Off ob = G::block(k2, o, u, N2);
