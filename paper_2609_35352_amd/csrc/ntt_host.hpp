@@ -249,15 +249,15 @@ inline bool inverse_b(const NttPass &P) { return P.store == fiona::kStoreF64 || 
 
 // The passes are instantiated per DFT side 2^4 .. 2^9.
 template <uint32_t LOG>
-void launch_pair(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPass &P) {
-  if (a && P.load == fiona::kLoadF64)
-    hipLaunchKernelGGL((fiona::ntt_pass_a<LOG, true>), grid, dim3(fiona::kNttThreads), smem, stream, P);
-  else if (a)
-    hipLaunchKernelGGL((fiona::ntt_pass_a<LOG, false>), grid, dim3(fiona::kNttThreads), smem, stream, P);
-  else if (inverse_b(P))
-    hipLaunchKernelGGL((fiona::ntt_pass_b<LOG, true>), grid, dim3(fiona::kNttThreads), smem, stream, P);
-  else
-    hipLaunchKernelGGL((fiona::ntt_pass_b<LOG, false>), grid, dim3(fiona::kNttThreads), smem, stream, P);
+auto *pass_kernel(bool a, const NttPass &P) {
+  if (a && P.load == fiona::kLoadF64) return P.nt ? fiona::ntt_pass_a<LOG, true, true> : fiona::ntt_pass_a<LOG, true, false>;
+  if (a) return P.nt ? fiona::ntt_pass_a<LOG, false, true> : fiona::ntt_pass_a<LOG, false, false>;
+  if (inverse_b(P)) return P.nt ? fiona::ntt_pass_b<LOG, true, true> : fiona::ntt_pass_b<LOG, true, false>;
+  return fiona::ntt_pass_b<LOG, false, false>;   // stores no doubles
+}
+template <uint32_t LOG>
+void launch_one(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPass &P) {
+  hipLaunchKernelGGL(pass_kernel<LOG>(a, P), grid, dim3(fiona::kNttThreads), smem, stream, P);
 }
 
 // LDS of a pass of side M: the columns and at most M twiddles.
@@ -275,6 +275,29 @@ inline uint32_t chunk_size(uint32_t n, size_t fit) {
   return (n + chunks - 1) / chunks;
 }
 
+// Whether the two transforms of a step (the inverse one, then the forward one
+// over V vectors, the larger) store their doubles nontemporally.  With the
+// default policy the 256 MiB memory-side cache keeps them for the pass that
+// reads them: a loop of writes and reads over 128 MiB moves 7.1 TB/s, with
+// nontemporal stores 5.6, over 1 GiB 5.4 and 5.2.  But what a launch leaves in
+// the L2s (8 of 4 MiB) is written back at its end, with nothing else in flight,
+// which launches of one or two turns of workgroups pay for; with few words
+// there is little to write back.  Default / nontemporal, us, by the forward
+// intermediates' MiB, rescales: 2.1 (N = 2^16, L = 3, 1 ciphertext) 22.1 / 22.6,
+// 4.2 (2^16, L = 2, 4) 24.3 / 23.4, 13 (2^15, L = 3, 12) 33.9 / 30.1, 21 (2^16,
+// L = 6, 4) 38.9 / 35.4, 32 (2^15, L = 6, 12; 2^16, L = 16, 2) 46.3 / 46.3 and
+// 43.9 / 41.3, 34 (2^15, L = 3, 32; 2^17, L = 2, 16) 53.4 / 52.9 and 68.6 /
+// 67.8, 43 (2^15, L = 6, 16) 53.3 / 57.1, 64 (2^16, L = 16, 4) 64.0 / 66.9, 272
+// (2^15, L = 6, 64) 149 / 175; rotations: 17 (2^15, L = 2, 16) 79.5 / 76.3, 27
+// (2^14, L = 4, 24) 94.8 / 92.8 (but 28 at L = 1, 100 of 2^14, 120 / 125), 42
+// (2^15, L = 2, 40) 143 / 145.  One policy for both transforms: a small inverse
+// launch beside a large forward one loses with nontemporal stores (2^16, L = 8,
+// 128 ciphertexts 822 -> 892).
+inline bool stores_nontemporal(uint32_t log_n1, uint32_t log_n2, uint32_t V) {
+  const size_t bytes = V * fiona::tmp_words(1u << log_n1, 1u << log_n2) * sizeof(double);
+  return bytes >= (size_t)4 << 20 && bytes <= (size_t)32 << 20;
+}
+
 // One pass over gridDim.y = V vectors (V <= 65535).
 inline void launch_pass(bool a, uint32_t log_side, uint32_t log_other, uint32_t V, hipStream_t stream,
                         const NttPass &P) {
@@ -285,12 +308,12 @@ inline void launch_pass(bool a, uint32_t log_side, uint32_t log_other, uint32_t 
   const dim3 grid((1u << log_other) / fiona::kNttCols, V);
   const size_t smem = pass_smem(1u << log_side);
   switch (log_side) {
-    case 4: launch_pair<4>(a, grid, smem, stream, P); break;
-    case 5: launch_pair<5>(a, grid, smem, stream, P); break;
-    case 6: launch_pair<6>(a, grid, smem, stream, P); break;
-    case 7: launch_pair<7>(a, grid, smem, stream, P); break;
-    case 8: launch_pair<8>(a, grid, smem, stream, P); break;
-    default: launch_pair<9>(a, grid, smem, stream, P); break;
+    case 4: launch_one<4>(a, grid, smem, stream, P); break;
+    case 5: launch_one<5>(a, grid, smem, stream, P); break;
+    case 6: launch_one<6>(a, grid, smem, stream, P); break;
+    case 7: launch_one<7>(a, grid, smem, stream, P); break;
+    case 8: launch_one<8>(a, grid, smem, stream, P); break;
+    default: launch_one<9>(a, grid, smem, stream, P); break;
   }
 }
 
@@ -302,10 +325,14 @@ inline void launch_transform(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipSt
 
 template <uint32_t LOG>
 bool allow_smem_one(size_t bytes) {
-  const void *k[4] = {(const void *)fiona::ntt_pass_a<LOG, true>, (const void *)fiona::ntt_pass_a<LOG, false>,
-                      (const void *)fiona::ntt_pass_b<LOG, true>, (const void *)fiona::ntt_pass_b<LOG, false>};
-  for (const void *f : k)
-    if (!allow_lds(f, bytes)) return false;
+  NttPass P{};
+  for (uint32_t nt = 0; nt < 2; ++nt)
+    for (uint32_t k = 0; k < 4; ++k) {
+      P.nt = nt;
+      P.load = k & 1 ? fiona::kLoadF64 : fiona::kLoadU64;
+      P.store = k & 1 ? fiona::kStoreRescale : fiona::kStoreF64;
+      if (!allow_lds((const void *)pass_kernel<LOG>(k < 2, P), bytes)) return false;
+    }
   return true;
 }
 

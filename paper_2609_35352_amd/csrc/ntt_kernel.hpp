@@ -134,13 +134,12 @@ struct Buf {
   __device__ __forceinline__ void put(uint64_t x, uint32_t voff, uint32_t soff) const {
     __builtin_amdgcn_raw_buffer_store_b64((nv2){(uint32_t)x, (uint32_t)(x >> 32)}, rs, voff, soff, 2);
   }
-  // Stores of intermediates and remainders take the default policy, under which
-  // the 256 MiB memory-side cache keeps them for the pass that reads them: a
-  // loop of writes and reads over 128 MiB moves 7.1 TB/s, with nontemporal
-  // stores 5.6, over 1 GiB 5.4 and 5.2.
+  // Stores of intermediates and remainders, nontemporal or with the default
+  // policy (stores_nontemporal in ntt_host.hpp).
+  template <bool NT>
   __device__ __forceinline__ void put(double y, uint32_t voff, uint32_t soff) const {
     const uint64_t x = __builtin_bit_cast(uint64_t, y);
-    __builtin_amdgcn_raw_buffer_store_b64((nv2){(uint32_t)x, (uint32_t)(x >> 32)}, rs, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b64((nv2){(uint32_t)x, (uint32_t)(x >> 32)}, rs, voff, soff, NT ? 2 : 0);
   }
 };
 
@@ -441,6 +440,7 @@ struct NttPass {
   uint64_t in_stride, out_stride, base_stride;
   uint64_t in_set_stride, out_set_stride, base_set_stride, add_set_stride;
   uint32_t vps, log_n1, log_n2, load, store;
+  uint32_t nt;             // the kernels' NT
   uint32_t nsets_shared;   // pass A: 0, or the number of sets when they all read the same input
                            // vectors (in_set_stride 0) and gridDim.x * vps is a multiple of 8
 };
@@ -611,6 +611,8 @@ struct GeomRot {
 // column n1 hold rows n2 = i' + I1 v; the quarter waves read runs of
 // kNttCols columns of one row (kLoadU64T: runs of consecutive rows of one
 // column, which are contiguous there).  FWD: the forward transform (kLoadF64).
+// NT: nontemporal stores; a kernel of its own, as both policies' stores in one
+// cost the smallest calls 0.1 us a launch.
 // What bounds it: the L1 path (it serves one 64-byte access a clock), the
 // arithmetic and the stores take about the same time and overlap badly
 // (parts taken out one at a time, N = 2^16, L = 8, 128 ciphertexts, of 444 us:
@@ -622,7 +624,7 @@ struct GeomRot {
 // rescale 980 -> 932 us (loads that pass B issued ahead of its input instead
 // cost 1%: they return in order).  The last groups store rows
 // k2 = o + (u << S0L) of the intermediate, again in runs of kNttCols columns.
-template <uint32_t LOGM, bool FWD>
+template <uint32_t LOGM, bool FWD, bool NT>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
   static_assert(dft_out<LOGM>() < 4, "mid's input");
   using D = DftShape<LOGM>;
@@ -698,7 +700,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
     for (uint32_t u = 0; u < D::E2; ++u) {
       const Off ot = G::tmp(o, n1, u, N1);
       const uint32_t e = FWD ? rev4(u) >> (4 - D::R2) : u;
-      tmp.put(mul_tw(r[e], Tw{m[u], m[u] * qinv}, q), ot.v, ot.s);
+      tmp.put<NT>(mul_tw(r[e], Tw{m[u], m[u] * qinv}, q), ot.v, ot.s);
     }
   }
 }
@@ -716,7 +718,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
 // post ahead of the barrier as well, rescales in us, common -> two kernels:
 // N = 2^17, L = 3, 4 ciphertexts 52.0 -> 45.1; 2^16, L = 6, 4 42.2 -> 39.2,
 // L = 16, 4 67.4 -> 64.0; 2^15, L = 3, 12 37.1 -> 34.4.
-template <uint32_t LOGM, bool INV>
+template <uint32_t LOGM, bool INV, bool NT>
 __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
   using D = DftShape<LOGM>;
   using G = GeomB<LOGM>;
@@ -791,7 +793,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
         const Off ob = G::block(k2, o, u, N2);
         double z = reduce(y[u], q, qinv);
         if (P.store == kStoreF64C && z < 0.0) z += q;
-        out.put(z, ob.v, ob.s);
+        out.put<NT>(z, ob.v, ob.s);
       }
     } else if (rescale) {
 #pragma unroll

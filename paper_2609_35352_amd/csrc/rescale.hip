@@ -144,6 +144,8 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
   for (uint32_t c = 0; c < n_ct; c += chunk) {
     const uint32_t n = 2 * (n_ct - c < chunk ? n_ct - c : chunk);
     const uint64_t *in = in_cts + (size_t)c * 2 * L * N;
+    const uint32_t nl = (uint32_t)L - 1;
+    const bool nt = stores_nontemporal(R->log_n1, R->log_n2, nl * n);
     // 1. the last limb back to its coefficients, kept as centred residues mod q_t
     NttPass P{};
     P.sets = R->sets + (L - 1);
@@ -160,6 +162,7 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
     P.out_stride = N;
     P.load = fiona::kLoadU64;
     P.store = fiona::kStoreF64;
+    P.nt = nt;
     launch_transform(R->log_n1, R->log_n2, n, stream, P);
 
     // 2. every other limb: the centred remainder (a signed integer, so its
@@ -167,7 +170,6 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
     //    subtracted, multiplied by q_t^-1; all limbs in one launch pair (one
     //    set per limb, the vectors of a set share its modulus), pass A in the
     //    order that fetches each input block once per XCD
-    const uint32_t nl = (uint32_t)L - 1;
     NttPass Q{};
     Q.sets = R->sets;
     Q.vps = n;
@@ -188,6 +190,7 @@ void rescale_enqueue(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t n
     Q.base_set_stride = N;
     Q.load = fiona::kLoadF64;
     Q.store = fiona::kStoreRescale;
+    Q.nt = nt;
     const uint32_t col_blocks = (1u << R->log_n1) / fiona::kNttCols;
     Q.nsets_shared = nl > 1 && (col_blocks * n) % 8 == 0 ? nl : 0;
     launch_transform(R->log_n1, R->log_n2, nl * n, stream, Q);

@@ -501,6 +501,7 @@ void launch_whole_divide(const fiona_rotator *R, const uint64_t *ct, uint64_t *o
 void digits_by_passes(const fiona_rotator *R, const uint64_t *ct, hipStream_t stream) {
   const uint32_t N = R->N, L = R->L, M = L + 1;
   const void *ct_end = ct + (size_t)2 * L * N;
+  const bool nt = stores_nontemporal(R->log_n1, R->log_n2, L * M);
   NttPass A{};
   A.sets = R->inv_sets;
   A.vps = 1;
@@ -516,6 +517,7 @@ void digits_by_passes(const fiona_rotator *R, const uint64_t *ct, hipStream_t st
   A.out_set_stride = N;
   A.load = fiona::kLoadU64;
   A.store = fiona::kStoreF64C;
+  A.nt = nt;
   launch_transform(R->log_n1, R->log_n2, L, stream, A);
   NttPass B{};
   B.sets = R->fwd_sets;
@@ -533,6 +535,7 @@ void digits_by_passes(const fiona_rotator *R, const uint64_t *ct, hipStream_t st
   B.out_set_stride = N;
   B.load = fiona::kLoadF64;
   B.store = fiona::kStoreU64T;
+  B.nt = nt;
   B.nsets_shared = ((1u << R->log_n1) / fiona::kNttCols * L) % 8 == 0 ? M : 0;   // every modulus reads D_j
   launch_transform(R->log_n1, R->log_n2, L * M, stream, B);
 }
@@ -598,6 +601,7 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
     const uint32_t n = std::min(chunk, V - v0);
     const uint64_t *u = R->U + (size_t)v0 * M * N;
     G.lv0 = v0;
+    const bool nt = stores_nontemporal(R->log_n1, R->log_n2, L * n);
     NttPass C{};
     C.sets = R->p_inv_set;
     C.vps = n;
@@ -613,6 +617,7 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
     C.out_stride = N;
     C.load = fiona::kLoadU64T;
     C.store = fiona::kStoreF64;
+    C.nt = nt;
     launch_transform(R->log_n1, R->log_n2, n, stream, C);
     NttPass Q{};
     Q.sets = R->down_sets;
@@ -634,6 +639,7 @@ void rotate_enqueue(const fiona_rotator *R, const uint64_t *ct, uint32_t n_rot, 
     Q.add_end = c0_natural ? (const void *)(ct + (size_t)2 * L * N) : R->c0t_end;
     Q.add_set_stride = N;
     Q.load = fiona::kLoadF64;
+    Q.nt = nt;
     const uint32_t col_blocks = (1u << R->log_n1) / fiona::kNttCols;
     Q.nsets_shared = L > 1 && (col_blocks * n) % 8 == 0 ? L : 0;
     launch_pass(true, R->log_n2, R->log_n1, L * n, stream, Q);

@@ -165,6 +165,21 @@ def test_rescale_chunks(dev, n_ct):
         assert np.array_equal(_np(out[c]), rs.rescale(_np(cts[c]), moduli)), "ciphertext %d differs" % c
 
 
+@pytest.mark.parametrize("n_ct", [3, 4, 30, 31])
+def test_rescale_store_policy_edges(dev, n_ct):
+    """Intermediates of just under 4 MiB and just over 32 (stores of the default policy), and just within (nontemporal)."""
+    import torch
+    N, L = 1 << 15, 3
+    _say("[ntt sizes] rescale store policy n_ct=%d" % n_ct)
+    moduli = _moduli(N, False)
+    cts = _residues(moduli, (n_ct, 2, L, N), n_ct, dev)
+    out = torch.full((n_ct, 2, L - 1, N), -1, dtype=torch.int64, device=dev)
+    fiona.rescale(fiona.Rescaler(fiona.Ctx(N, L, moduli), n_ct), cts, n_ct, out)
+    torch.cuda.synchronize()
+    for c in (0, n_ct - 1):
+        assert np.array_equal(_np(out[c]), rs.rescale(_np(cts[c]), moduli)), "ciphertext %d differs" % c
+
+
 def test_rotate_division_chunks(dev):
     """The division in three chunks of 132, 132 and 130 vectors, the second over both polynomials."""
     import torch
