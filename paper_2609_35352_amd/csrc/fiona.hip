@@ -860,6 +860,27 @@ int enqueue_layer(const fiona_plan *plan, const uint64_t *in_cts, const uint64_t
 // for common partial sums, resident sums and output rows beside them.
 constexpr uint32_t kPassInputs = 128;
 
+// Whether the workgroups stage their inputs in batches of kStageInputs loads a
+// wavefront, instead of waiting for each in turn: a chain of memory latencies,
+// with nothing else on the CU where one workgroup fills its LDS (us, one by one
+// -> four in flight: 320 inputs, N = 2^14, L = 6, 24 outputs 740 -> 699; 100
+// inputs, 16 outputs, N = 2^14, L = 8 187 -> 183; 64 inputs, 16 outputs,
+// N = 2^16, L = 7 498 -> 469; 48 inputs, 2 outputs, N = 2^15, L = 4 54.7 -> 49.5;
+// two in flight within 2% of four, either way).  Not where
+//  - a wavefront has one input: the batches' code costs 1 to 2% (14 inputs,
+//    N = 2^16, L = 5 125.7 -> 127.6; 13, N = 2^14, L = 8 47.2 -> 48.0);
+//  - the inputs are a multiple of 4 MiB apart, so that a batch's loads meet on
+//    the same memory channels, and there are outputs enough for a call to be
+//    bound by its bytes: 64 inputs, 16 outputs, N = 2^16, L = 8 534 -> 546,
+//    L = 4 253 -> 259, L = 12 850 -> 863; N = 2^15, L = 16 540 -> 554; but 4
+//    outputs, L = 8 269 -> 268, and 2 181 -> 163.  Input passes gain all the same
+//    (320 inputs, 24 outputs, L = 8 3694 -> 3603).
+constexpr uint32_t kBatchOutputs = 12;
+bool stage_in_batches(const fiona_ctx *ctx, const fiona_plan *P, bool pass) {
+  const uint64_t apart = (uint64_t)2 * ctx->L * ctx->N * 8;
+  return P->n_in > P->nw && (pass || P->n_out < kBatchOutputs || apart % ((uint64_t)4 << 20) != 0);
+}
+
 // Compiles one plan over all of d's inputs and, unless host-only, uploads it.
 // slot_map (or null): for each member of d, its index in the caller's
 // ternary_groups; n_member: the caller's member count.
@@ -914,6 +935,7 @@ int build_plan(const fiona_ctx *ctx, const fiona_layer_desc *d, uint64_t pitch, 
   for (uint32_t l = 0; l < fiona::kMaxLevels; ++l) k.level_end[l] = P->part_levels[l];
   k.tiles = P->tiles;
   k.xcd_runs = (ctx->N | pitch) % 16 != 0;   // rows of 16 words are whole lines
+  k.stage_batches = stage_in_batches(ctx, P, slot_map != nullptr);
   if (!(d->flags & FIONA_PLAN_HOST_ONLY)) {
     rc = upload_plan(P);
     if (rc != FIONA_OK) {

@@ -83,6 +83,7 @@ struct KShape {
   uint32_t N, L, n_in, n_part, n_levels, n_mat, zero_row, tiles, n_rounds, obuf_row, use_block0, words_row;
   uint32_t level_end[kMaxLevels];
   uint32_t xcd_runs;   // the tiles' order: xcd_run_unit
+  uint32_t stage_batches;
 };
 
 // The tile of workgroup b of n where each XCD takes a run of consecutive tiles
@@ -383,24 +384,32 @@ __global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4,
   const size_t LN = (size_t)S.L * S.N;
   const LimbConst lc = limbs[limb];
 
-  // 1. stage this tile of every input ciphertext (read once), the loads of
-  // kStageInputs of them in flight: waiting for each in turn is a chain of
-  // memory latencies, with nothing else on the CU where one workgroup fills its
-  // LDS (320 inputs in passes of 107, 16 wavefronts, N = 2^14, L = 6: 655 ->
-  // 600 us; 8 in flight 597; 200 inputs, N = 2^15, L = 4: 1275 -> 1196)
-  for (uint32_t i = wave; i < S.n_in; i += kStageInputs * NW) {
-    uint64_t a[kStageInputs], b[kStageInputs];
+  // 1. stage this tile of every input ciphertext (read once), S.stage_batches:
+  // with the loads of kStageInputs of them in flight (stage_in_batches in fiona.hip)
+  auto load_input = [&](uint32_t i, uint64_t &a, uint64_t &b) {
+    const uint64_t *src = in + ((size_t)i * 2 * S.L + limb) * S.N + k0;
+    a = __builtin_nontemporal_load(src + lane_off);
+    b = __builtin_nontemporal_load(src + LN + lane_off);
+  };
+  auto put_input = [&](uint32_t i, uint64_t a, uint64_t b) {
+    lds[i * kTile + lane] = make_uint4(lo_digit(a), hi_digit(a), lo_digit(b), hi_digit(b));
+  };
+  if (!S.stage_batches) {
+    for (uint32_t i = wave; i < S.n_in; i += NW) {
+      uint64_t a, b;
+      load_input(i, a, b);
+      put_input(i, a, b);
+    }
+  } else {
+    for (uint32_t i = wave; i < S.n_in; i += kStageInputs * NW) {
+      uint64_t a[kStageInputs], b[kStageInputs];
 #pragma unroll
-    for (uint32_t u = 0; u < kStageInputs; ++u)
-      if (i + u * NW < S.n_in) {
-        const uint64_t *src = in + ((size_t)(i + u * NW) * 2 * S.L + limb) * S.N + k0;
-        a[u] = __builtin_nontemporal_load(src + lane_off);
-        b[u] = __builtin_nontemporal_load(src + LN + lane_off);
-      }
+      for (uint32_t u = 0; u < kStageInputs; ++u)
+        if (i + u * NW < S.n_in) load_input(i + u * NW, a[u], b[u]);
 #pragma unroll
-    for (uint32_t u = 0; u < kStageInputs; ++u)
-      if (i + u * NW < S.n_in)
-        lds[(i + u * NW) * kTile + lane] = make_uint4(lo_digit(a[u]), hi_digit(a[u]), lo_digit(b[u]), hi_digit(b[u]));
+      for (uint32_t u = 0; u < kStageInputs; ++u)
+        if (i + u * NW < S.n_in) put_input(i + u * NW, a[u], b[u]);
+    }
   }
   if constexpr (OWN)
     for (uint32_t b = wave; b < pack.n_blocks; b += NW) pack_block(pack, b, lane, own + b * kSumWords);

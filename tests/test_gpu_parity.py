@@ -115,7 +115,6 @@ SMALL = {
                                          ternary=0.5),
     "wide_partial": synth.LayerConfig("wide_partial", N=128, L=2, n_in=200, n_out=48, T=400, g=40, ternary=0.95),
     "wide_repeat": synth.LayerConfig("wide_repeat", N=96, L=2, n_in=170, n_out=8, T=800, g=200, ternary=0.5),
-    # ragged N; 320 inputs, terms on the first 64 only: the other input ranges get no pass
     # 16 wavefronts: 32 word blocks, which the workgroups pack themselves, and 33, which they do not
     "word_blocks_32": synth.LayerConfig("word_blocks_32", N=130, L=2, n_in=8, n_out=9, T=12, g=4, ternary=1.0),
     "word_blocks_33": synth.LayerConfig("word_blocks_33", N=130, L=2, n_in=8, n_out=5, T=24, g=4, ternary=1.0),
@@ -124,6 +123,14 @@ SMALL = {
     "ragged_19_tiles": synth.LayerConfig("ragged_19_tiles", N=1201, L=1, n_in=9, n_out=5, T=40, g=5, ternary=0.5),
     "ragged_591_tiles": synth.LayerConfig("ragged_591_tiles", N=12583, L=3, n_in=5, n_out=2, T=20, g=5, ternary=0.5),
     "aligned_19_tiles": synth.LayerConfig("aligned_19_tiles", N=1168, L=1, n_in=9, n_out=5, T=40, g=5, ternary=0.5),
+    # one input a wavefront (staged one after the other: fold_raw with 8 wavefronts, many_outputs with 16) and
+    # one more (in batches); two and one more; inputs 4 MiB apart, with 11 outputs (batches) and 12 (one after the other)
+    "stage_9": synth.LayerConfig("stage_9", N=64, L=2, n_in=9, n_out=3, T=2600, g=8, ternary=0.3),
+    "stage_17": synth.LayerConfig("stage_17", N=130, L=2, n_in=17, n_out=9, T=64, g=4, ternary=0.4),
+    "stage_33": synth.LayerConfig("stage_33", N=130, L=2, n_in=33, n_out=9, T=64, g=4, ternary=0.4),
+    "stage_4mib_11": synth.LayerConfig("stage_4mib_11", N=1 << 15, L=8, n_in=34, n_out=11, T=8, g=4, ternary=0.5),
+    "stage_4mib_12": synth.LayerConfig("stage_4mib_12", N=1 << 15, L=8, n_in=34, n_out=12, T=8, g=4, ternary=0.5),
+    # ragged N; 320 inputs, terms on the first 64 only: the other input ranges get no pass
     "wide_sparse": synth.LayerConfig("wide_sparse", N=100, L=2, n_in=320, n_out=5, T=64, g=8, ternary=0.5),
 }
 
