@@ -117,6 +117,8 @@ SMALL = {
     "wide_repeat": synth.LayerConfig("wide_repeat", N=96, L=2, n_in=170, n_out=8, T=800, g=200, ternary=0.5),
     # 16 wavefronts: 32 word blocks, which the workgroups pack themselves, and 33, which they do not
     "word_blocks_32": synth.LayerConfig("word_blocks_32", N=130, L=2, n_in=8, n_out=9, T=12, g=4, ternary=1.0),
+    # with two levels of common partial sums read from them
+    "word_blocks_partial": synth.LayerConfig("word_blocks_partial", N=130, L=2, n_in=4, n_out=12, T=32, g=16, ternary=1.0),
     "word_blocks_33": synth.LayerConfig("word_blocks_33", N=130, L=2, n_in=8, n_out=5, T=24, g=4, ternary=1.0),
     # rows off the 128-byte lines, 1, 19 and 591 tiles (fewer than, and no multiple of, the 8 XCDs); rows on them
     "ragged_1_tile": synth.LayerConfig("ragged_1_tile", N=37, L=1, n_in=5, n_out=3, T=20, g=5, ternary=0.5),
@@ -160,6 +162,16 @@ def _small_layer(name):
         return synth.make_layer(cfg, 1)
     Nq = 1 << max(6, (cfg.N - 1).bit_length())
     return synth.make_layer(cfg, 5, moduli=synth.ntt_primes(Nq, cfg.L))
+
+
+@pytest.mark.parametrize("name,own", [("word_blocks_32", True), ("word_blocks_partial", True), ("word_blocks_33", False)])
+def test_layers_on_both_sides_of_the_word_blocks_rule(dev, name, own):
+    """Up to two word blocks a wavefront, in one turn of workgroups, are packed by the workgroups themselves."""
+    layer = _small_layer(name)
+    st = fiona.Plan.from_layer(fiona.Ctx(layer.N, layer.L, layer.moduli), layer, flags=fiona.FIONA_PLAN_HOST_ONLY).stats()
+    blocks = st["n_partial"] + st["n_sum_resident"] + st["n_use"]
+    assert st["grid"] <= 256 and (blocks <= 2 * st["waves"]) == own
+    assert (st["n_partial"] > 0 and st["partial_levels"] == 2) == (name == "word_blocks_partial")
 
 
 @pytest.mark.parametrize("name", list(SMALL))
