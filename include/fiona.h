@@ -454,9 +454,9 @@ int fiona_stream_write(uint64_t *dst, uint64_t words, uint32_t blocks, hipStream
  * rescaler (capacity = max_ct) or rotator (capacity = max_rot) is laid out
  * at fake device addresses, the call's launches are recorded instead of
  * issued, and every global access of every workgroup and thread of every NTT
- * pass is recomputed with the kernels' own offset arithmetic; the other
- * kernels (whole transforms, inner product, transpose) are checked by the
- * byte ranges they touch.
+ * pass and launch of whole transforms is recomputed with the kernels' own
+ * offset arithmetic, as are the whole transforms' LDS words; the inner product
+ * and the transpose are checked by the byte ranges they touch.
  *   moduli      host, L moduli (op 0) or L data moduli then the special
  *               prime (op 1), each = 1 mod 2N
  *   n_call      ciphertexts (op 0) or rotations (op 1) of the call; the

@@ -2,11 +2,14 @@
 //
 // A rescaler or rotator is laid out at fake device addresses, one call is
 // recorded instead of launched (ntt_host.hpp), and every global access of
-// every workgroup and thread of every recorded pass is recomputed on the host
-// through the same offset helpers the kernels use (GeomA, GeomB, GeomRot in
-// ntt_kernel.hpp).  Each access must lie inside the buffer that holds its
+// every workgroup and thread of every recorded pass and launch of whole
+// transforms is recomputed on the host through the same offset helpers the
+// kernels use (GeomA, GeomB, GeomRot in ntt_kernel.hpp, GeomWhole in
+// ntt_whole.hpp).  Each access must lie inside the buffer that holds its
 // descriptor's base, every offset must stay below 2^32 bytes, and every
-// descriptor's end pointer must be that buffer's end.  No device is needed.
+// descriptor's end pointer must be that buffer's end.  Of the whole
+// transforms the LDS words are recomputed too: each step must touch every word
+// of the vector once, inside the LDS.  No device is needed.
 #include <algorithm>
 #include <cstdint>
 #include <cstring>
@@ -15,6 +18,7 @@
 
 #include "fiona.h"
 #include "ntt_host.hpp"
+#include "ntt_whole.hpp"
 
 namespace fiona_host {
 
@@ -243,6 +247,126 @@ bool replay_one(Checker &C, const PassLaunch &L) {
   }
 }
 
+// A set of N words, each to be met once.
+struct Once {
+  std::vector<uint8_t> seen;
+  uint32_t left;
+  explicit Once(uint32_t words, uint32_t n) : seen(words, 0), left(n) {}
+  bool take(uint64_t w) {
+    if (w >= seen.size() || seen[w] || !left) return false;
+    seen[w] = 1;
+    --left;
+    return true;
+  }
+};
+
+template <uint32_t LN>
+bool whole(Checker &C, const WholeLaunch &L) {
+  using W = fiona::Whole<LN>;
+  using A = typename W::A;
+  using B = typename W::B;
+  using G = fiona::GeomWhole<LN>;
+  constexpr uint32_t N = W::N;
+  const bool trans = L.kind == WholeLaunch::kDivide, rowwise = L.kind != WholeLaunch::kRescale;
+  const std::string name = L.kind == WholeLaunch::kRescale  ? "whole rescale"
+                           : L.kind == WholeLaunch::kDigits ? "whole digits"
+                                                            : "whole division";
+  // one workgroup: the LDS words of each step (distinct, all N of them, inside
+  // the vector's part of the LDS) and the offsets of each buffer (every word once)
+  auto step = [&](const char *what, uint32_t words, uint32_t its, uint32_t per, auto index) {
+    Once once(words, N);
+    for (uint32_t it = 0; it < its; ++it)
+      for (uint32_t u = 0; u < per; ++u)
+        if (!once.take(index(it, u))) return C.fail(name + ": " + what + ": word met twice or outside");
+    return once.left == 0 || C.fail(name + ": " + what + ": words left out");
+  };
+  auto bytes = [](Off o) { return ((uint64_t)o.v + o.s) % 8 ? ~0ull : ((uint64_t)o.v + o.s) / 8; };
+  for (const bool fwd : {false, true})
+    if (!step("first groups", W::WORDS, W::T, A::E1, [&](uint32_t t, uint32_t u) {
+          return G::first(G::col1(t), G::grp1(t), u, fwd);
+        }) ||
+        !step("pass A's last groups", W::WORDS, G::IT2, A::E2, [&](uint32_t it, uint32_t e) {
+          return G::last_a(G::col2(it), G::off2(it), e, fwd);
+        }))
+      return false;
+  if (!step("pass B's reads", W::WORDS, G::IT3, B::E1,
+            [&](uint32_t it, uint32_t u) { return G::b_in(G::pos3(it), G::grp3(it), u); }) ||
+      !step("pass B's writes", W::WORDS, G::IT3, B::E1,
+            [&](uint32_t it, uint32_t u) { return G::b_out(G::pos3(it), G::grp3(it), u); }) ||
+      !step("coefficients", W::WORDS, W::T, A::E1, [&](uint32_t t, uint32_t v) {
+        const uint32_t n = G::coef(G::col1(t), G::grp1(t), v);
+        return G::word(n % W::N2, n);
+      }))
+    return false;
+  for (const bool rw : {false, rowwise})   // the inverse's last groups, then the forward one's
+    if (!step("last groups", W::WORDS, G::IT4, B::E2, [&](uint32_t it, uint32_t u) {
+          const uint32_t k2 = G::row4(it, rw);
+          return G::last_b(rw == rowwise ? G::pos_fwd(k2) : k2, G::off4(it, rw), u);
+        }))
+      return false;
+  if (!step("input", N, W::T, A::E1,
+            [&](uint32_t t, uint32_t u) { return bytes(Off{G::in(G::col1(t), G::grp1(t), u, trans), 0}); }) ||
+      !step("mid", N, G::IT2, A::E2,
+            [&](uint32_t it, uint32_t u) { return bytes(G::mid(G::col2(it), G::off2(it), u)); }) ||
+      !step("natural order", N, G::IT4, B::E2, [&](uint32_t it, uint32_t u) {
+        return bytes(G::natural(G::row4(it, rowwise), G::off4(it, rowwise), u));
+      }))
+    return false;
+  if (rowwise && !step("transposed", N, G::IT4, B::E2, [&](uint32_t it, uint32_t u) {
+        return bytes(G::row(G::row4(it, true), G::off4(it, true), u));
+      }))
+    return false;
+  uint64_t post_hi = 0;
+  for (uint32_t it = 0; it < G::IT4; ++it)
+    for (uint32_t u = 0; u < B::E2; ++u)
+      if (!C.grow(post_hi, G::post(G::off4(it, false), u), 16, "whole transform post")) return false;
+  if (trans)
+    for (uint32_t r = 0; r < L.G.n_rot; ++r)
+      if (!step("automorphism's reads", W::WORDS, N, 1, [&](uint32_t d, uint32_t) {
+            const uint32_t k = G::slot(L.G.g[r], d);
+            return G::word(G::pos_fwd(k % W::N2), k);
+          }) ||
+          !step("automorphism's writes", N, N, 1, [&](uint32_t d, uint32_t) { return bytes(Off{G::dest(d), 0}); }))
+        return false;
+
+  // every workgroup: its buffers and tables, each output vector once
+  constexpr uint64_t vec = (uint64_t)N * 8;
+  auto tables = [&](const NttSet *S, bool fwd) {
+    return S && (fwd == (S->post == nullptr) || C.fail(name + ": post table and direction differ")) &&
+           C.span("whole transform mid", (uint64_t)S->mid, 0, vec, nullptr) &&
+           C.tables(S->dft_a, fwd ? W::N2 : W::N2 / 2) && C.tables(S->dft_b, W::N1 / 2) &&
+           (fwd || C.span("whole transform post", (uint64_t)S->post, 0, post_hi, nullptr));
+  };
+  const uint32_t in_vec = L.kind == WholeLaunch::kDigits ? 1 : L.n + 1;   // vectors per input vector: all its limbs
+  Once outs(L.V * L.n, L.V * L.n);
+  for (uint32_t b = 0; b < L.V * L.groups; ++b) {
+    const fiona::WholeUnit un = fiona::whole_unit(b, L.groups, L.n);
+    if (un.v >= L.V || un.last > L.n) return C.fail(name + ": workgroup outside the call");
+    const uint64_t in = (uint64_t)L.in + un.v * in_vec * vec;
+    const NttSet *I = C.set(L.inv_sets, L.kind == WholeLaunch::kDigits ? un.v : 0);
+    if (!tables(I, false)) return false;
+    const uint64_t inv_at = in + (in_vec - 1) * vec;   // the limb that goes back to its coefficients
+    const std::string at = name + ", vector " + std::to_string(un.v);
+    if (!C.span((at + ": input").c_str(), inv_at, 0, vec, L.in_end)) return false;
+    for (uint32_t l = un.first; l < un.last; ++l) {
+      const std::string atl = at + ", modulus " + std::to_string(l);
+      if (!tables(C.set(L.fwd_sets, l), true)) return false;
+      uint64_t o = (uint64_t)un.v * L.n + l;   // the output vector
+      if (L.kind == WholeLaunch::kDivide) {
+        const uint32_t p = un.v / L.G.n_rot, r = un.v - p * L.G.n_rot;
+        if (p > 1 || L.G.L != L.n) return C.fail(atl + ": bad shape");
+        o = ((uint64_t)r * 2 + p) * L.n + l;
+        if (p == 0 && !C.span((atl + ": c0").c_str(), (uint64_t)L.add + l * vec, 0, vec, L.add_end)) return false;
+      }
+      if (L.kind != WholeLaunch::kDigits && !C.span((atl + ": minuends").c_str(), in + l * vec, 0, vec, L.in_end))
+        return false;
+      if (!C.span((atl + ": output").c_str(), (uint64_t)L.out + o * vec, 0, vec, L.out_end)) return false;
+      if (!outs.take(o)) return C.fail(atl + ": output written twice");
+    }
+  }
+  return outs.left == 0 || C.fail(name + ": outputs left out");
+}
+
 }  // namespace
 
 std::string check_launches(const LaunchRecord &rec, const std::vector<Region> &regions, uint64_t sets_dev,
@@ -254,6 +378,16 @@ std::string check_launches(const LaunchRecord &rec, const std::vector<Region> &r
              std::to_string(u.most);
   for (const SpanAccess &s : rec.spans)
     if (!C.span(s.what, s.base, s.lo, s.hi, nullptr)) return C.err;
+  for (const WholeLaunch &L : rec.whole) {
+    if (L.V == 0 || L.groups == 0 || L.groups > L.n) {
+      C.fail("bad whole launch");
+      return C.err;
+    }
+    bool ok = false;
+    for_log_n<14>(L.log_n, [&](auto ln) { ok = whole<decltype(ln)::value>(C, L); });
+    if (!ok) return C.err.empty() ? "whole launch outside 2^8 .. 2^14" : C.err;
+    ++C.launch;
+  }
   for (const PassLaunch &L : rec.passes) {
     if (L.V == 0 || L.V > 65535 || L.P.vps == 0) {
       C.fail("bad vector count");

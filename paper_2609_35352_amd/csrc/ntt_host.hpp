@@ -30,7 +30,17 @@ struct PassLaunch {
   NttPass P;
   RotArgs G;                         // kPassBRot only
 };
-struct SpanAccess {   // a kernel that is not an NTT pass: bytes [lo, hi) of the buffer at base
+// A launch of whole transforms (ntt_whole.hpp): V vectors, each with n moduli in groups.
+struct WholeLaunch {
+  enum Kind : uint32_t { kRescale, kDigits, kDivide } kind;
+  uint32_t log_n, V, n, groups;
+  const uint64_t *in, *add;   // kDivide: u' and c0
+  uint64_t *out;
+  const void *in_end, *add_end, *out_end;
+  const NttSet *inv_sets, *fwd_sets;
+  RotArgs G;                  // kDivide only
+};
+struct SpanAccess {   // another kernel: bytes [lo, hi) of the buffer at base
   const char *what;
   uint64_t base, lo, hi;
 };
@@ -40,6 +50,7 @@ struct LdsUse {   // the LDS a launch asks for, and the most its kernel may
 };
 struct LaunchRecord {
   std::vector<PassLaunch> passes;
+  std::vector<WholeLaunch> whole;
   std::vector<SpanAccess> spans;
   std::vector<LdsUse> lds;
 };

@@ -143,7 +143,9 @@ struct Buf {
   }
 };
 
-__device__ __forceinline__ uint32_t bit_reverse(uint32_t x, uint32_t bits) { return __brev(x) >> (32 - bits); }
+__host__ __device__ constexpr uint32_t bit_reverse(uint32_t x, uint32_t bits) {
+  return __builtin_bitreverse32(x) >> (32 - bits);
+}
 // The four-bit reversal of u < 16 (a group's position in the bit-reversed order).
 __host__ __device__ constexpr uint32_t rev4(uint32_t u) {
   return ((u & 1u) << 3) | ((u & 2u) << 1) | ((u & 4u) >> 1) | ((u & 8u) >> 3);
@@ -155,7 +157,7 @@ __host__ __device__ constexpr uint32_t rev4(uint32_t u) {
 // different banks.  Within a column one padding word follows every 16, so
 // that 16 consecutive bit-reversed positions (the row loads of pass B) fall
 // into different banks too.
-__device__ __forceinline__ uint32_t pidx(uint32_t i) { return i + (i >> 4); }
+__host__ __device__ constexpr uint32_t pidx(uint32_t i) { return i + (i >> 4); }
 __host__ __device__ constexpr uint32_t padded_len(uint32_t m) { return m + m / 16 + 1; }
 
 // Stages S0 .. S0+R-1 of the radix-2 DFT on one group of 2^R words held in

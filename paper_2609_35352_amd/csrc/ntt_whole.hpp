@@ -48,21 +48,94 @@ struct Whole {
   using B = Side<LOG1>;
   static constexpr uint32_t T = N / A::E1;                      // threads: one first group of pass A each
   static constexpr uint32_t PM = padded_len(N2), WORDS = N1 * PM;   // LDS words of a column and of the vector
-  // the LDS word of row position p, column c
-  static __device__ __forceinline__ uint32_t at(uint32_t p, uint32_t c) { return c * PM + pidx(p); }
-  // the column that holds output k1 = o + 2^R1 u of a row (pass B works in
-  // place: first group i' leaves word u of its results in column i' + E2 u)
-  static __device__ __forceinline__ uint32_t col(uint32_t o, uint32_t u) { return B::rev2(u) + B::E2 * o; }
-  static __device__ __forceinline__ uint32_t col_of(uint32_t k1) { return col(k1 % B::E1, k1 / B::E1); }
-  static __host__ __device__ constexpr uint32_t mid(uint32_t n1, uint32_t k2) {
-    return ((n1 / kNttCols) * N2 + k2) * kNttCols + n1 % kNttCols;
-  }
 };
+
+// The kernels' indexes: LDS words, and byte offsets from each buffer's base.
+// They address memory and LDS only through these, and the host replay of a
+// launch (ntt_check.hip) runs them over every workgroup and thread.
+template <uint32_t LN>
+struct GeomWhole {
+  using W = Whole<LN>;
+  using A = typename W::A;
+  using B = typename W::B;
+  static constexpr uint32_t N = W::N, N1 = W::N1, N2 = W::N2;
+  // the LDS word of row position p, column c
+  static __host__ __device__ constexpr uint32_t at(uint32_t p, uint32_t c) { return c * W::PM + pidx(p); }
+  // the column that holds output k1 = o + E1 u of a row (pass B works in place:
+  // first group i' leaves word u of its results in column i' + E2 u)
+  static __host__ __device__ constexpr uint32_t col(uint32_t o, uint32_t u) { return B::rev2(u) + B::E2 * o; }
+  // pass A's first groups: thread t's column n1 and group i'
+  static __host__ __device__ constexpr uint32_t col1(uint32_t t) { return t % N1; }
+  static __host__ __device__ constexpr uint32_t grp1(uint32_t t) { return t / N1; }
+  // word u of the inverse's group (element coef(n1, i', rev1(u))), and where result u goes
+  static __host__ __device__ constexpr uint32_t coef(uint32_t n1, uint32_t ip, uint32_t v) {
+    return n1 + N1 * (ip + A::E2 * v);
+  }
+  static __host__ __device__ constexpr uint32_t in(uint32_t n1, uint32_t ip, uint32_t u, bool trans) {
+    const uint32_t n = coef(n1, ip, A::rev1(u));
+    return (trans ? (n % N2) * N1 + n / N2 : n) * 8;
+  }
+  static __host__ __device__ constexpr uint32_t first(uint32_t n1, uint32_t ip, uint32_t u, bool fwd) {
+    return at(fwd ? u * A::E2 + ip : A::E1 * A::rev2(ip) + u, n1);
+  }
+  // pass A's last groups, loop index it < N / A::E2: column, and o of the outputs k2 = o + E1 u
+  static constexpr uint32_t IT2 = N / A::E2;
+  static __host__ __device__ constexpr uint32_t col2(uint32_t it) { return it % N1; }
+  static __host__ __device__ constexpr uint32_t off2(uint32_t it) { return it / N1; }
+  static __host__ __device__ constexpr Off mid(uint32_t c, uint32_t o, uint32_t u) {
+    return Off{(((c / kNttCols) * N2 + o) * kNttCols + c % kNttCols) * 8, A::E1 * u * kNttCols * 8};
+  }
+  static __host__ __device__ constexpr uint32_t last_a(uint32_t c, uint32_t o, uint32_t e, bool fwd) {
+    return at(fwd ? A::rev1(o) * A::E2 + e : o + A::E1 * e, c);
+  }
+  // pass B's first groups, it < N / B::E1: row position p and group i'; word u read and written
+  static constexpr uint32_t IT3 = N / B::E1;
+  static __host__ __device__ constexpr uint32_t pos3(uint32_t it) { return it % N2; }
+  static __host__ __device__ constexpr uint32_t grp3(uint32_t it) { return it / N2; }
+  static __host__ __device__ constexpr uint32_t b_in(uint32_t p, uint32_t ip, uint32_t u) {
+    return at(p, ip + B::E2 * B::rev1(u));
+  }
+  static __host__ __device__ constexpr uint32_t b_out(uint32_t p, uint32_t ip, uint32_t u) {
+    return at(p, ip + B::E2 * u);
+  }
+  // its last groups, it < N / B::E2: row k2 and o of the outputs k1 = o + E1 u, rows first or (rowwise) a row's o first
+  static constexpr uint32_t IT4 = N / B::E2;
+  static __host__ __device__ constexpr uint32_t row4(uint32_t it, bool rowwise) { return rowwise ? it / B::E1 : it % N2; }
+  static __host__ __device__ constexpr uint32_t off4(uint32_t it, bool rowwise) { return rowwise ? it % B::E1 : it / N2; }
+  // the row position of k2 after a forward pass A
+  static __host__ __device__ constexpr uint32_t pos_fwd(uint32_t k2) { return bit_reverse(k2, W::LOG2); }
+  static __host__ __device__ constexpr uint32_t last_b(uint32_t p, uint32_t o, uint32_t u) { return at(p, col(o, u)); }
+  static __host__ __device__ constexpr Off post(uint32_t o, uint32_t u) { return Off{o * 16, u * B::E1 * 16}; }
+  // output (k2, k1 = o + E1 u) in natural order and transposed
+  static __host__ __device__ constexpr Off natural(uint32_t k2, uint32_t o, uint32_t u) {
+    return Off{(k2 + N2 * o) * 8, N2 * B::E1 * 8 * u};
+  }
+  static __host__ __device__ constexpr Off row(uint32_t k2, uint32_t o, uint32_t u) {
+    return Off{(k2 * N1 + o) * 8, u * B::E1 * 8};
+  }
+  // the LDS word of output k, its row at position p
+  static __host__ __device__ constexpr uint32_t word(uint32_t p, uint32_t k) {
+    return at(p, col((k / N2) % B::E1, (k / N2) / B::E1));
+  }
+  // destination d of the automorphism by g takes slot pi(d) = g d + (g - 1) / 2 mod N
+  static __host__ __device__ constexpr uint32_t slot(uint32_t g, uint32_t d) { return (g * d + (g - 1) / 2) & (N - 1); }
+  static __host__ __device__ constexpr uint32_t dest(uint32_t d) { return d * 8; }
+};
+
+// The vector and the moduli [first, last) of n of workgroup b, the moduli in `groups` groups.
+struct WholeUnit {
+  uint32_t v, first, last;
+};
+__host__ __device__ inline WholeUnit whole_unit(uint32_t b, uint32_t groups, uint32_t n) {
+  const uint32_t v = b / groups, g = b - v * groups;
+  return WholeUnit{v, n * g / groups, n * (g + 1) / groups};
+}
 template <uint32_t LN>
 constexpr size_t whole_smem() {
   using W = Whole<LN>;
   return W::WORDS * sizeof(double) + (W::N2 + W::N1 / 2) * sizeof(Tw);
 }
+static_assert(whole_smem<12>() <= 64 * 1024, "from 2^13 on the kernels are given more LDS than by default");
 
 // The two passes' twiddles of one set into LDS (tw_a, then tw_b).
 template <uint32_t LN>
@@ -89,48 +162,50 @@ __device__ __forceinline__ void whole_middle(double *xs, const Tw *tw_a, const N
   using W = Whole<LN>;
   using A = typename W::A;
   using B = typename W::B;
+  using G = GeomWhole<LN>;
   const double q = S.q, qinv = S.qinv;
   const Buf mid(S.mid, S.mid + W::N);
   __syncthreads();
 #pragma unroll 1
-  for (uint32_t it = threadIdx.x; it < W::N / A::E2; it += W::T) {
-    const uint32_t c = it % W::N1, o = it / W::N1;   // outputs k2 = o + E1 u, o < E1
+  for (uint32_t it = threadIdx.x; it < G::IT2; it += W::T) {
+    const uint32_t c = G::col2(it), o = G::off2(it);
     double m[A::E2], r[A::E2];
 #pragma unroll
-    for (uint32_t u = 0; u < A::E2; ++u) m[u] = mid.f64(W::mid(c, o) * 8, A::E1 * u * kNttCols * 8);
-    const uint32_t j = A::rev1(o);
+    for (uint32_t u = 0; u < A::E2; ++u) {
+      const Off om = G::mid(c, o, u);
+      m[u] = mid.f64(om.v, om.s);
+    }
 #pragma unroll
-    for (uint32_t e = 0; e < A::E2; ++e) r[e] = xs[W::at(FWD ? j * A::E2 + e : o + A::E1 * e, c)];
-    if constexpr (FWD) tree_butterflies<A::R1, A::R2>(r, j, [&](uint32_t t) { return tw_a[t]; }, q);
+    for (uint32_t e = 0; e < A::E2; ++e) r[e] = xs[G::last_a(c, o, e, FWD)];
+    if constexpr (FWD) tree_butterflies<A::R1, A::R2>(r, A::rev1(o), [&](uint32_t t) { return tw_a[t]; }, q);
     else butterflies<W::LOG2, A::R1, A::R2>(r, o, [&](uint32_t t) { return tw_a[t]; }, q, qinv);
 #pragma unroll
     for (uint32_t e = 0; e < A::E2; ++e) {
       const double w = m[FWD ? A::rev2(e) : e];
-      xs[W::at(FWD ? j * A::E2 + e : o + A::E1 * e, c)] = mul_tw(r[e], Tw{w, w * qinv}, q);
+      xs[G::last_a(c, o, e, FWD)] = mul_tw(r[e], Tw{w, w * qinv}, q);
     }
   }
   __syncthreads();
 #pragma unroll 1
-  for (uint32_t it = threadIdx.x; it < W::N / B::E1; it += W::T) {
-    const uint32_t p = it % W::N2, ip = it / W::N2;
+  for (uint32_t it = threadIdx.x; it < G::IT3; it += W::T) {
+    const uint32_t p = G::pos3(it), ip = G::grp3(it);
     double r[B::E1];
 #pragma unroll
-    for (uint32_t u = 0; u < B::E1; ++u) r[u] = xs[W::at(p, ip + B::E2 * B::rev1(u))];
+    for (uint32_t u = 0; u < B::E1; ++u) r[u] = xs[G::b_in(p, ip, u)];
     whole_first<W::LOG1>(r, S.dft_b, q, qinv);
 #pragma unroll
-    for (uint32_t u = 0; u < B::E1; ++u) xs[W::at(p, ip + B::E2 * u)] = reduce(r[u], q, qinv);
+    for (uint32_t u = 0; u < B::E1; ++u) xs[G::b_out(p, ip, u)] = reduce(r[u], q, qinv);
   }
   __syncthreads();
 }
 
-// Pass B's last groups: y[u] is output (k2, k1 = o + E1 u), its LDS word at
-// W::at(p, W::col(o, u)).
+// Pass B's last groups: y[u] is output (k2, k1 = o + E1 u), its row at position p.
 template <uint32_t LN>
 __device__ __forceinline__ void whole_last(const double *xs, uint32_t p, uint32_t o, const Tw *tw_b,
                                            double (&y)[Whole<LN>::B::E2], const NttSet &S) {
   using W = Whole<LN>;
 #pragma unroll
-  for (uint32_t u = 0; u < W::B::E2; ++u) y[u] = xs[W::at(p, W::col(o, u))];
+  for (uint32_t u = 0; u < W::B::E2; ++u) y[u] = xs[GeomWhole<LN>::last_b(p, o, u)];
   butterflies<W::LOG1, W::B::R1, W::B::R2>(y, o, [&](uint32_t t) { return tw_b[t]; }, S.q, S.qinv);
 }
 
@@ -144,13 +219,11 @@ __device__ __forceinline__ void whole_inverse(double *xs, Tw *tw_a, Tw *tw_b, co
   using W = Whole<LN>;
   using A = typename W::A;
   using B = typename W::B;
-  const uint32_t n1 = threadIdx.x % W::N1, ip = threadIdx.x / W::N1;
+  using G = GeomWhole<LN>;
+  const uint32_t n1 = G::col1(threadIdx.x), ip = G::grp1(threadIdx.x);
   uint64_t x[A::E1];
 #pragma unroll
-  for (uint32_t u = 0; u < A::E1; ++u) {
-    const uint32_t n = n1 + W::N1 * (ip + A::E2 * A::rev1(u));
-    x[u] = in.u64((TRANS ? (n % W::N2) * W::N1 + n / W::N2 : n) * 8, 0);
-  }
+  for (uint32_t u = 0; u < A::E1; ++u) x[u] = in.u64(G::in(n1, ip, u, TRANS), 0);
   const NttSet S = *sets;
   const double q = S.q, qinv = S.qinv;
   whole_twiddles<LN>(tw_a, tw_b, S, false);
@@ -159,29 +232,29 @@ __device__ __forceinline__ void whole_inverse(double *xs, Tw *tw_a, Tw *tw_b, co
 #pragma unroll
     for (uint32_t u = 0; u < A::E1; ++u) r[u] = to_f64(x[u]);
     whole_first<W::LOG2>(r, S.dft_a, q, qinv);
-    const uint32_t i = A::rev2(ip);
 #pragma unroll
-    for (uint32_t u = 0; u < A::E1; ++u) xs[W::at(A::E1 * i + u, n1)] = reduce(r[u], q, qinv);
+    for (uint32_t u = 0; u < A::E1; ++u) xs[G::first(n1, ip, u, false)] = reduce(r[u], q, qinv);
   }
   whole_middle<LN, false>(xs, tw_a, S);
   const Buf post(S.post, S.post + W::N1);
 #pragma unroll 1
-  for (uint32_t it = threadIdx.x; it < W::N / B::E2; it += W::T) {
-    const uint32_t k2 = it % W::N2, o = it / W::N2;
+  for (uint32_t it = threadIdx.x; it < G::IT4; it += W::T) {
+    const uint32_t k2 = G::row4(it, false), o = G::off4(it, false);
     double y[B::E2];
     whole_last<LN>(xs, k2, o, tw_b, y, S);
 #pragma unroll
     for (uint32_t u = 0; u < B::E2; ++u) {
-      double z = reduce(mul_tw(y[u], post.tw(o * 16, u * B::E1 * 16), q), q, qinv);
+      const Off op = G::post(o, u);
+      double z = reduce(mul_tw(y[u], post.tw(op.v, op.s), q), q, qinv);
       if (CANON && z < 0.0) z += q;
-      xs[W::at(k2, W::col(o, u))] = z;
+      xs[G::last_b(k2, o, u)] = z;
     }
   }
   __syncthreads();
 #pragma unroll
   for (uint32_t v = 0; v < A::E1; ++v) {
-    const uint32_t n = n1 + W::N1 * (ip + A::E2 * v);
-    w[v] = xs[W::at(n % W::N2, W::col_of(n / W::N2))];
+    const uint32_t n = G::coef(n1, ip, v);
+    w[v] = xs[G::word(n % W::N2, n)];
   }
   __syncthreads();
 }
@@ -193,15 +266,16 @@ __device__ __forceinline__ void whole_forward(double *xs, Tw *tw_a, Tw *tw_b, co
                                               const NttSet &S) {
   using W = Whole<LN>;
   using A = typename W::A;
+  using G = GeomWhole<LN>;
   whole_twiddles<LN>(tw_a, tw_b, S, true);
-  const uint32_t n1 = threadIdx.x % W::N1, ip = threadIdx.x / W::N1;
+  const uint32_t n1 = G::col1(threadIdx.x), ip = G::grp1(threadIdx.x);
   double r[A::E1];
 #pragma unroll
   for (uint32_t v = 0; v < A::E1; ++v) r[v] = w[v];
   const Tw *__restrict__ tree = S.dft_a;
   tree_butterflies<0, A::R1>(r, 0, [&](uint32_t t) { return tree[t]; }, S.q);
 #pragma unroll
-  for (uint32_t v = 0; v < A::E1; ++v) xs[W::at(v * A::E2 + ip, n1)] = reduce(r[v], S.q, S.qinv);
+  for (uint32_t v = 0; v < A::E1; ++v) xs[G::first(n1, ip, v, true)] = reduce(r[v], S.q, S.qinv);
   whole_middle<LN, true>(xs, tw_a, S);
 }
 
@@ -217,31 +291,36 @@ whole_rescale_kernel(const uint64_t *in, uint64_t *out, const NttSet *sets, uint
   using W = Whole<LN>;
   extern __shared__ double xs[];
   Tw *tw_a = (Tw *)(xs + W::WORDS), *tw_b = tw_a + W::N2;
-  const uint32_t v = blockIdx.x / groups, g = blockIdx.x - v * groups;
-  const uint32_t l0 = (L - 1) * g / groups, l1 = (L - 1) * (g + 1) / groups;
+  using G = GeomWhole<LN>;
+  const WholeUnit un = whole_unit(blockIdx.x, groups, L - 1);
+  const uint32_t v = un.v;
   double w[W::A::E1];
   whole_inverse<LN, false, false>(xs, tw_a, tw_b, Buf(in + ((size_t)v * L + L - 1) * W::N, in_end), sets + (L - 1), w);
 #pragma unroll 1
-  for (uint32_t l = l0; l < l1; ++l) {
+  for (uint32_t l = un.first; l < un.last; ++l) {
     const NttSet S = sets[l];
     const double q = S.q, qinv = S.qinv;
     const Buf base(in + ((size_t)v * L + l) * W::N, in_end), o_buf(out + ((size_t)v * (L - 1) + l) * W::N, out_end);
     whole_forward<LN>(xs, tw_a, tw_b, w, S);
 #pragma unroll 1
-    for (uint32_t it = threadIdx.x; it < W::N / W::B::E2; it += W::T) {
-      const uint32_t k2 = it % W::N2, o = it / W::N2;
+    for (uint32_t it = threadIdx.x; it < G::IT4; it += W::T) {
+      const uint32_t k2 = G::row4(it, false), o = G::off4(it, false);
       uint64_t b[W::B::E2];
 #pragma unroll
-      for (uint32_t u = 0; u < W::B::E2; ++u) b[u] = base.u64_once((k2 + W::N2 * o) * 8, W::N2 * W::B::E1 * 8 * u);
+      for (uint32_t u = 0; u < W::B::E2; ++u) {
+        const Off on = G::natural(k2, o, u);
+        b[u] = base.u64_once(on.v, on.s);
+      }
       double y[W::B::E2];
-      whole_last<LN>(xs, bit_reverse(k2, W::LOG2), o, tw_b, y, S);
+      whole_last<LN>(xs, G::pos_fwd(k2), o, tw_b, y, S);
 #pragma unroll
       for (uint32_t u = 0; u < W::B::E2; ++u) {
+        const Off on = G::natural(k2, o, u);
         const double z = mul_tw(minuend<W::LOG1>(b[u], y[u], q, qinv), S.inv, q);
-        o_buf.put(to_u64(canonical(z, q, qinv)), (k2 + W::N2 * o) * 8, W::N2 * W::B::E1 * 8 * u);
+        o_buf.put(to_u64(canonical(z, q, qinv)), on.v, on.s);
       }
     }
-    if (l + 1 < l1) __syncthreads();   // uniform over the workgroup
+    if (l + 1 < un.last) __syncthreads();   // uniform over the workgroup
   }
 }
 
@@ -254,25 +333,29 @@ whole_digits_kernel(const uint64_t *c1, uint64_t *dhat, const NttSet *inv_sets, 
   using W = Whole<LN>;
   extern __shared__ double xs[];
   Tw *tw_a = (Tw *)(xs + W::WORDS), *tw_b = tw_a + W::N2;
-  const uint32_t M = L + 1, j = blockIdx.x / groups, g = blockIdx.x - j * groups;
-  const uint32_t m0 = M * g / groups, m1 = M * (g + 1) / groups;
+  using G = GeomWhole<LN>;
+  const uint32_t M = L + 1;
+  const WholeUnit un = whole_unit(blockIdx.x, groups, M);
+  const uint32_t j = un.v;
   double w[W::A::E1];
   whole_inverse<LN, false, true>(xs, tw_a, tw_b, Buf(c1 + (size_t)j * W::N, c1_end), inv_sets + j, w);
 #pragma unroll 1
-  for (uint32_t m = m0; m < m1; ++m) {
+  for (uint32_t m = un.first; m < un.last; ++m) {
     const NttSet S = fwd_sets[m];
     const Buf o_buf(dhat + ((size_t)j * M + m) * W::N, dhat_end);
     whole_forward<LN>(xs, tw_a, tw_b, w, S);
 #pragma unroll 1
-    for (uint32_t it = threadIdx.x; it < W::N / W::B::E2; it += W::T) {
-      const uint32_t k2 = it / W::B::E1, o = it % W::B::E1;
+    for (uint32_t it = threadIdx.x; it < G::IT4; it += W::T) {
+      const uint32_t k2 = G::row4(it, true), o = G::off4(it, true);
       double y[W::B::E2];
-      whole_last<LN>(xs, bit_reverse(k2, W::LOG2), o, tw_b, y, S);
+      whole_last<LN>(xs, G::pos_fwd(k2), o, tw_b, y, S);
 #pragma unroll
-      for (uint32_t u = 0; u < W::B::E2; ++u)
-        o_buf.put(to_u64(canonical(y[u], S.q, S.qinv)), (k2 * W::N1 + o) * 8, u * W::B::E1 * 8);
+      for (uint32_t u = 0; u < W::B::E2; ++u) {
+        const Off ot = G::row(k2, o, u);
+        o_buf.put(to_u64(canonical(y[u], S.q, S.qinv)), ot.v, ot.s);
+      }
     }
-    if (m + 1 < m1) __syncthreads();
+    if (m + 1 < un.last) __syncthreads();
   }
 }
 
@@ -287,27 +370,34 @@ whole_divide_kernel(const uint64_t *u_in, const uint64_t *c0, uint64_t *out, con
   using W = Whole<LN>;
   extern __shared__ double xs[];
   Tw *tw_a = (Tw *)(xs + W::WORDS), *tw_b = tw_a + W::N2;
-  const uint32_t L = R.L, M = L + 1, lv = blockIdx.x / groups, g = blockIdx.x - lv * groups;
-  const uint32_t l0 = L * g / groups, l1 = L * (g + 1) / groups;
-  const uint32_t p = lv / R.n_rot, r = lv - p * R.n_rot, gal = R.g[r], cg = (gal - 1) / 2;
+  using G = GeomWhole<LN>;
+  const uint32_t L = R.L, M = L + 1;
+  const WholeUnit un = whole_unit(blockIdx.x, groups, L);
+  const uint32_t lv = un.v, p = lv / R.n_rot, r = lv - p * R.n_rot, gal = R.g[r];
   double w[W::A::E1];
   whole_inverse<LN, true, false>(xs, tw_a, tw_b, Buf(u_in + ((size_t)lv * M + L) * W::N, u_end), p_inv_set, w);
 #pragma unroll 1
-  for (uint32_t l = l0; l < l1; ++l) {
+  for (uint32_t l = un.first; l < un.last; ++l) {
     const NttSet S = down_sets[l];
     const double q = S.q, qinv = S.qinv;
     const Buf base(u_in + ((size_t)lv * M + l) * W::N, u_end), add(c0 + (size_t)l * W::N, c0_end),
         o_buf(out + ((size_t)(r * 2 + p) * L + l) * W::N, out_end);
     whole_forward<LN>(xs, tw_a, tw_b, w, S);
 #pragma unroll 1
-    for (uint32_t it = threadIdx.x; it < W::N / W::B::E2; it += W::T) {
-      const uint32_t k2 = it / W::B::E1, o = it % W::B::E1, pos = bit_reverse(k2, W::LOG2);
+    for (uint32_t it = threadIdx.x; it < G::IT4; it += W::T) {
+      const uint32_t k2 = G::row4(it, true), o = G::off4(it, true), pos = G::pos_fwd(k2);
       uint64_t b[W::B::E2], a[W::B::E2];
 #pragma unroll
-      for (uint32_t u = 0; u < W::B::E2; ++u) b[u] = base.u64_once((k2 * W::N1 + o) * 8, u * W::B::E1 * 8);
+      for (uint32_t u = 0; u < W::B::E2; ++u) {
+        const Off ot = G::row(k2, o, u);
+        b[u] = base.u64_once(ot.v, ot.s);
+      }
       if (p == 0) {
 #pragma unroll
-        for (uint32_t u = 0; u < W::B::E2; ++u) a[u] = add.u64((k2 + W::N2 * o) * 8, W::N2 * W::B::E1 * 8 * u);
+        for (uint32_t u = 0; u < W::B::E2; ++u) {
+          const Off on = G::natural(k2, o, u);
+          a[u] = add.u64(on.v, on.s);
+        }
       }
       double y[W::B::E2];
       whole_last<LN>(xs, pos, o, tw_b, y, S);
@@ -318,17 +408,16 @@ whole_divide_kernel(const uint64_t *u_in, const uint64_t *c0, uint64_t *out, con
           z += to_f64(a[u]);
           z = z >= q ? z - q : z;
         }
-        xs[W::at(pos, W::col(o, u))] = z;
+        xs[G::last_b(pos, o, u)] = z;
       }
     }
     __syncthreads();
-    // destination d takes slot pi(d) = g d + (g - 1) / 2 mod N
 #pragma unroll 4
     for (uint32_t d = threadIdx.x; d < W::N; d += W::T) {
-      const uint32_t k = (gal * d + cg) & (W::N - 1), k2 = k % W::N2, k1 = k / W::N2;
-      o_buf.put(to_u64(xs[W::at(bit_reverse(k2, W::LOG2), W::col_of(k1))]), d * 8, 0);
+      const uint32_t k = G::slot(gal, d);
+      o_buf.put(to_u64(xs[G::word(G::pos_fwd(k % W::N2), k)]), G::dest(d), 0);
     }
-    if (l + 1 < l1) __syncthreads();
+    if (l + 1 < un.last) __syncthreads();
   }
 }
 #undef FIONA_WHOLE_KERNEL

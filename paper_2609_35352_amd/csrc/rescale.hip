@@ -117,15 +117,14 @@ void rescaler_place(fiona_rescaler *R, const TableImage &img, void *dev) {
 void launch_whole(const fiona_rescaler *R, const uint64_t *in_cts, uint32_t V, uint64_t *out_cts, hipStream_t stream) {
   const uint32_t L = R->L;
   const size_t in_words = (size_t)V * L * R->N, out_words = (size_t)V * (L - 1) * R->N;
-  if (launch_recorder()) {   // every word of the input and of the output, once; every set's tables
-    record_span("whole rescale: in_cts", in_cts, 0, in_words * 8);
-    record_span("whole rescale: out_cts", out_cts, 0, out_words * 8);
-    record_span("whole rescale: sets", R->sets, 0, L * sizeof(NttSet));
-    return;
-  }
   for_log_n<kWholeMax>(R->log_n1 + R->log_n2, [&](auto ln) {
     constexpr uint32_t LN = decltype(ln)::value;
     const uint32_t groups = fiona::whole_groups<LN>(V, L - 1);
+    if (LaunchRecord *rec = launch_recorder()) {
+      rec->whole.push_back(WholeLaunch{WholeLaunch::kRescale, LN, V, L - 1, groups, in_cts, nullptr, out_cts,
+                                       in_cts + in_words, nullptr, out_cts + out_words, R->sets + (L - 1), R->sets, {}});
+      return;
+    }
     hipLaunchKernelGGL(fiona::whole_rescale_kernel<LN>, dim3(V * groups), dim3(fiona::Whole<LN>::T),
                        fiona::whole_smem<LN>(), stream, in_cts, out_cts, R->sets, L, groups,
                        (const void *)(in_cts + in_words), (const void *)(out_cts + out_words));

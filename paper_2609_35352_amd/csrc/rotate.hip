@@ -463,15 +463,14 @@ constexpr uint64_t kC0NaturalWords = 1u << 17;
 // Digits: reads c1, writes every digit's transforms.
 void launch_whole_digits(const fiona_rotator *R, const uint64_t *ct, hipStream_t stream) {
   const uint32_t N = R->N, L = R->L;
-  if (launch_recorder()) {
-    record_span("whole digits: c1", ct, (uint64_t)L * N * 8, (uint64_t)2 * L * N * 8);
-    record_span("whole digits: Dhat", R->Dhat, 0, (uint64_t)L * (L + 1) * N * 8);
-    record_span("whole digits: sets", R->inv_sets, 0, (2 * L + 1) * sizeof(NttSet));
-    return;
-  }
   for_log_n<kDigitsMax>(R->log_n1 + R->log_n2, [&](auto ln) {
     constexpr uint32_t LN = decltype(ln)::value;
     const uint32_t groups = fiona::whole_groups<LN>(L, L + 1);
+    if (LaunchRecord *rec = launch_recorder()) {
+      rec->whole.push_back(WholeLaunch{WholeLaunch::kDigits, LN, L, L + 1, groups, ct + (size_t)L * N, nullptr, R->Dhat,
+                                       ct + (size_t)2 * L * N, nullptr, R->Dhat_end, R->inv_sets, R->fwd_sets, {}});
+      return;
+    }
     hipLaunchKernelGGL(fiona::whole_digits_kernel<LN>, dim3(L * groups), dim3(fiona::Whole<LN>::T),
                        fiona::whole_smem<LN>(), stream, ct + (size_t)L * N, R->Dhat, R->inv_sets, R->fwd_sets, L,
                        groups, (const void *)(ct + (size_t)2 * L * N), R->Dhat_end);
@@ -481,16 +480,14 @@ void launch_whole_digits(const fiona_rotator *R, const uint64_t *ct, hipStream_t
 void launch_whole_divide(const fiona_rotator *R, const uint64_t *ct, uint64_t *out, uint32_t V, const fiona::RotArgs &G,
                          hipStream_t stream) {
   const uint32_t N = R->N, L = R->L;
-  if (launch_recorder()) {
-    record_span("whole division: U", R->U, 0, (uint64_t)V * (L + 1) * N * 8);
-    record_span("whole division: c0", ct, 0, (uint64_t)L * N * 8);
-    record_span("whole division: out_cts", out, 0, (uint64_t)V * L * N * 8);
-    record_span("whole division: sets", R->down_sets, 0, (L + 1) * sizeof(NttSet));
-    return;
-  }
   for_log_n<kDivideMax>(R->log_n1 + R->log_n2, [&](auto ln) {
     constexpr uint32_t LN = decltype(ln)::value;
     const uint32_t groups = fiona::whole_groups<LN>(V, L);
+    if (LaunchRecord *rec = launch_recorder()) {
+      rec->whole.push_back(WholeLaunch{WholeLaunch::kDivide, LN, V, L, groups, R->U, ct, out, R->U_end,
+                                       ct + (size_t)2 * L * N, out + (size_t)V * L * N, R->p_inv_set, R->down_sets, G});
+      return;
+    }
     hipLaunchKernelGGL(fiona::whole_divide_kernel<LN>, dim3(V * groups), dim3(fiona::Whole<LN>::T),
                        fiona::whole_smem<LN>(), stream, R->U, ct, out, R->p_inv_set, R->down_sets, groups, R->U_end,
                        (const void *)(ct + (size_t)2 * L * N), (const void *)(out + (size_t)V * L * N), G);
