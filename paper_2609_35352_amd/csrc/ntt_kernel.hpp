@@ -35,8 +35,8 @@
 // then b w - k q = (h - k q) + l exactly.  The tables hold centred twiddles,
 // |w| <= q/2: then for |b| < 2^52 the quotient stays below 2^51 and the result
 // r satisfies r = b w (mod q) and |r| <= q (1/2 + |b| 2^-54).  Values between
-// stages are signed and lazily reduced (BoundsDft checks every bound at
-// compile time); reduce() brings any |x| < 2^53 to |x| <= q/2 + 1, and any
+// stages are signed and lazily reduced (BoundsTransform checks every bound at
+// compile time, of the passes' groups of stages and of the whole transforms'); reduce() brings any |x| < 2^53 to |x| <= q/2 + 1, and any
 // |x| < 2^52 to the exact centred residue, |x| <= (q-1)/2 (the FMA's error
 // |x/q| 2^-53 is then below 1/(2q), the distance from x/q to the nearest
 // half-integer).
@@ -166,7 +166,7 @@ __host__ __device__ constexpr uint32_t padded_len(uint32_t m) { return m + m / 1
 // tw_at(t) returns w_M^t.  Nothing is reduced here but, in the first group
 // (S0 = 0), the even words after its second stage: the butterflies with the
 // twiddle 1 add their input unmultiplied, so those words double in both
-// stages, while a product's output is back near q/2.  BoundsDft follows every
+// stages, while a product's output is back near q/2.  BoundsTransform follows every
 // word's bound through this schedule.  Reducing every word after every second
 // stage instead took 8 reductions a word and transform pair, now 3.  That alone
 // left the large rescales as they were (1.07 ms at N = 2^16, L = 8, 128
@@ -217,14 +217,16 @@ __device__ __forceinline__ void tree_butterflies(double (&r)[1u << R], uint32_t 
   }
 }
 
-// Bounds of the words through a size-2^LOGM DFT whose input is at most `in`,
-// in units of 2^50 (every q is below one unit), for the schedule of
-// butterflies, first_stages, middle_stages and last_stages: a product's input
-// must stay below 4 units and every word below 8 (exact integers in a double).
+// Bounds of the words through a transform of `stages` stages, the first `first`
+// of them in a thread's first group, whose input is at most `in`, in units of
+// 2^50 (every q is below one unit): a product's input must stay below 4 units
+// and every word below 8 (exact integers in a double).  tree: the negacyclic
+// transform (tree_butterflies), else the DFT (butterflies).  Both kinds reduce
+// every word after the first group (put_first, tree_first, and the same in
+// ntt_whole.hpp).
 constexpr double kUnitReduced = 0.5 + 0x1p-40;   // after reduce(): at most q/2 + 1
 constexpr double product_bound(double b) { return 0.5 + b / 16; }
-template <uint32_t LOGM>
-struct BoundsDft {
+struct BoundsTransform {
   bool ok = true;
   double out = 0;   // the last group's output
   constexpr double product(double b) {
@@ -235,37 +237,37 @@ struct BoundsDft {
     if (x >= 8) ok = false;
     return x;
   }
-  constexpr explicit BoundsDft(double in) {
+  constexpr BoundsTransform(uint32_t stages, uint32_t first, double in, bool tree) {
     double r[16] = {};
     for (int u = 0; u < 16; ++u) r[u] = in;
-    for (int st = 0; st < 4; ++st) {   // the first group
+    for (int st = 0; st < (int)first; ++st) {   // the first group
       const int hh = 1 << st;
-      for (int u = 0; u < 16; ++u) {
+      for (int u = 0; u < 1 << first; ++u) {
         if ((u & (2 * hh - 1)) >= hh) continue;
-        const double t = (u & (hh - 1)) == 0 ? r[u + hh] : product(r[u + hh]);
+        const double t = !tree && (u & (hh - 1)) == 0 ? r[u + hh] : product(r[u + hh]);
         const double x = word(r[u] + t);
         r[u] = x;
         r[u + hh] = x;
       }
-      if (st == 1)
+      if (!tree && st == 1 && first > 2)
         for (int u = 0; u < 16; u += 2) r[u] = kUnitReduced;
     }
-    out = kUnitReduced;   // put_first reduces every word
-    for (uint32_t st = 4; st < LOGM; ++st) out = word(out + product(out));
+    out = kUnitReduced;
+    for (uint32_t st = first; st < stages; ++st) out = word(out + product(out));
   }
 };
-// The DFT's output, and the negacyclic transform's (four stages from an
-// integer below 2^50, a reduction, then the rest like the DFT's).
-template <uint32_t LOGM>
-constexpr double dft_out() {
-  // inputs: residues, or pass A's products by mid, whose quotient takes w / q
-  // as w fl(1/q), twice the rounding error: 1/2 + b/8 of an input b below 4
-  constexpr BoundsDft<LOGM> b(1.0);
-  static_assert(b.ok && b.out < 4, "the products after the last stage (mid, post) take their input below 4 units");
-  double x = 1;   // tree_butterflies' first group
-  for (int st = 0; st < 4; ++st) x += product_bound(x);
-  return x < 4 ? b.out : 8;
+// The output of a transform of 2^stages words.  Inputs: residues, or pass A's
+// products by mid, whose quotient takes w / q as w fl(1/q), twice the rounding
+// error: 1/2 + b/8 of an input b below 4; forward, integers below 2^50.
+template <uint32_t STAGES, uint32_t FIRST>
+constexpr double transform_out() {
+  constexpr BoundsTransform b(STAGES, FIRST, 1.0, false), t(STAGES, FIRST, 1.0, true);
+  static_assert(b.ok && t.ok, "a product's input or a word passes its bound");
+  static_assert(b.out < 4 && t.out < 4, "the products after the last stage (mid, post) take their input below 4 units");
+  return b.out > t.out ? b.out : t.out;
 }
+template <uint32_t LOGM>
+constexpr double dft_out() { return transform_out<LOGM, 4>(); }   // the passes': first groups of 16
 
 // How a size-M DFT (16 <= M <= kNttMaxSide) splits over a workgroup's
 // kNttCols columns.  The first four stages run on groups of 16 words that a
@@ -378,12 +380,15 @@ __device__ __forceinline__ void last_stages(const double *xs, uint32_t col, uint
   butterflies<LOGM, D::S0L, D::R2>(r, o, [&](uint32_t t) { return tw[t]; }, q, qinv);
 }
 
-// b - y for a residue b and a DFT output y, small enough for a product.
-template <uint32_t LOGM>
+// b - y for a residue b and a transform's output y, small enough for a product:
+// REDUCE, where y's bound does not leave room for b.
+template <bool REDUCE>
 __device__ __forceinline__ double minuend(uint64_t b, double y, double q, double qinv) {
-  if constexpr (dft_out<LOGM>() + 1 >= 4) y = reduce(y, q, qinv);
+  if constexpr (REDUCE) y = reduce(y, q, qinv);
   return to_f64(b) - y;
 }
+template <uint32_t LOGM>
+constexpr bool reduce_minuend() { return dft_out<LOGM>() + 1 >= 4; }
 
 // Copy n twiddles into LDS.
 __device__ __forceinline__ void stage_twiddles(Tw *dst, const Tw *__restrict__ src, uint32_t n) {
@@ -801,7 +806,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b(const NttPass P) {
 #pragma unroll
       for (uint32_t u = 0; u < D::E2; ++u) {
         const Off oc = G::col(k2, o, u, N2);
-        const double z = mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q);
+        const double z = mul_tw(minuend<reduce_minuend<LOGM>()>(bv[u], y[u], q, qinv), S.inv, q);
         out.put(to_u64(canonical(z, q, qinv)), oc.v, oc.s);
       }
     } else {

@@ -36,7 +36,8 @@ template <uint32_t LOGM>
 struct Side {
   static constexpr uint32_t M = 1u << LOGM, R1 = LOGM == 4 ? 2 : LOGM == 7 ? 4 : 3, R2 = LOGM - R1;
   static constexpr uint32_t E1 = 1u << R1, E2 = 1u << R2;   // words of a first and a last group
-  static_assert(LOGM >= 4 && LOGM <= 7 && R1 <= 4 && R2 <= 4, "the bounds of dft_out hold for up to four stages");
+  static_assert(LOGM >= 4 && LOGM <= 7 && R1 <= 4 && R2 <= 4, "groups of up to 16 words");
+  static constexpr double kOut = transform_out<LOGM, R1>();   // the outputs' bound
   static __host__ __device__ constexpr uint32_t rev1(uint32_t u) { return rev4(u) >> (4 - R1); }
   static __host__ __device__ constexpr uint32_t rev2(uint32_t u) { return rev4(u) >> (4 - R2); }
 };
@@ -316,7 +317,7 @@ whole_rescale_kernel(const uint64_t *in, uint64_t *out, const NttSet *sets, uint
 #pragma unroll
       for (uint32_t u = 0; u < W::B::E2; ++u) {
         const Off on = G::natural(k2, o, u);
-        const double z = mul_tw(minuend<W::LOG1>(b[u], y[u], q, qinv), S.inv, q);
+        const double z = mul_tw(minuend<(W::B::kOut + 1 >= 4)>(b[u], y[u], q, qinv), S.inv, q);
         o_buf.put(to_u64(canonical(z, q, qinv)), on.v, on.s);
       }
     }
@@ -403,7 +404,7 @@ whole_divide_kernel(const uint64_t *u_in, const uint64_t *c0, uint64_t *out, con
       whole_last<LN>(xs, pos, o, tw_b, y, S);
 #pragma unroll
       for (uint32_t u = 0; u < W::B::E2; ++u) {
-        double z = canonical(mul_tw(minuend<W::LOG1>(b[u], y[u], q, qinv), S.inv, q), q, qinv);
+        double z = canonical(mul_tw(minuend<(W::B::kOut + 1 >= 4)>(b[u], y[u], q, qinv), S.inv, q), q, qinv);
         if (p == 0) {
           z += to_f64(a[u]);
           z = z >= q ? z - q : z;

@@ -212,7 +212,7 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_b_rot(const NttPass P, c
     last_stages<LOGM>(xs, cc, o, tw, y, q, qinv);
 #pragma unroll
     for (uint32_t u = 0; u < D::E2; ++u)
-      y[u] = canonical(mul_tw(minuend<LOGM>(bv[u], y[u], q, qinv), S.inv, q), q, qinv);
+      y[u] = canonical(mul_tw(minuend<reduce_minuend<LOGM>()>(bv[u], y[u], q, qinv), S.inv, q), q, qinv);
     if (p == 0) {
       uint64_t av[D::E2];
 #pragma unroll
