@@ -238,15 +238,6 @@ bool pass_b_rot(Checker &C, const PassLaunch &L) {
   return true;
 }
 
-template <uint32_t LOGM>
-bool replay_one(Checker &C, const PassLaunch &L) {
-  switch (L.kind) {
-    case PassLaunch::kPassA: return pass_a<LOGM>(C, L);
-    case PassLaunch::kPassB: return pass_b<LOGM>(C, L);
-    default: return pass_b_rot<LOGM>(C, L);
-  }
-}
-
 // A set of N words, each to be met once.
 struct Once {
   std::vector<uint8_t> seen;
@@ -394,15 +385,14 @@ std::string check_launches(const LaunchRecord &rec, const std::vector<Region> &r
       return C.err;
     }
     bool ok = false;
-    switch (L.log_side) {
-      case 4: ok = replay_one<4>(C, L); break;
-      case 5: ok = replay_one<5>(C, L); break;
-      case 6: ok = replay_one<6>(C, L); break;
-      case 7: ok = replay_one<7>(C, L); break;
-      case 8: ok = replay_one<8>(C, L); break;
-      case 9: ok = replay_one<9>(C, L); break;
-      default: C.fail("DFT side outside 2^4 .. 2^9"); break;
-    }
+    if (L.kind == PassLaunch::kPassA)
+      for_log_n<kSideMaxA, kSideMinA>(L.log_side, [&](auto ls) { ok = pass_a<decltype(ls)::value>(C, L); });
+    else
+      for_log_n<kSideMaxB, kSideMinB>(L.log_side, [&](auto ls) {
+        constexpr uint32_t LOG = decltype(ls)::value;
+        ok = L.kind == PassLaunch::kPassB ? pass_b<LOG>(C, L) : pass_b_rot<LOG>(C, L);
+      });
+    if (!ok && C.err.empty()) C.fail("DFT side of no kernel");
     if (!ok) return C.err;
     ++C.launch;
   }

@@ -258,17 +258,19 @@ inline bool allow_lds(const void *kernel, size_t bytes) {
 // Whether a pass B ends an inverse transform.
 inline bool inverse_b(const NttPass &P) { return P.store == fiona::kStoreF64 || P.store == fiona::kStoreF64C; }
 
-// The passes are instantiated per DFT side 2^4 .. 2^9.
+// The passes run from N = 2^13 on (smaller rings go as whole transforms): pass A
+// over sides N2 = 2^6 .. 2^8, pass B over N1 = 2^7 .. 2^9.
+constexpr uint32_t kPassMinLogN = 13, kSideMinA = 6, kSideMaxA = 8, kSideMinB = 7, kSideMaxB = 9;
+
 template <uint32_t LOG>
-auto *pass_kernel(bool a, const NttPass &P) {
-  if (a && P.load == fiona::kLoadF64) return P.nt ? fiona::ntt_pass_a<LOG, true, true> : fiona::ntt_pass_a<LOG, true, false>;
-  if (a) return P.nt ? fiona::ntt_pass_a<LOG, false, true> : fiona::ntt_pass_a<LOG, false, false>;
-  if (inverse_b(P)) return P.nt ? fiona::ntt_pass_b<LOG, true, true> : fiona::ntt_pass_b<LOG, true, false>;
-  return fiona::ntt_pass_b<LOG, false, false>;   // stores no doubles
+auto *pass_a_kernel(const NttPass &P) {
+  if (P.load == fiona::kLoadF64) return P.nt ? fiona::ntt_pass_a<LOG, true, true> : fiona::ntt_pass_a<LOG, true, false>;
+  return P.nt ? fiona::ntt_pass_a<LOG, false, true> : fiona::ntt_pass_a<LOG, false, false>;
 }
 template <uint32_t LOG>
-void launch_one(bool a, dim3 grid, size_t smem, hipStream_t stream, const NttPass &P) {
-  hipLaunchKernelGGL(pass_kernel<LOG>(a, P), grid, dim3(fiona::kNttThreads), smem, stream, P);
+auto *pass_b_kernel(const NttPass &P) {
+  if (inverse_b(P)) return P.nt ? fiona::ntt_pass_b<LOG, true, true> : fiona::ntt_pass_b<LOG, true, false>;
+  return fiona::ntt_pass_b<LOG, false, false>;   // stores no doubles
 }
 
 // LDS of a pass of side M: the columns and at most M twiddles.
@@ -318,14 +320,13 @@ inline void launch_pass(bool a, uint32_t log_side, uint32_t log_other, uint32_t 
   }
   const dim3 grid((1u << log_other) / fiona::kNttCols, V);
   const size_t smem = pass_smem(1u << log_side);
-  switch (log_side) {
-    case 4: launch_one<4>(a, grid, smem, stream, P); break;
-    case 5: launch_one<5>(a, grid, smem, stream, P); break;
-    case 6: launch_one<6>(a, grid, smem, stream, P); break;
-    case 7: launch_one<7>(a, grid, smem, stream, P); break;
-    case 8: launch_one<8>(a, grid, smem, stream, P); break;
-    default: launch_one<9>(a, grid, smem, stream, P); break;
-  }
+  const dim3 block(fiona::kNttThreads);
+  if (a)
+    for_log_n<kSideMaxA, kSideMinA>(
+        log_side, [&](auto ls) { hipLaunchKernelGGL(pass_a_kernel<decltype(ls)::value>(P), grid, block, smem, stream, P); });
+  else
+    for_log_n<kSideMaxB, kSideMinB>(
+        log_side, [&](auto ls) { hipLaunchKernelGGL(pass_b_kernel<decltype(ls)::value>(P), grid, block, smem, stream, P); });
 }
 
 // Both passes of one transform.
@@ -334,24 +335,14 @@ inline void launch_transform(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipSt
   launch_pass(false, log_n1, log_n2, V, stream, P);
 }
 
-template <uint32_t LOG>
-bool allow_smem_one(size_t bytes) {
-  NttPass P{};
-  for (uint32_t nt = 0; nt < 2; ++nt)
-    for (uint32_t k = 0; k < 4; ++k) {
-      P.nt = nt;
-      P.load = k & 1 ? fiona::kLoadF64 : fiona::kLoadU64;
-      P.store = k & 1 ? fiona::kStoreRescale : fiona::kStoreF64;
-      if (!allow_lds((const void *)pass_kernel<LOG>(k < 2, P), bytes)) return false;
-    }
-  return true;
-}
-
-// Lets every pass use the LDS of its largest side.
+// Lets pass B over its largest side use its LDS (the other passes' fits the
+// default of 64 KiB).
+static_assert(pass_smem(1u << kSideMaxA) <= 64 * 1024 && pass_smem(1u << (kSideMaxB - 1)) <= 64 * 1024, "allow_smem");
 inline bool allow_smem() {
-  const size_t smem = pass_smem(fiona::kNttMaxSide);
-  return allow_smem_one<4>(smem) && allow_smem_one<5>(smem) && allow_smem_one<6>(smem) &&
-         allow_smem_one<7>(smem) && allow_smem_one<8>(smem) && allow_smem_one<9>(smem);
+  constexpr size_t smem = pass_smem(1u << kSideMaxB);
+  return allow_lds((const void *)fiona::ntt_pass_b<kSideMaxB, true, true>, smem) &&
+         allow_lds((const void *)fiona::ntt_pass_b<kSideMaxB, true, false>, smem) &&
+         allow_lds((const void *)fiona::ntt_pass_b<kSideMaxB, false, false>, smem);
 }
 
 }  // namespace fiona_host

@@ -50,7 +50,6 @@ namespace fiona {
 
 constexpr uint32_t kNttCols = 16;      // columns (pass A) or rows (pass B) per workgroup
 constexpr uint32_t kNttThreads = 256;
-constexpr uint32_t kNttMaxSide = 512;  // N1, N2 <= 512: N <= 2^17
 
 struct Tw {   // a twiddle w, an integer with |w| <= q/2, and fl(w / q)
   double w, wq;
@@ -269,7 +268,7 @@ constexpr double transform_out() {
 template <uint32_t LOGM>
 constexpr double dft_out() { return transform_out<LOGM, 4>(); }   // the passes': first groups of 16
 
-// How a size-M DFT (16 <= M <= kNttMaxSide) splits over a workgroup's
+// How a size-M DFT (M = 64 .. 512: kSideMinA .. kSideMaxB in ntt_host.hpp) splits over a workgroup's
 // kNttCols columns.  The first four stages run on groups of 16 words that a
 // thread loads straight from global memory (natural index i' + I1 v,
 // v < 16: position 16 i + bitrev4(v) of the bit-reversed input order,
@@ -305,7 +304,7 @@ template <uint32_t LOGM>
 __device__ __forceinline__ void put_first(double *xs, uint32_t col, uint32_t ip, const double (&r)[16], double q,
                                           double qinv) {
   using D = DftShape<LOGM>;
-  const uint32_t i = LOGM > 4 ? bit_reverse(ip, LOGM - 4) : 0u;   // (M = 16: one group, i' = 0)
+  const uint32_t i = bit_reverse(ip, LOGM - 4);
 #pragma unroll
   for (uint32_t u = 0; u < 16; ++u) xs[col * D::PM + pidx(16 * i + u)] = reduce(r[u], q, qinv);
 }
@@ -331,24 +330,6 @@ __device__ __forceinline__ void tree_last(const double *xs, uint32_t col, uint32
 #pragma unroll
   for (uint32_t e = 0; e < D::E2; ++e) r[e] = xs[col * D::PM + pidx(j * D::E2 + e)];
   tree_butterflies<D::S0L, D::R2>(r, j, [&](uint32_t t) { return tw[t]; }, q);
-}
-
-// Its middle stage (M = 512: distance 16 inside each block of 32); barriers on both sides.
-template <uint32_t LOGM>
-__device__ __forceinline__ void tree_middle(double *xs, const Tw *tw, double q) {
-  using D = DftShape<LOGM>;
-  __syncthreads();
-  if constexpr (D::S0L > 4) {
-    static_assert(D::S0L == 5, "one middle stage at most");
-    for (uint32_t it = threadIdx.x; it < kNttCols * D::M / 2; it += kNttThreads) {
-      const uint32_t col = it % kNttCols, gi = it / kNttCols, v = gi >> 4, p = v * 32 + (gi & 15u);
-      double r[2] = {xs[col * D::PM + pidx(p)], xs[col * D::PM + pidx(p + 16)]};
-      tree_butterflies<4, 1>(r, v, [&](uint32_t t) { return tw[t]; }, q);
-      xs[col * D::PM + pidx(p)] = r[0];
-      xs[col * D::PM + pidx(p + 16)] = r[1];
-    }
-    __syncthreads();
-  }
 }
 
 // Between the first and the last groups: the middle stages in LDS (M = 512),
@@ -694,8 +675,8 @@ __global__ void __launch_bounds__(kNttThreads) ntt_pass_a(const NttPass P) {
     }
   };
   load_mid(threadIdx.x);   // in flight over the barrier and the last stages
-  if constexpr (FWD) tree_middle<LOGM>(xs, tw, q);
-  else middle_stages<LOGM>(xs, tw, q, qinv);
+  static_assert(D::S0L == 4, "the last groups follow the first");
+  __syncthreads();
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < D::IT2; it += kNttThreads) {
     const uint32_t cl = G::col2(it), o = G::off2(it), n1 = cb * kNttCols + cl;

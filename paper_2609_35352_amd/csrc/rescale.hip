@@ -50,6 +50,7 @@ namespace {
 // transforms on (L = 6, 16 ciphertexts, 160 of them: 32.5 us in passes, 31.9
 // whole; 128 ciphertexts 186 and 116; but 4, 40 of them, 21.2 and 28.9).
 constexpr uint32_t kWholeAlways = 13, kWholeMax = 14, kWholeTransforms = 160;
+static_assert(kWholeAlways + 1 >= kPassMinLogN, "no passes are built for smaller rings");
 bool use_whole(const fiona_rescaler *R, uint32_t V) {
   const uint32_t log_n = R->log_n1 + R->log_n2;
   return log_n <= kWholeAlways || (log_n <= kWholeMax && (uint64_t)V * (R->L - 1) >= kWholeTransforms);

@@ -325,11 +325,6 @@ size_t tmp_vectors(const fiona_rotator *R) {
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 
-template <uint32_t LOG>
-void launch_rot_b(dim3 grid, size_t smem, hipStream_t stream, const NttPass &P, const fiona::RotArgs &G) {
-  hipLaunchKernelGGL(fiona::ntt_pass_b_rot<LOG>, grid, dim3(fiona::kNttThreads), smem, stream, P, G);
-}
-
 // The fused pass B over V vectors: grid (N2 / 16 destination blocks, V).
 void launch_rot_pass_b(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipStream_t stream, const NttPass &P,
                        const fiona::RotArgs &G) {
@@ -339,25 +334,9 @@ void launch_rot_pass_b(uint32_t log_n1, uint32_t log_n2, uint32_t V, hipStream_t
   }
   const dim3 grid((1u << log_n2) / fiona::kNttCols, V);
   const size_t smem = pass_smem(1u << log_n1);
-  switch (log_n1) {
-    case 4: launch_rot_b<4>(grid, smem, stream, P, G); break;
-    case 5: launch_rot_b<5>(grid, smem, stream, P, G); break;
-    case 6: launch_rot_b<6>(grid, smem, stream, P, G); break;
-    case 7: launch_rot_b<7>(grid, smem, stream, P, G); break;
-    case 8: launch_rot_b<8>(grid, smem, stream, P, G); break;
-    default: launch_rot_b<9>(grid, smem, stream, P, G); break;
-  }
-}
-
-template <uint32_t LOG>
-bool allow_rot_one(int bytes) {
-  return hipFuncSetAttribute((const void *)fiona::ntt_pass_b_rot<LOG>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             bytes) == hipSuccess;
-}
-
-bool allow_rot_smem(int bytes) {
-  return allow_rot_one<4>(bytes) && allow_rot_one<5>(bytes) && allow_rot_one<6>(bytes) &&
-         allow_rot_one<7>(bytes) && allow_rot_one<8>(bytes) && allow_rot_one<9>(bytes);
+  for_log_n<kSideMaxB, kSideMinB>(log_n1, [&](auto ls) {
+    hipLaunchKernelGGL(fiona::ntt_pass_b_rot<decltype(ls)::value>, grid, dim3(fiona::kNttThreads), smem, stream, P, G);
+  });
 }
 
 bool overlap(const void *a, size_t na, const void *b, size_t nb) {
@@ -447,6 +426,7 @@ void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
 // from 256 forward transforms on (L = 6, 64 rotations, 768 of them: 170 us in
 // passes, 158 whole; 4 rotations, 48 of them, 45.3 and 49.5).
 constexpr uint32_t kDigitsMax = 12, kDivideAlways = 12, kDivideMax = 13, kDivideTransforms = 256;
+static_assert(kDigitsMax + 1 >= kPassMinLogN && kDivideAlways + 1 >= kPassMinLogN, "no passes are built for smaller rings");
 bool whole_digits(const fiona_rotator *R) { return R->log_n1 + R->log_n2 <= kDigitsMax; }
 bool whole_divide(const fiona_rotator *R, uint32_t V) {
   const uint32_t log_n = R->log_n1 + R->log_n2;
@@ -739,9 +719,8 @@ int fiona_rotator_create(const fiona_ctx *ctx, uint64_t special_prime, const uin
       return FIONA_ERR_HIP;
     }
     // (the inner product's limit is every rotator's: a call's rounds, so its LDS, follow its own n_rot and L)
-    const int nt_smem = (int)pass_smem(fiona::kNttMaxSide);
     if (!allow_lds((const void *)fiona::whole_divide_kernel<13>, fiona::whole_smem<13>()) ||
-        !allow_smem() || !allow_rot_smem(nt_smem) ||
+        !allow_smem() || !allow_lds((const void *)fiona::ntt_pass_b_rot<kSideMaxB>, pass_smem(1u << kSideMaxB)) ||
         !allow_lds((const void *)fiona::ks_inner_kernel<8>, fiona::kKsLdsMax) ||
         !allow_lds((const void *)fiona::ks_inner_kernel<4>, fiona::kKsLdsMax)) {
       fiona_rotator_destroy(R);

@@ -1,7 +1,8 @@
-"""GPU parity of the NTT passes at every side they are built for: rescales and
-rotations at N = 2^8 .. 2^17 (both splits, even and odd log N), with uniform
-residues, residues at the ends of their range and moduli of very different
-sizes, bit-exact against the oracle's integer arithmetic."""
+"""GPU parity of the NTT kernels at every size they are built for: rescales and
+rotations at N = 2^8 .. 2^17 (whole transforms up to 2^14, passes from 2^13 on;
+both splits, even and odd log N), with uniform residues, residues at the ends of
+their range and moduli of very different sizes, bit-exact against the oracle's
+integer arithmetic."""
 import sys
 
 import numpy as np
@@ -165,12 +166,13 @@ def test_rescale_chunks(dev, n_ct):
         assert np.array_equal(_np(out[c]), rs.rescale(_np(cts[c]), moduli)), "ciphertext %d differs" % c
 
 
-@pytest.mark.parametrize("n_ct", [3, 4, 30, 31])
-def test_rescale_store_policy_edges(dev, n_ct):
-    """Intermediates of just under 4 MiB and just over 32 (stores of the default policy), and just within (nontemporal)."""
+@pytest.mark.parametrize("log_n,n_ct", [(15, 3), (15, 4), (15, 30), (15, 31), (14, 12), (16, 6), (17, 3)])
+def test_rescale_store_policies(dev, log_n, n_ct):
+    """Intermediates of just under 4 MiB and just over 32 (stores of the default policy), just within
+    (nontemporal), and within at every pair of sides."""
     import torch
-    N, L = 1 << 15, 3
-    _say("[ntt sizes] rescale store policy n_ct=%d" % n_ct)
+    N, L = 1 << log_n, 3
+    _say("[ntt sizes] rescale store policy N=2^%d n_ct=%d" % (log_n, n_ct))
     moduli = _moduli(N, False)
     cts = _residues(moduli, (n_ct, 2, L, N), n_ct, dev)
     out = torch.full((n_ct, 2, L - 1, N), -1, dtype=torch.int64, device=dev)
