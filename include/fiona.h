@@ -360,10 +360,11 @@ int fiona_rescale(const fiona_rescaler *rescaler, const uint64_t *in_cts, uint32
  * as for the rescaler, for every modulus including P.
  *
  * fiona_rotator_create: NTT tables of q_0 .. q_{L-1} and P, and a workspace
- * for up to max_rot rotations per call (max_rot <= 256; about
- * 8 N (2 L (L + 1) + 2 L + max_rot (4 L + 4)) bytes and 1 + 16 / sqrt(N) times
- * the NTT intermediates' share of it, at most: the division by P has
- * intermediates of at most 416 MiB, a call with more takes it in chunks).
+ * for up to max_rot rotations per call (max_rot <= 256): about
+ * 8 N (L + 1) (L + 2 max_rot) bytes, and from N = 2^13 on
+ * 8 N (2 L + c + (1 + 16 / sqrt(N)) L max(L + 1, c)) more, c = 2 max_rot or the
+ * vectors whose L intermediates fill 416 MiB if those are fewer (a call over
+ * more divides by P in chunks).
  *   special_prime  P with 2^20 < P < 2^50, P = 1 mod 2N, unequal to every q_l
  *   psi            host [L + 1] roots (the data moduli, then P) or NULL for
  *                  the defaults of fiona_rescaler_create

@@ -297,6 +297,23 @@ struct fiona_rotator {
 
 namespace {
 
+// Which steps of a call go as launches of whole transforms (ntt_whole.hpp).
+// The digits up to N = 2^12 (one rotation at 2^12, L = 6: 42.6 us in passes,
+// 34.5 whole; at 2^13 within 3% of each other, 7 rotations at L = 4 44.8 and
+// 46.3; at 2^14 51.6 and 61.1: a workgroup's chain of two transforms).  The
+// division by P up to N = 2^12, and at 2^13 from 256 forward transforms on (L =
+// 6, 64 rotations, 768 of them: 170 us in passes, 158 whole; 4 rotations, 48 of
+// them, 45.3 and 49.5).
+constexpr uint32_t kDigitsMax = 12, kDivideAlways = 12, kDivideMax = 13, kDivideTransforms = 256;
+static_assert(kDigitsMax + 1 >= kPassMinLogN && kDivideAlways + 1 >= kPassMinLogN, "no passes are built for smaller rings");
+bool whole_digits(const fiona_rotator *R) { return R->log_n1 + R->log_n2 <= kDigitsMax; }
+bool whole_divide(const fiona_rotator *R, uint32_t V) {
+  const uint32_t log_n = R->log_n1 + R->log_n2;
+  return log_n <= kDivideAlways || (log_n <= kDivideMax && V * R->L >= kDivideTransforms);
+}
+// Whether a call may run passes at all: rings without need no workspace for them.
+bool any_passes(const fiona_rotator *R) { return R->log_n1 + R->log_n2 > std::min(kDigitsMax, kDivideAlways); }
+
 // Bytes of one intermediate.
 size_t tmp_vec_bytes(const fiona_rotator *R) {
   return fiona::tmp_words(1u << R->log_n1, 1u << R->log_n2) * sizeof(double);
@@ -319,8 +336,14 @@ uint32_t divide_chunk_max(const fiona_rotator *R) {
   const size_t fit = kTmpBytes / (R->L * tmp_vec_bytes(R)), all = (size_t)2 * R->max_rot;
   return (uint32_t)std::max<size_t>(1, std::min(fit, all));
 }
-size_t tmp_vectors(const fiona_rotator *R) {
-  return std::max((size_t)R->L * (R->L + 1), (size_t)R->L * divide_chunk_max(R));
+// The passes' workspace: vectors of D and c0t each, W and T (their intermediates).
+struct PassVectors {
+  size_t d, w, t;
+};
+PassVectors pass_vectors(const fiona_rotator *R) {
+  if (!any_passes(R)) return PassVectors{0, 0, 0};
+  const size_t L = R->L, chunk = divide_chunk_max(R);
+  return PassVectors{L, chunk, std::max(L * (L + 1), L * chunk)};
 }
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
@@ -385,9 +408,9 @@ int rotator_layout(const fiona_ctx *ctx, uint64_t special_prime, const uint64_t 
   img.add(make_tables(R->log_n1, R->log_n2, P, roots[L], true), P);
   const size_t vec = (size_t)N * 8;
   R->limb_bytes = round256((L + 1) * sizeof(fiona::LimbConst));
-  total = img.bytes() + R->limb_bytes + round256(L * vec) + round256((size_t)L * (L + 1) * vec) +
-          round256(L * vec) + round256(tmp_vectors(R) * tmp_vec_bytes(R)) +
-          round256(divide_chunk_max(R) * vec) +
+  const PassVectors pv = pass_vectors(R);
+  total = img.bytes() + R->limb_bytes + round256(pv.d * vec) + round256((size_t)L * (L + 1) * vec) +
+          round256(pv.d * vec) + round256(pv.t * tmp_vec_bytes(R)) + round256(pv.w * vec) +
           round256((size_t)max_rot * 2 * (L + 1) * vec);
   return FIONA_OK;
 }
@@ -411,26 +434,13 @@ void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
   };
   const void *limbs_end = nullptr;
   R->limbs = (const fiona::LimbConst *)take((L + 1) * sizeof(fiona::LimbConst), limbs_end);
-  R->D = (double *)take(L * vec, R->D_end);
+  const PassVectors pv = pass_vectors(R);
+  R->D = (double *)take(pv.d * vec, R->D_end);
   R->Dhat = (uint64_t *)take((size_t)L * (L + 1) * vec, R->Dhat_end);
-  R->c0t = (uint64_t *)take(L * vec, R->c0t_end);
-  R->T = (double *)take(tmp_vectors(R) * tmp_vec_bytes(R), R->T_end);
-  R->W = (double *)take(divide_chunk_max(R) * vec, R->W_end);
+  R->c0t = (uint64_t *)take(pv.d * vec, R->c0t_end);
+  R->T = (double *)take(pv.t * tmp_vec_bytes(R), R->T_end);
+  R->W = (double *)take(pv.w * vec, R->W_end);
   R->U = (uint64_t *)take((size_t)R->max_rot * 2 * (L + 1) * vec, R->U_end);
-}
-
-// Which steps of a call go as launches of whole transforms (ntt_whole.hpp).
-// The digits up to N = 2^12 (one rotation at 2^12, L = 6: 42.6 us in passes,
-// 34.5 whole; at 2^13 within 3% of each other, 7 rotations at L = 4 44.8 and
-// 46.3; at 2^14 51.6 and 61.1: a workgroup's chain of two transforms).  The division by P up to N = 2^12, and at 2^13
-// from 256 forward transforms on (L = 6, 64 rotations, 768 of them: 170 us in
-// passes, 158 whole; 4 rotations, 48 of them, 45.3 and 49.5).
-constexpr uint32_t kDigitsMax = 12, kDivideAlways = 12, kDivideMax = 13, kDivideTransforms = 256;
-static_assert(kDigitsMax + 1 >= kPassMinLogN && kDivideAlways + 1 >= kPassMinLogN, "no passes are built for smaller rings");
-bool whole_digits(const fiona_rotator *R) { return R->log_n1 + R->log_n2 <= kDigitsMax; }
-bool whole_divide(const fiona_rotator *R, uint32_t V) {
-  const uint32_t log_n = R->log_n1 + R->log_n2;
-  return log_n <= kDivideAlways || (log_n <= kDivideMax && V * R->L >= kDivideTransforms);
 }
 
 // The passes' division reads c0 in natural order, words sqrt(N) apart, while

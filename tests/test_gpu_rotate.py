@@ -235,6 +235,27 @@ def test_rotate_max_rotations():
         np.testing.assert_array_equal(got[r], orot.rotate(ct, galois[r], keys[r], moduli, P))
 
 
+@pytest.mark.parametrize("log_n", [12, 13])
+def test_rotator_workspace(log_n):
+    """The device memory of a rotator is what the header says: up to N = 2^12, where
+    every call goes as whole transforms, without the passes' share."""
+    _dev()
+    N, L, max_rot = 1 << log_n, 16, 256
+    moduli = synth.ntt_primes(N, L + 1)
+    ctx = fiona.Ctx(N, L, moduli[:L])
+    fiona.Rotator(ctx, moduli[L], 1)   # the library's kernels are loaded
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    rot = fiona.Rotator(ctx, moduli[L], max_rot)
+    used = before - torch.cuda.mem_get_info()[0]
+    want = 8 * N * (L + 1) * (L + 2 * max_rot) + (3 * L + 2) * (8 * N + (1 << 14))   # and the tables
+    if log_n >= 13:
+        vec = 8 * N + 128 * (1 << log_n // 2)
+        c = min(2 * max_rot, (416 << 20) // (L * vec))
+        want += 8 * N * (2 * L + c) + L * max(L + 1, c) * vec
+    assert rot.key_words() and abs(used - want) < (8 << 20), (used, want)
+
+
 @pytest.mark.parametrize("N,g", [(256, 5), (2048, 2 * 2048 - 1)])
 def test_rotation_key_layout_format(N, g):
     """The library's key layout word for word, as include/fiona.h documents
