@@ -203,7 +203,7 @@ typedef struct fiona_plan_stats_t {
                                       distinct sums plus the common terms themselves */
   uint32_t tile;                   /* coefficients per workgroup */
   uint32_t waves;                  /* wavefronts per workgroup */
-  uint32_t lds_bytes;              /* LDS per workgroup, without the word blocks that a small call packs there */
+  uint32_t lds_bytes;              /* LDS per workgroup */
   uint32_t grid;                   /* workgroups per launch */
   uint32_t split_outputs;          /* outputs split into segments over several wavefronts */
   uint32_t segment_slots;          /* LDS rows holding the segments' partial residues */

@@ -794,9 +794,14 @@ bool own_words(const fiona_plan *plan) {
   return packs * ((plan->grid + slots - 1) / slots) <= kOwnPacks;
 }
 
+// LDS of a workgroup.
+uint32_t launch_lds(const fiona_plan *plan) {
+  return plan->lds_bytes + (own_words(plan) ? own_words_bytes(plan) : 0);
+}
+
 // The launches of one call: the sign-packing kernel writes this call's word
 // blocks at words (plan->blocks.size() blocks of kSumWords words), then the
-// main kernel reads them.
+// main kernel reads them; or the main kernel packs them itself (own_words).
 int enqueue_one(const fiona_plan *plan, const uint64_t *in_cts, const uint64_t *pt_diags,
                   const int8_t *ternary_groups, const uint64_t *scales, uint64_t *out_cts, uint32_t *words,
                   const CallBytes &b, hipStream_t stream) {
@@ -828,8 +833,8 @@ int enqueue_one(const fiona_plan *plan, const uint64_t *in_cts, const uint64_t *
   kp.splits = plan->d_splits;
   kp.pm = plan->d_pm;
   kp.words = words;
-  hipLaunchKernelGGL(kernel, dim3(plan->grid), dim3(plan->nw * 64), plan->lds_bytes + (own ? own_words_bytes(plan) : 0),
-                     stream, in_cts, pt_diags, out_cts, kp, plan->shape, pp, (const void *)((const char *)pt_diags + b.pt),
+  hipLaunchKernelGGL(kernel, dim3(plan->grid), dim3(plan->nw * 64), launch_lds(plan), stream,
+                     in_cts, pt_diags, out_cts, kp, plan->shape, pp, (const void *)((const char *)pt_diags + b.pt),
                      (const void *)((const char *)out_cts + b.out));
   if (hipGetLastError() != hipSuccess) return FIONA_ERR_HIP;
   return FIONA_OK;
@@ -917,7 +922,7 @@ int build_plan(const fiona_ctx *ctx, const fiona_layer_desc *d, uint64_t pitch, 
   P->st.segment_slots = P->n_seg_slots;
   P->st.output_rounds = P->n_rounds;
   P->st.output_buffer_rows = P->obuf_rows;
-  P->st.lds_bytes = P->lds_bytes;
+  P->st.lds_bytes = launch_lds(P);
   P->st.grid = P->grid;
   P->st.input_passes = 1;
   KShape &k = P->shape;
@@ -1022,7 +1027,7 @@ int build_passes(const fiona_ctx *ctx, const fiona_layer_desc *d, uint64_t pitch
     st.addsub_partial += a.addsub_partial;
     st.tile = a.tile;
     st.waves = std::max(st.waves, a.waves);
-    st.lds_bytes = std::max(st.lds_bytes, a.lds_bytes);
+    st.lds_bytes = std::max(st.lds_bytes, launch_lds(S));   // (a later pass packs no blocks of its own)
     st.grid = a.grid;
     st.split_outputs += a.split_outputs;
     st.segment_slots = std::max(st.segment_slots, a.segment_slots);

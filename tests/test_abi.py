@@ -208,6 +208,19 @@ def test_config_plans(name):
     assert nb["lds_bytes"] == st["lds_bytes"] - st["output_buffer_rows"] * 1024
 
 
+@pytest.mark.parametrize("n_out,T,own", [(9, 12, True), (16, 24, False)])
+def test_lds_bytes_are_the_launch_s(n_out, T, own):
+    """A small layer's workgroups pack their word blocks (256 bytes each) into their own LDS,
+    up to two a wavefront: the stat counts them."""
+    cfg = synth.LayerConfig("w", N=130, L=2, n_in=8, n_out=n_out, T=T, g=4, ternary=1.0)
+    lay = synth.make_layer(cfg, 5, moduli=synth.ntt_primes(256, 2))
+    st = fiona.Plan.from_layer(fiona.Ctx(lay.N, lay.L, lay.moduli), lay, flags=HOST).stats()
+    rows = (lay.n_in + st["n_partial"] + st["n_sum_resident"] + st["segment_slots"] + 1 + st["output_buffer_rows"])
+    blocks = st["n_partial"] + st["n_sum_resident"] + st["n_use"]
+    assert (blocks <= 2 * st["waves"]) == own
+    assert st["lds_bytes"] == rows * 1024 + (blocks * 256 if own else 0)
+
+
 def test_output_rounds_split_evenly():
     """Consecutive outputs go to rounds of at most the free LDS rows; 150 outputs
     over 64 inputs (95 free rows) make two rounds of 75; 9 free rows force 17."""
