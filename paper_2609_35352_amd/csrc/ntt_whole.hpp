@@ -5,16 +5,17 @@
 // What bounds the passes of ntt_kernel.hpp at these sizes is their number: a
 // launch costs the host 3.3 us and the GPU 4 to 5 us however small it is, and
 // at larger counts their intermediates and the half of their threads that a
-// side of 128 leaves idle.  Measured, passes -> one launch: rescale at L = 6 of
-// 4 / 128 ciphertexts, N = 2^10 17.0 -> 6.9 / 30.2 -> 14.6 us, 2^12 17.2 -> 9.9
-// / 66.3 -> 32.8, 2^13 17.6 -> 15.7 / 104 -> 58; rotations at L = 6, 4 / 64 of
-// them, N = 2^11 43.0 -> 24.2 / 81.3 -> 64.2, 2^12 43.1 -> 31.3 / 102 -> 82.
+// side of 128 leaves idle.  Measured when the passes went there too, passes ->
+// one launch: rescale at L = 6 of 4 / 128 ciphertexts, N = 2^10 17.0 -> 6.9 /
+// 30.2 -> 14.6 us, 2^12 17.2 -> 9.9 / 66.3 -> 32.8, 2^13 17.6 -> 15.7 / 104 -> 58;
+// rotations at L = 6, 4 / 64 of them, N = 2^11 43.0 -> 24.2 / 81.3 -> 64.2, 2^12
+// 43.1 -> 31.3 / 102 -> 82.
 //
 // The four-step transform of ntt_kernel.hpp with its intermediate in LDS: the
 // N1 columns of N2 words lie padded_len(N2) apart, and every step works in
 // place, so that no word leaves the CU between the first load and the last
 // store.  A workgroup transforms one vector back to its coefficients, keeps
-// them in registers (16 a thread), and transforms them forward under the
+// them in registers (4, 8 or 16 a thread), and transforms them forward under the
 // moduli of its group, one after the other.  Splitting the moduli over several
 // groups repeats the inverse transform in each, which a small call pays for
 // idle CUs (whole_groups).
@@ -280,6 +281,8 @@ __device__ __forceinline__ void whole_forward(double *xs, Tw *tw_a, Tw *tw_b, co
   whole_middle<LN, true>(xs, tw_a, S);
 }
 
+// (four waves per SIMD: 1,024 threads are as many.  It leaves 128 registers, and
+// whole_divide_kernel<13> spills five words a thread.)
 #define FIONA_WHOLE_KERNEL(LN) \
   __global__ void __launch_bounds__(Whole<LN>::T) __attribute__((amdgpu_waves_per_eu(4)))
 

@@ -24,12 +24,11 @@ using namespace fiona_host;
 
 // Intermediates of one launch pair, at most (chunk_size): the memory-side
 // cache's 256 MiB.  Limits of 128 / 192 / 256 / 320 / 416 MiB and none, us:
-// N = 2^16, L = 8, 128 ciphertexts 884 / 849 / 821 / 837 / 840 / 892; L = 16,
-// 128: 1776 / 1683 / 1619 / 1628 / 1677 / 1817; L = 12, 96: 1032 / 935 / 921 /
-// 911 / 934 / 1007; N = 2^15, L = 16, 128: 891 / 852 / 813 / 819 / 833 / 915;
-// N = 2^15, L = 8, 64 (one chunk from 256 on): 226 / 228 / 211 / 211 / 211 /
-// 208.  Of these the first was 932 and the last 249 with nontemporal stores,
-// one launch pair and pass B's vectors set by set.
+// N = 2^16, L = 8, 128 ciphertexts 889 / 839 / 808 / 824 / 829 / 886; L = 16,
+// 128: 1746 / 1659 / 1621 / 1640 / 1678 / 1811; L = 12, 96: 1024 / 933 / 923 /
+// 916 / 942 / 1014; L = 32, 24: 714 / 644 / 627 / 615 / 632 / 660; N = 2^15,
+// L = 16, 128: 890 / 850 / 812 / 819 / 835 / 923; N = 2^15, L = 8, 64 (one chunk
+// from 256 on): 221 / 220 / 205 / 205 / 205 / 206.
 constexpr size_t kTmpBytes = (size_t)256 << 20;
 
 struct fiona_rescaler {
@@ -47,8 +46,11 @@ namespace {
 
 // Whether V vectors go as one launch of whole transforms (ntt_whole.hpp): up
 // to N = 2^13 always; at 2^14, where a workgroup fills a CU, from 160 forward
-// transforms on (L = 6, 16 ciphertexts, 160 of them: 32.5 us in passes, 31.9
-// whole; 128 ciphertexts 186 and 116; but 4, 40 of them, 21.2 and 28.9).
+// transforms on.  In passes / whole, us: L = 6, 4 ciphertexts (40 transforms)
+// 21.0 / 28.9, 12 (120) 28.6 / 31.1, 16 (160) 32.9 / 32.1, 128 162 / 119; L = 16,
+// 5 (150) 30.3 / 32.5, 6 (180) 34.5 / 33.7, 12 (360) 54.5 / 51.9, but 9 (270, one
+// group too many for a turn of 256 workgroups) 45.3 / 48.6; L = 2, 60 (120)
+// 36.7 / 31.6, 80 (160) 46.7 / 32.5.
 constexpr uint32_t kWholeAlways = 13, kWholeMax = 14, kWholeTransforms = 160;
 static_assert(kWholeAlways + 1 >= kPassMinLogN, "no passes are built for smaller rings");
 bool use_whole(const fiona_rescaler *R, uint32_t V) {

@@ -298,12 +298,13 @@ struct fiona_rotator {
 namespace {
 
 // Which steps of a call go as launches of whole transforms (ntt_whole.hpp).
-// The digits up to N = 2^12 (one rotation at 2^12, L = 6: 42.6 us in passes,
-// 34.5 whole; at 2^13 within 3% of each other, 7 rotations at L = 4 44.8 and
-// 46.3; at 2^14 51.6 and 61.1: a workgroup's chain of two transforms).  The
-// division by P up to N = 2^12, and at 2^13 from 256 forward transforms on (L =
-// 6, 64 rotations, 768 of them: 170 us in passes, 158 whole; 4 rotations, 48 of
-// them, 45.3 and 49.5).
+// The digits up to N = 2^12 (one rotation at 2^12, L = 6: 42.6 us when they went
+// in passes, 34.5 whole); above, in passes / whole: 2^13, L = 4, 7 rotations
+// 43.7 / 45.6, L = 8, 4 50.2 / 49.3, L = 16, 4 83.6 / 84.1; 2^14, L = 4, 7 54.5 /
+// 66.4: a workgroup's chain of two transforms.  The division by P up to
+// N = 2^12, and at 2^13 from 256 forward transforms on: L = 6, 4 rotations (48
+// transforms) 43.4 / 48.4, 16 (192) 65.5 / 65.8, 21 (252) 78.3 / 75.1, 22 (264)
+// 80.7 / 83.1, 32 (384) 99.2 / 97.7, 64 (768) 166 / 159; L = 16, 24 (768) 244 / 252.
 constexpr uint32_t kDigitsMax = 12, kDivideAlways = 12, kDivideMax = 13, kDivideTransforms = 256;
 static_assert(kDigitsMax + 1 >= kPassMinLogN && kDivideAlways + 1 >= kPassMinLogN, "no passes are built for smaller rings");
 bool whole_digits(const fiona_rotator *R) { return R->log_n1 + R->log_n2 <= kDigitsMax; }
@@ -322,9 +323,9 @@ size_t tmp_vec_bytes(const fiona_rotator *R) {
 // Intermediates of one chunk of the division, at most: more than the rescale's
 // (rescale.hip), as here only the division's launches repeat and u' passes
 // through the memory-side cache as well.  Limits of 192 / 256 / 416 MiB and
-// none, us: 63 rotations at N = 2^16, L = 8 1425 / 1433 / 1408 / 1470 (1487
-// with nontemporal stores and pass B's vectors set by set); 100 at 2^15, L = 5
-// 711 / 710 / 699 / 691; 31 at 2^16, L = 12 1437 / 1411 / 1414 / 1417.
+// none, us: 63 rotations at N = 2^16, L = 8 1417 / 1426 / 1389 / 1446; 100 at
+// 2^15, L = 5 707 / 713 / 698 / 694; 31 at 2^16, L = 12 1435 / 1426 / 1414 /
+// 1417; 40 at L = 16 2777 / 2803 / 2797 / 2791.
 constexpr size_t kTmpBytes = (size_t)416 << 20;
 
 // Vectors of the division by P that one chunk holds, of a call's V.
@@ -445,9 +446,9 @@ void rotator_place(fiona_rotator *R, const TableImage &img, void *dev) {
 
 // The passes' division reads c0 in natural order, words sqrt(N) apart, while
 // it has few words to read that way; more than these take a transposed copy, a
-// launch of 4 us that then pays (L = 6, N = 2^13: 4 rotations 45.5 us with the
-// copy, 43.4 without; 2^14: 7 71.1 and 69.0, 16 103.5 and 107.4; 2^16: 1 102.9
-// and 98.9, 4 139.0 and 140.0).
+// launch of 4 us that then pays.  With the copy / without, us, L = 6: N = 2^13, 4
+// rotations 44.9 / 43.2, 16 65.2 / 65.5; 2^14, 7 70.0 / 69.2, 16 102.2 / 103.6;
+// 2^15, 4 85.5 / 82.1, 5 90.5 / 89.9; 2^16, 1 96.4 / 92.0, 4 130.7 / 130.8.
 constexpr uint64_t kC0NaturalWords = 1u << 17;
 
 // Digits: reads c1, writes every digit's transforms.
