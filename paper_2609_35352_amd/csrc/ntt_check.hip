@@ -274,10 +274,11 @@ bool whole(Checker &C, const WholeLaunch &L) {
   auto bytes = [](Off o) { return ((uint64_t)o.v + o.s) % 8 ? ~0ull : ((uint64_t)o.v + o.s) / 8; };
   for (const bool fwd : {false, true})
     if (!step("first groups", W::WORDS, W::T, A::E1, [&](uint32_t t, uint32_t u) {
-          return G::first(G::col1(t), G::grp1(t), u, fwd);
+          const uint32_t n1 = G::col1(t), ip = G::grp1(t);
+          return fwd ? G::first_fwd(n1, ip, u) : G::first_inv(n1, A::rev2(ip), u);
         }) ||
         !step("pass A's last groups", W::WORDS, G::IT2, A::E2, [&](uint32_t it, uint32_t e) {
-          return G::last_a(G::col2(it), G::off2(it), e, fwd);
+          return G::last_a(G::col2(it), G::off2(it), A::rev1(G::off2(it)), e, fwd);
         }))
       return false;
   if (!step("pass B's reads", W::WORDS, G::IT3, B::E1,

@@ -77,18 +77,23 @@ struct GeomWhole {
     const uint32_t n = coef(n1, ip, A::rev1(u));
     return (trans ? (n % N2) * N1 + n / N2 : n) * 8;
   }
-  static __host__ __device__ constexpr uint32_t first(uint32_t n1, uint32_t ip, uint32_t u, bool fwd) {
-    return at(fwd ? u * A::E2 + ip : A::E1 * A::rev2(ip) + u, n1);
+  // (inverse: i = rev2(i'))
+  static __host__ __device__ constexpr uint32_t first_inv(uint32_t n1, uint32_t i, uint32_t u) {
+    return at(A::E1 * i + u, n1);
   }
-  // pass A's last groups, loop index it < N / A::E2: column, and o of the outputs k2 = o + E1 u
+  static __host__ __device__ constexpr uint32_t first_fwd(uint32_t n1, uint32_t ip, uint32_t u) {
+    return at(u * A::E2 + ip, n1);
+  }
+  // pass A's last groups, loop index it < N / A::E2: column, and o of the outputs
+  // k2 = o + E1 u (forward: words of block j = rev1(o))
   static constexpr uint32_t IT2 = N / A::E2;
   static __host__ __device__ constexpr uint32_t col2(uint32_t it) { return it % N1; }
   static __host__ __device__ constexpr uint32_t off2(uint32_t it) { return it / N1; }
   static __host__ __device__ constexpr Off mid(uint32_t c, uint32_t o, uint32_t u) {
     return Off{(((c / kNttCols) * N2 + o) * kNttCols + c % kNttCols) * 8, A::E1 * u * kNttCols * 8};
   }
-  static __host__ __device__ constexpr uint32_t last_a(uint32_t c, uint32_t o, uint32_t e, bool fwd) {
-    return at(fwd ? A::rev1(o) * A::E2 + e : o + A::E1 * e, c);
+  static __host__ __device__ constexpr uint32_t last_a(uint32_t c, uint32_t o, uint32_t j, uint32_t e, bool fwd) {
+    return at(fwd ? j * A::E2 + e : o + A::E1 * e, c);
   }
   // pass B's first groups, it < N / B::E1: row position p and group i'; word u read and written
   static constexpr uint32_t IT3 = N / B::E1;
@@ -170,7 +175,7 @@ __device__ __forceinline__ void whole_middle(double *xs, const Tw *tw_a, const N
   __syncthreads();
 #pragma unroll 1
   for (uint32_t it = threadIdx.x; it < G::IT2; it += W::T) {
-    const uint32_t c = G::col2(it), o = G::off2(it);
+    const uint32_t c = G::col2(it), o = G::off2(it), j = A::rev1(o);
     double m[A::E2], r[A::E2];
 #pragma unroll
     for (uint32_t u = 0; u < A::E2; ++u) {
@@ -178,13 +183,13 @@ __device__ __forceinline__ void whole_middle(double *xs, const Tw *tw_a, const N
       m[u] = mid.f64(om.v, om.s);
     }
 #pragma unroll
-    for (uint32_t e = 0; e < A::E2; ++e) r[e] = xs[G::last_a(c, o, e, FWD)];
-    if constexpr (FWD) tree_butterflies<A::R1, A::R2>(r, A::rev1(o), [&](uint32_t t) { return tw_a[t]; }, q);
+    for (uint32_t e = 0; e < A::E2; ++e) r[e] = xs[G::last_a(c, o, j, e, FWD)];
+    if constexpr (FWD) tree_butterflies<A::R1, A::R2>(r, j, [&](uint32_t t) { return tw_a[t]; }, q);
     else butterflies<W::LOG2, A::R1, A::R2>(r, o, [&](uint32_t t) { return tw_a[t]; }, q, qinv);
 #pragma unroll
     for (uint32_t e = 0; e < A::E2; ++e) {
       const double w = m[FWD ? A::rev2(e) : e];
-      xs[G::last_a(c, o, e, FWD)] = mul_tw(r[e], Tw{w, w * qinv}, q);
+      xs[G::last_a(c, o, j, e, FWD)] = mul_tw(r[e], Tw{w, w * qinv}, q);
     }
   }
   __syncthreads();
@@ -234,8 +239,9 @@ __device__ __forceinline__ void whole_inverse(double *xs, Tw *tw_a, Tw *tw_b, co
 #pragma unroll
     for (uint32_t u = 0; u < A::E1; ++u) r[u] = to_f64(x[u]);
     whole_first<W::LOG2>(r, S.dft_a, q, qinv);
+    const uint32_t i = A::rev2(ip);
 #pragma unroll
-    for (uint32_t u = 0; u < A::E1; ++u) xs[G::first(n1, ip, u, false)] = reduce(r[u], q, qinv);
+    for (uint32_t u = 0; u < A::E1; ++u) xs[G::first_inv(n1, i, u)] = reduce(r[u], q, qinv);
   }
   whole_middle<LN, false>(xs, tw_a, S);
   const Buf post(S.post, S.post + W::N1);
@@ -277,7 +283,7 @@ __device__ __forceinline__ void whole_forward(double *xs, Tw *tw_a, Tw *tw_b, co
   const Tw *__restrict__ tree = S.dft_a;
   tree_butterflies<0, A::R1>(r, 0, [&](uint32_t t) { return tree[t]; }, S.q);
 #pragma unroll
-  for (uint32_t v = 0; v < A::E1; ++v) xs[G::first(n1, ip, v, true)] = reduce(r[v], S.q, S.qinv);
+  for (uint32_t v = 0; v < A::E1; ++v) xs[G::first_fwd(n1, ip, v)] = reduce(r[v], S.q, S.qinv);
   whole_middle<LN, true>(xs, tw_a, S);
 }
 
